@@ -1,0 +1,79 @@
+"""GPU parity at the sizes where a kernel or a branch of a launch can go wrong:
+tile edges, remainders, the smallest and largest of a range, both sides of a
+rule on sizes.  Integer results and fixed-order fp32 results are compared with
+the CPU oracle bit for bit; other bounds are derived where they are used."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_17652_amd as F
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+D = 128
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    F.lib()
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def status(st):
+    torch.cuda.synchronize()
+    return int(st.item()) & 0xFFFFFFFF
+
+
+def threshold_keys(rng, n, kdt):
+    """Keys on and one unit in the last place beside the cell boundaries T * s of
+    their block, signed zeros, and magnitudes far below a cell."""
+    K = (rng.standard_normal((n, D)) * np.exp(rng.standard_normal(D))).astype(kdt)
+    for c in range(0, D, 3):
+        a = np.float16(np.exp(rng.uniform(-6, 6)))
+        s = np.float32(a) / np.float32(8)
+        k = (rng.integers(-8, 9, n) * s).astype(kdt)
+        side = rng.integers(-1, 2, n)
+        k = np.where(side == 0, k, np.nextafter(k, np.where(side > 0, np.inf, -np.inf).astype(kdt), dtype=kdt))
+        tiny = rng.random(n) < 0.2
+        k[tiny] = (rng.choice([-1.0, 1.0, -0.0, 0.0], tiny.sum()) * s * 2.0 ** rng.integers(-30, -10, tiny.sum())).astype(kdt)
+        k[::64] = np.float32(a)  # the block maximum
+        K[:, c] = np.clip(k, -np.float32(a), np.float32(a)).astype(kdt)
+    return K
+
+
+@pytest.mark.parametrize("kdt", [np.float32, np.float16])
+@pytest.mark.parametrize("U,nb_cap,ld", [(52, 67, 128), (3, 67, 160), (17, 256, 128)])
+def test_pack_tiles(kdt, U, nb_cap, ld):
+    """Workgroups of 16 blocks (the first and the last shape) and one wave per
+    item (the second) at odd block strides: ragged ends inside a tile, empty
+    units, padded rows, keys at the cell boundaries, NaN and infinite keys."""
+    rng = np.random.default_rng(7 * U + nb_cap)
+    cap = nb_cap * 64
+    ns = [int(x) for x in rng.integers(0, cap + 1, U)]
+    ns[:3] = [cap, cap - 1, 1023]
+    if U > 6:
+        ns[3:7] = [0, 1, 1024, 1025]
+    K = torch.full((U, cap, ld), float("nan"), dtype=torch.float32 if kdt == np.float32 else torch.float16, device=DEV)
+    host = {}
+    for u in range(min(U, 7)):
+        k = threshold_keys(rng, ns[u], kdt)
+        if u == 2:
+            k[70, 5], k[71, 6], k[200, 5], k[1000, 9] = np.nan, np.inf, -np.inf, np.nan
+        host[u] = k
+        K[u, :ns[u], :D] = dev(k)
+    for u in range(7, U):
+        K[u, :ns[u], :D] = torch.randn((ns[u], D), device=DEV).to(K.dtype)
+    st = F.new_status()
+    planes, scales = F.fathom_pack(K[:, :, :D], dev(np.array(ns, np.int64)), nb_cap=nb_cap, dev_status=st)
+    assert status(st) == (F.FATHOM_DEV_NONFINITE | F.FATHOM_DEV_SCALE_OVERFLOW)
+    for u, k in host.items():
+        op, os_, _ = oracle.pack(k.astype(np.float32), nb_cap=nb_cap)
+        assert np.array_equal(scales[u].cpu().numpy().view(np.uint16), os_), f"scales unit {u} n={ns[u]}"
+        assert np.array_equal(planes[u].cpu().numpy().view(np.uint64), op), f"planes unit {u} n={ns[u]}"
