@@ -32,9 +32,7 @@ constexpr int kEigThreads = 1024;
 constexpr int kEigPitch = kD + 1;     // LDS row pitch (column sweeps are conflict free)
 constexpr int kJacobiSweeps = 12;     // fp32 cyclic Jacobi on 128 x 128 converges in fewer
 constexpr int kRotThreads = 256;
-constexpr int kRotTile = 64;          // tokens per rotation tile
-constexpr int kRotTilesPerWG = 4;
-constexpr int kRotPitch = kRotTile + 4;  // transposed tile row: 16-byte aligned, fewer bank conflicts
+constexpr int kRotTokens = 4;         // tokens a wave rotates at a time
 
 size_t klt_ws_bytes(int U) {
   const size_t ms = (size_t)U * kCalChunks * kD * sizeof(double);
@@ -237,56 +235,116 @@ __global__ __launch_bounds__(kEigThreads) void klt_eig_kernel(const int64_t* __r
 }
 
 // ---------------------------------------------------------------- rotations
-template <typename KT>
-__global__ __launch_bounds__(kRotThreads) void klt_rotate_keys_kernel(const KT* __restrict__ K, int64_t ld_tok,
-                                                                     int64_t ld_unit, const int64_t* __restrict__ n,
-                                                                     int64_t n_cap, const float* __restrict__ mu,
-                                                                     const float* __restrict__ V,
-                                                                     float* __restrict__ out, int64_t ld_out,
-                                                                     uint32_t* __restrict__ st) {
-  __shared__ float Vs[kD * kD];
-  __shared__ __attribute__((aligned(16))) float dT[kD * kRotPitch];  // [channel][token]
-  const int u = blockIdx.y, tid = threadIdx.x;
-  const int64_t nu = unit_tokens(n, u, n_cap, (blockIdx.x == 0 && tid == 0) ? st : nullptr);
-  const int64_t base = (int64_t)blockIdx.x * kRotTile * kRotTilesPerWG;
-  if (base >= nu) return;
-  const float* Vu = V + (int64_t)u * kD * kD;
-  for (int e = tid; e < kD * kD; e += kRotThreads) Vs[e] = Vu[e];
-  const int ch = tid & (kD - 1), hf = tid >> 7;
-  const float muc = mu[(int64_t)u * kD + ch];
-  const KT* Ku = K + (int64_t)u * ld_unit;
-  float* Ou = out + (int64_t)u * ld_out;
-  for (int tt = 0; tt < kRotTilesPerWG; ++tt) {
-    const int64_t t0 = base + (int64_t)tt * kRotTile;
-    if (t0 >= nu) break;
-    __syncthreads();  // Vs written / previous tile's reads done
-    // centred tile, transposed: thread (ch, hf) takes tokens hf, hf + 2, ...
-    for (int r = hf; r < kRotTile; r += 2) {
-      const float k = t0 + r < nu ? key_at(Ku + (t0 + r) * ld_tok + ch) : 0.0f;
-      dT[ch * kRotPitch + r] = __fsub_rn(k, muc);
-    }
-    __syncthreads();
-    // thread (c = ch, tokens 32 hf .. 32 hf + 31): acc over j ascending
-    float acc[kRotTile / 2];
+// The fixed order allows no fused multiply-add, so the contraction is 2 VALU
+// operations per (token, j, channel) at best; everything else is kept out of
+// the loop.  A wave owns 64 channels and holds its half of V in registers (lane
+// = channel, 128 VGPRs); of a token row every 16 lanes hold a copy (8 channels a
+// lane), and the multiply broadcasts d_j from lane j / 8 of each row by its
+// DPP operand: no LDS, no scalar moves, four tokens' chains interleaved.
+// 8 x 131072 fp16 keys: 0.98 ms, of which the two operations are 0.87 (V and
+// the keys through LDS, one wave per SIMD, before: 2.70 ms).
+template <typename KT, bool VEC>
+struct RotRow {  // 8 consecutive channels of one token, as read
+  uint32_t w[2 * sizeof(KT)];
+  __device__ __forceinline__ void load(const KT* p) {
+    if constexpr (VEC) {
 #pragma unroll
-    for (int i = 0; i < kRotTile / 2; ++i) acc[i] = 0.0f;
-    for (int j = 0; j < kD; ++j) {
-      const float v = Vs[j * kD + ch];
-      const float4* dr = reinterpret_cast<const float4*>(&dT[j * kRotPitch + 32 * hf]);
+      for (int i = 0; i < (int)sizeof(KT) / 2; ++i) {
+        const uint4 r = reinterpret_cast<const uint4*>(p)[i];
+        w[4 * i] = r.x; w[4 * i + 1] = r.y; w[4 * i + 2] = r.z; w[4 * i + 3] = r.w;
+      }
+    } else {
 #pragma unroll
-      for (int i4 = 0; i4 < kRotTile / 8; ++i4) {
-        const float4 d = dr[i4];
-        acc[4 * i4] = __fadd_rn(acc[4 * i4], __fmul_rn(d.x, v));
-        acc[4 * i4 + 1] = __fadd_rn(acc[4 * i4 + 1], __fmul_rn(d.y, v));
-        acc[4 * i4 + 2] = __fadd_rn(acc[4 * i4 + 2], __fmul_rn(d.z, v));
-        acc[4 * i4 + 3] = __fadd_rn(acc[4 * i4 + 3], __fmul_rn(d.w, v));
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (sizeof(KT) == 4) {
+          w[e] = *(const __attribute__((address_space(1))) uint32_t*)(p + e);
+        } else {
+          const uint32_t h = *(const __attribute__((address_space(1))) uint16_t*)(p + e);
+          w[e >> 1] = (e & 1) ? w[e >> 1] | (h << 16) : h;
+        }
       }
     }
+  }
+  __device__ __forceinline__ float at(int e) const {
+    if constexpr (sizeof(KT) == 4) return __uint_as_float(w[e]);
+    return half_bits_to_float((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+  }
+};
+
+// acc[t] += pr[t], then pr[t] = d[t] of lane X of each row of 16 times v.  The
+// four additions stand first, so that a register written just before has the
+// two wait states that a DPP read needs.
+template <int X>
+__device__ __forceinline__ void rot_step(float (&acc)[kRotTokens], float (&pr)[kRotTokens], float d0, float d1,
+                                         float d2, float d3, float v) {
+  static_assert(kRotTokens == 4, "one asm block per four tokens");
+  asm("v_add_f32 %0, %0, %4\n\t"
+      "v_add_f32 %1, %1, %5\n\t"
+      "v_add_f32 %2, %2, %6\n\t"
+      "v_add_f32 %3, %3, %7\n\t"
+      "v_mul_f32_dpp %4, %8, %12 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_mul_f32_dpp %5, %9, %12 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_mul_f32_dpp %6, %10, %12 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_mul_f32_dpp %7, %11, %12 row_newbcast:%13 row_mask:0xf bank_mask:0xf"
+      : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3]), "+&v"(pr[0]), "+&v"(pr[1]), "+&v"(pr[2]),
+        "+&v"(pr[3])
+      : "v"(d0), "v"(d1), "v"(d2), "v"(d3), "v"(v), "n"(X));
+}
+
+template <int X>
+__device__ __forceinline__ void rot_steps(const float (&d)[kRotTokens][8], const float (&v)[kD],
+                                          float (&acc)[kRotTokens], float (&pr)[kRotTokens]) {
+  if constexpr (X < 16) {
 #pragma unroll
-    for (int i = 0; i < kRotTile / 2; ++i) {
-      const int64_t t = t0 + 32 * hf + i;
-      if (t < nu) Ou[t * kD + ch] = acc[i];
+    for (int e = 0; e < 8; ++e) rot_step<X>(acc, pr, d[0][e], d[1][e], d[2][e], d[3][e], v[8 * X + e]);
+    rot_steps<X + 1>(d, v, acc, pr);
+  }
+}
+
+template <typename KT, bool VEC>
+__global__ __launch_bounds__(kRotThreads, 2) void klt_rotate_keys_kernel(const KT* __restrict__ K, int64_t ld_tok,
+                                                                        int64_t ld_unit, const int64_t* __restrict__ n,
+                                                                        int64_t n_cap, const float* __restrict__ mu,
+                                                                        const float* __restrict__ V,
+                                                                        float* __restrict__ out, int64_t ld_out,
+                                                                        int chunk, uint32_t* __restrict__ st) {
+  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t nu = unit_tokens(n, u, n_cap, (blockIdx.x == 0 && tid == 0) ? st : nullptr);
+  // two waves (the channel halves) share a run of chunk / 2 tokens
+  const int c = 64 * (wave & 1) + lane, x = lane & 15;
+  const int64_t t0 = (int64_t)blockIdx.x * chunk + (wave >> 1) * (chunk / 2);
+  const int64_t t1 = t0 + chunk / 2 < nu ? t0 + chunk / 2 : nu;
+  if (t0 >= t1) return;
+  const KT* Ku = K + (int64_t)u * ld_unit + 8 * x;
+  RotRow<KT, VEC> row[kRotTokens];
+#pragma unroll
+  for (int t = 0; t < kRotTokens; ++t) row[t].load(Ku + (t0 + t < t1 ? t0 + t : t1 - 1) * ld_tok);
+  float m[8], v[kD];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) m[e] = mu[(int64_t)u * kD + 8 * x + e];
+  const float* Vu = V + (int64_t)u * kD * kD + c;
+#pragma unroll
+  for (int j = 0; j < kD; ++j) v[j] = Vu[j * kD];
+  float* Ou = out + (int64_t)u * ld_out + c;
+  for (int64_t i = t0; i < t1; i += kRotTokens) {
+    float d[kRotTokens][8], acc[kRotTokens], pr[kRotTokens];
+#pragma unroll
+    for (int t = 0; t < kRotTokens; ++t) {
+      acc[t] = pr[t] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[t][e] = __fsub_rn(row[t].at(e), m[e]);
     }
+    // the next tokens' rows are in flight while these are rotated (past the end: the last row again)
+#pragma unroll
+    for (int t = 0; t < kRotTokens; ++t) {
+      const int64_t nx = i + kRotTokens + t;
+      row[t].load(Ku + (nx < t1 ? nx : t1 - 1) * ld_tok);
+    }
+    rot_steps<0>(d, v, acc, pr);
+#pragma unroll
+    for (int t = 0; t < kRotTokens; ++t)
+      if (i + t < t1) Ou[(i + t) * kD] = __fadd_rn(acc[t], pr[t]);
   }
 }
 
@@ -342,14 +400,30 @@ fathom_status launch_klt_rotate_keys(const void* K, fathom_dtype kdt, int64_t ld
                                      const int64_t* n, int64_t n_cap, int U, const float* mu, const float* V,
                                      float* out, int64_t ld_out, uint32_t* st, hipStream_t s) {
   if (U == 0 || n_cap == 0) return FATHOM_OK;
-  const int64_t per = (int64_t)kRotTile * kRotTilesPerWG;
-  const dim3 g((unsigned)((n_cap + per - 1) / per), (unsigned)U);
-  if (kdt == FATHOM_F32)
-    hipLaunchKernelGGL(klt_rotate_keys_kernel<float>, g, dim3(kRotThreads), 0, s,
-                       reinterpret_cast<const float*>(K), ld_tok, ld_unit, n, n_cap, mu, V, out, ld_out, st);
+  // Tokens per workgroup: about 2048 workgroups (four rounds of two per CU, so
+  // that one's loads of V run beside another's rotations and ragged units even
+  // out), of 16 to 512 tokens (at 512 a wave's 32 KB of V is 1 % of its time).
+  // One round only: 131072 keys 140 us against 134, 4 x 8346 keys 47 against 45.
+  int64_t chunk = (n_cap * U / 2048 + 15) & ~(int64_t)15;
+  chunk = chunk < 16 ? 16 : chunk > 512 ? 512 : chunk;
+  const dim3 g((unsigned)((n_cap + chunk - 1) / chunk), (unsigned)U);
+  // 16-byte row loads when every row start is 16-byte aligned
+  const int64_t vec = kdt == FATHOM_F32 ? 4 : 8;
+  const bool al = (reinterpret_cast<uintptr_t>(K) & 15) == 0 && ld_tok % vec == 0 && ld_unit % vec == 0;
+  const float* Kf = reinterpret_cast<const float*>(K);
+  const __half* Kh = reinterpret_cast<const __half*>(K);
+  if (kdt == FATHOM_F32 && al)
+    hipLaunchKernelGGL((klt_rotate_keys_kernel<float, true>), g, dim3(kRotThreads), 0, s, Kf, ld_tok, ld_unit, n, n_cap,
+                       mu, V, out, ld_out, (int)chunk, st);
+  else if (kdt == FATHOM_F32)
+    hipLaunchKernelGGL((klt_rotate_keys_kernel<float, false>), g, dim3(kRotThreads), 0, s, Kf, ld_tok, ld_unit, n,
+                       n_cap, mu, V, out, ld_out, (int)chunk, st);
+  else if (al)
+    hipLaunchKernelGGL((klt_rotate_keys_kernel<__half, true>), g, dim3(kRotThreads), 0, s, Kh, ld_tok, ld_unit, n,
+                       n_cap, mu, V, out, ld_out, (int)chunk, st);
   else
-    hipLaunchKernelGGL(klt_rotate_keys_kernel<__half>, g, dim3(kRotThreads), 0, s,
-                       reinterpret_cast<const __half*>(K), ld_tok, ld_unit, n, n_cap, mu, V, out, ld_out, st);
+    hipLaunchKernelGGL((klt_rotate_keys_kernel<__half, false>), g, dim3(kRotThreads), 0, s, Kh, ld_tok, ld_unit, n,
+                       n_cap, mu, V, out, ld_out, (int)chunk, st);
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;
 }

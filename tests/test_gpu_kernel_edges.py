@@ -77,3 +77,30 @@ def test_pack_tiles(kdt, U, nb_cap, ld):
         op, os_, _ = oracle.pack(k.astype(np.float32), nb_cap=nb_cap)
         assert np.array_equal(scales[u].cpu().numpy().view(np.uint16), os_), f"scales unit {u} n={ns[u]}"
         assert np.array_equal(planes[u].cpu().numpy().view(np.uint64), op), f"planes unit {u} n={ns[u]}"
+
+
+@pytest.mark.parametrize("kdt", [np.float32, np.float16])
+@pytest.mark.parametrize("U,cap,pad", [(3, 1, 0), (1, 8195, 0), (2, 4099, 3), (600, 17, 8), (1, 262200, 0)])
+def test_rotate_keys_runs(kdt, U, cap, pad):
+    """Runs of 16 to 512 tokens per workgroup with ragged last groups of four,
+    empty and one-token units, and rows whose stride rules out 16-byte loads
+    (pad 3); bit-exact to the oracle on sampled rows of every unit checked."""
+    rng = np.random.default_rng(U + cap)
+    ld = D + pad
+    tdt = torch.float32 if kdt == np.float32 else torch.float16
+    K = torch.randn((U, cap, ld), device=DEV).to(tdt)
+    ns = rng.integers(0, cap + 1, U)
+    ns[0] = cap
+    mu = rng.standard_normal((U, D)).astype(np.float32)
+    V = rng.standard_normal((U, D, D)).astype(np.float32)
+    st = F.new_status()
+    out = torch.full((U, cap, D), 7.0, device=DEV)
+    F.fathom_klt_rotate_keys(K[:, :, :D], dev(ns.astype(np.int64)), dev(mu), dev(V), out=out, dev_status=st)
+    assert status(st) == 0
+    for u in sorted({0, U // 2, U - 1}):
+        n = int(ns[u])
+        rows = np.unique(np.concatenate([np.arange(min(n, 600)), np.arange(max(0, n - 600), n)])).astype(np.int64)
+        got = out[u, dev(rows)].cpu().numpy()
+        ref = oracle.klt_rotate_keys(K[u, dev(rows), :D].cpu().numpy(), mu[u], V[u])
+        assert np.array_equal(got.view(np.uint32), ref.view(np.uint32)), (u, n)
+        assert bool((out[u, n:] == 7.0).all())  # rows past n are left as they were
