@@ -5,12 +5,11 @@
 // allocation and scan run on rotated keys, rotated queries and var = lambda.
 //
 // fathom_klt_calibrate (one-time, per unit; the unit's own keys calibrate):
-//   klt_mean_kernel   kCalChunks token chunks per unit, fp64 channel sums.
-//   klt_cov_kernel    the same chunks: fp64 sums of centred outer products,
-//                     8 x 8 entries per thread, 32-token tiles in LDS.
-//   klt_eig_kernel    one 1024-thread workgroup per unit: fixed-order sums of
-//                     the chunk partials, then cyclic Jacobi in fp32 with the
-//                     matrix and the basis in LDS -- each sweep is 127 rounds
+//   klt_cov_kernel    chunks of the keys: fp64 sums of y and y y^T, y the keys
+//                     shifted by the unit's first, on the fp64 matrix cores.
+//   klt_reduce_kernel the chunks' sums in chunk order: mean and covariance.
+//   klt_eig_kernel    one 1024-thread workgroup per unit: cyclic Jacobi in
+//                     fp32 with the matrix and the basis in LDS -- each sweep is 127 rounds
 //                     of 64 disjoint rotations (round-robin pairing), applied
 //                     to rows, then columns and the basis -- and finally the
 //                     columns ordered by eigenvalue (descending) with each
@@ -25,20 +24,16 @@
 
 namespace fathom {
 
-constexpr int kCalChunks = 32;        // token chunks per unit in the calibration sums
-constexpr int kCalThreads = 256;
-constexpr int kCovTile = 32;          // tokens per LDS tile in the covariance pass
+constexpr size_t kCalUnitBytes = (size_t)32 * kD * (kD + 1) * sizeof(double);  // calibration workspace of one unit
+constexpr int kCalChunks = 54;        // token chunks per unit in the calibration sums, at most (they fit the above)
 constexpr int kEigThreads = 1024;
 constexpr int kEigPitch = kD + 1;     // LDS row pitch (column sweeps are conflict free)
 constexpr int kJacobiSweeps = 12;     // fp32 cyclic Jacobi on 128 x 128 converges in fewer
 constexpr int kRotThreads = 256;
 constexpr int kRotTokens = 4;         // tokens a wave rotates at a time
 
-size_t klt_ws_bytes(int U) {
-  const size_t ms = (size_t)U * kCalChunks * kD * sizeof(double);
-  const size_t cs = (size_t)U * kCalChunks * kD * kD * sizeof(double);
-  return ((ms + 255) & ~(size_t)255) + cs;
-}
+// Per unit: the covariance (fp64, 128 KB) and up to kCalChunks chunks' sums.
+size_t klt_ws_bytes(int U) { return (size_t)U * kCalUnitBytes; }
 
 template <typename KT>
 __device__ __forceinline__ float key_at(const KT* p) {
@@ -46,118 +41,234 @@ __device__ __forceinline__ float key_at(const KT* p) {
   return half_bits_to_float(*(const __attribute__((address_space(1))) uint16_t*)p);
 }
 
-__device__ __forceinline__ void chunk_range(int64_t nu, int c, int64_t* t0, int64_t* t1) {
-  const int64_t cs = (nu + kCalChunks - 1) / kCalChunks;
+template <typename KT, bool VEC>
+struct KeyRow {  // 8 consecutive channels of one token, as read
+  uint32_t w[2 * sizeof(KT)];
+  __device__ __forceinline__ void load(const KT* p) {
+    if constexpr (VEC) {
+#pragma unroll
+      for (int i = 0; i < (int)sizeof(KT) / 2; ++i) {
+        const uint4 r = reinterpret_cast<const uint4*>(p)[i];
+        w[4 * i] = r.x; w[4 * i + 1] = r.y; w[4 * i + 2] = r.z; w[4 * i + 3] = r.w;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (sizeof(KT) == 4) {
+          w[e] = *(const __attribute__((address_space(1))) uint32_t*)(p + e);
+        } else {
+          const uint32_t h = *(const __attribute__((address_space(1))) uint16_t*)(p + e);
+          w[e >> 1] = (e & 1) ? w[e >> 1] | (h << 16) : h;
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ float at(int e) const {
+    if constexpr (sizeof(KT) == 4) return __uint_as_float(w[e]);
+    return half_bits_to_float((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+  }
+};
+
+// ---------------------------------------------------------------- calibration
+// Chunks of a unit's keys: one workgroup each, one round of the chip (a
+// workgroup per CU) where the workspace holds as many.
+static inline int cal_chunks(int U, int64_t n_cap) {
+  int64_t c = 256 / U;
+  const int64_t most = n_cap / 256 + 1;  // not under 256 keys each
+  c = c < most ? c : most;
+  return (int)(c < 1 ? 1 : c > kCalChunks ? kCalChunks : c);
+}
+
+__device__ __forceinline__ void chunk_range(int64_t nu, int nch, int c, int64_t* t0, int64_t* t1) {
+  const int64_t cs = (nu + nch - 1) / nch;
   *t0 = (int64_t)c * cs < nu ? (int64_t)c * cs : nu;
   *t1 = *t0 + cs < nu ? *t0 + cs : nu;
 }
 
-// ---------------------------------------------------------------- calibration
-template <typename KT>
-__global__ __launch_bounds__(kCalThreads) void klt_mean_kernel(const KT* __restrict__ K, int64_t ld_tok,
-                                                              int64_t ld_unit, const int64_t* __restrict__ n,
-                                                              int64_t n_cap, double* __restrict__ msum,
-                                                              uint32_t* __restrict__ st) {
-  __shared__ double half2[kD];
-  const int c = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
-  const int ch = tid & (kD - 1), hf = tid >> 7;
-  const int64_t nu = unit_tokens(n, u, n_cap, (c == 0 && tid == 0) ? st : nullptr);
-  int64_t t0, t1;
-  chunk_range(nu, c, &t0, &t1);
-  const KT* Ku = K + (int64_t)u * ld_unit + ch;
-  double s = 0.0;
-  int64_t i = t0 + hf;
-  for (; i + 14 < t1; i += 16) {  // 8 loads in flight
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = key_at(Ku + (i + 2 * e) * ld_tok);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s += (double)v[e];
-  }
-  for (; i < t1; i += 2) s += (double)key_at(Ku + i * ld_tok);
-  if (hf == 1) half2[ch] = s;
-  __syncthreads();
-  if (hf == 0) msum[((int64_t)u * kCalChunks + c) * kD + ch] = s + half2[ch];
+// fp64 sums of y and y y^T over a chunk, y = k - (the unit's first key), in one
+// pass over the keys: shifting by a key keeps the covariance sum(y y^T) / n -
+// mean(y) mean(y)^T free of cancellation however far the mean lies from zero.
+// v_mfma_f64_16x16x4_f64 over 4 tokens a step: with channel 8 i + b at index i
+// of channel block b, the A and the B operand of block b are the same register
+// (lane (i, token)), a lane loads its 8 channels as one run, and no operand goes
+// through LDS.  Only the 36 tiles with bi <= bj are formed, 18 in each of a
+// pair of waves (144 accumulator registers, two waves per SIMD); four pairs
+// take every fourth step and add up through LDS in a fixed order.
+// Bound by the fp64 matrix rate (the 36 tiles: 0.25 ms at 78.6 TFLOP/s for 8 x
+// 131072 keys): 0.35 ms (full 128 x 128 products from LDS operands and a
+// pass of its own for the mean, before: 1.93 ms).
+constexpr int kCovTiles = 36;
+constexpr int kCovHalf = kCovTiles / 2;
+constexpr int kCovPairs = 4;
+constexpr int kCovThreads = 2 * kCovPairs * kWave;
+constexpr size_t kPartDoubles = (size_t)kCovTiles * 256 + kD;  // of one chunk: tiles as the lanes hold them, sums
+static_assert((kD * kD + kCalChunks * kPartDoubles) * sizeof(double) <= kCalUnitBytes, "calibration workspace");
+typedef double v4f64 __attribute__((ext_vector_type(4)));
+
+__host__ __device__ constexpr int tile_row(int t) {  // tile t of the upper triangle in row order: its block row
+  int r = 0;
+  while (t >= 8 - r) t -= 8 - r++;
+  return r;
+}
+__host__ __device__ constexpr int tile_col(int t) {
+  int r = 0;
+  while (t >= 8 - r) t -= 8 - r++;
+  return r + t;
 }
 
-template <typename KT>
-__global__ __launch_bounds__(kCalThreads) void klt_cov_kernel(const KT* __restrict__ K, int64_t ld_tok,
-                                                             int64_t ld_unit, const int64_t* __restrict__ n,
-                                                             int64_t n_cap, const double* __restrict__ msum,
-                                                             double* __restrict__ cpart) {
-  __shared__ double mu[kD];
-  __shared__ double tile[kCovTile][kD];
-  const int c = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
-  int64_t nu = n[u];
-  if (nu < 0 || nu > n_cap) nu = 0;  // flagged by the mean pass
-  if (tid < kD) {
-    double s = 0.0;
-    for (int x = 0; x < kCalChunks; ++x) s += msum[((int64_t)u * kCalChunks + x) * kD + tid];
-    mu[tid] = nu > 0 ? s / (double)nu : 0.0;
+template <int HALF, int T>
+__device__ __forceinline__ void cov_tiles(v4f64 (&acc)[kCovHalf], const double (&y)[8]) {
+  if constexpr (T < kCovHalf) {
+    constexpr int r = tile_row(HALF * kCovHalf + T), c = tile_col(HALF * kCovHalf + T);
+    acc[T] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[r], y[c], acc[T], 0, 0, 0);
+    cov_tiles<HALF, T + 1>(acc, y);
   }
-  __syncthreads();
-  int64_t t0, t1;
-  chunk_range(nu, c, &t0, &t1);
-  const int jb = 8 * (tid >> 4), lb = 8 * (tid & 15);
-  double acc[8][8];
+}
+
+template <int HALF, typename KT, bool VEC>
+__device__ __forceinline__ void cov_wave(const KT* Ku, int64_t ld_tok, int64_t t0, int64_t t1, int pair, double* red,
+                                         double* out) {
+  const int lane = threadIdx.x & 63, x = lane & 15, g = lane >> 4;
+  const KT* p = Ku + 8 * x;
+  KeyRow<KT, VEC> row;
+  double shift[8], sum[8];
+  v4f64 acc[kCovHalf];
+  row.load(p);  // the first key
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+  for (int b = 0; b < 8; ++b) {
+    shift[b] = (double)row.at(b);
+    sum[b] = 0.0;
+  }
 #pragma unroll
-    for (int b = 0; b < 8; ++b) acc[a][b] = 0.0;
-  const KT* Ku = K + (int64_t)u * ld_unit;
-  for (int64_t b0 = t0; b0 < t1; b0 += kCovTile) {
-    // centred tile (rows past the chunk are zero and add nothing)
-    for (int e = tid; e < kCovTile * kD; e += kCalThreads) {
-      const int r = e / kD, x = e % kD;
-      tile[r][x] = b0 + r < t1 ? (double)key_at(Ku + (b0 + r) * ld_tok + x) - mu[x] : 0.0;
+  for (int t = 0; t < kCovHalf; ++t) acc[t] = (v4f64){0.0, 0.0, 0.0, 0.0};
+  int64_t i = t0 + 4 * pair + g;
+  if (t0 < t1) row.load(p + (i < t1 ? i : t1 - 1) * ld_tok);
+  for (int64_t s = t0 + 4 * pair; s < t1; s += 4 * kCovPairs) {
+    double y[8];
+    const bool valid = i < t1;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) y[b] = valid ? (double)row.at(b) - shift[b] : 0.0;
+    i += 4 * kCovPairs;
+    row.load(p + (i < t1 ? i : t1 - 1) * ld_tok);  // the next step's keys
+    if (HALF == 0) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) sum[b] += y[b];
     }
-    __syncthreads();
-    for (int r = 0; r < kCovTile; ++r) {
-      double dj[8], dl[8];
+    cov_tiles<HALF, 0>(acc, y);
+  }
+  // ---- add up the four pairs: the others hand theirs to the first, in order ----
+  double* mine = red + HALF * (kCovHalf * 256 + kD) + lane;
+  for (int w = 1; w < kCovPairs; ++w) {
+    if (pair == w) {
 #pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        dj[a] = tile[r][jb + a];
-        dl[a] = tile[r][lb + a];
+      for (int t = 0; t < kCovHalf; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[(4 * t + r) * 64] = acc[t][r];
+      if (HALF == 0) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          sum[b] += __shfl_xor(sum[b], 16, kWave);
+          sum[b] += __shfl_xor(sum[b], 32, kWave);
+          if (g == 0) red[kCovHalf * 256 + 8 * x + b] = sum[b];
+        }
       }
+    }
+    __syncthreads();
+    if (pair == 0) {
 #pragma unroll
-      for (int a = 0; a < 8; ++a)
+      for (int t = 0; t < kCovHalf; ++t)
 #pragma unroll
-        for (int b = 0; b < 8; ++b) acc[a][b] = __fma_rn(dj[a], dl[b], acc[a][b]);
+        for (int r = 0; r < 4; ++r) acc[t][r] += mine[(4 * t + r) * 64];
+      if (HALF == 0) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          if (w == 1) {
+            sum[b] += __shfl_xor(sum[b], 16, kWave);
+            sum[b] += __shfl_xor(sum[b], 32, kWave);
+          }
+          sum[b] += red[kCovHalf * 256 + 8 * x + b];
+        }
+      }
     }
     __syncthreads();
   }
-  double* out = cpart + ((int64_t)u * kCalChunks + c) * kD * kD;
+  if (pair == 0) {
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+    for (int t = 0; t < kCovHalf; ++t)
 #pragma unroll
-    for (int b = 0; b < 8; ++b) out[(jb + a) * kD + lb + b] = acc[a][b];
+      for (int r = 0; r < 4; ++r) out[(HALF * kCovHalf + t) * 256 + r * 64 + lane] = acc[t][r];
+    if (HALF == 0 && g == 0) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) out[kCovTiles * 256 + 8 * x + b] = sum[b];
+    }
+  }
 }
 
-__global__ __launch_bounds__(kEigThreads) void klt_eig_kernel(const int64_t* __restrict__ n, int64_t n_cap,
-                                                             const double* __restrict__ msum,
-                                                             const double* __restrict__ cpart,
-                                                             float* __restrict__ mu_out, float* __restrict__ V_out,
+template <typename KT, bool VEC>
+__global__ __launch_bounds__(kCovThreads, 2) void klt_cov_kernel(const KT* __restrict__ K, int64_t ld_tok,
+                                                                int64_t ld_unit, const int64_t* __restrict__ n,
+                                                                int64_t n_cap, double* __restrict__ part,
+                                                                uint32_t* __restrict__ st) {
+  __shared__ double red[2 * (kCovHalf * 256 + kD)];
+  const int c = blockIdx.x, u = blockIdx.y, nch = (int)gridDim.x, tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t nu = unit_tokens(n, u, n_cap, (c == 0 && tid == 0) ? st : nullptr);
+  if (nu == 0) return;  // the reduction knows
+  int64_t t0, t1;
+  chunk_range(nu, nch, c, &t0, &t1);
+  const KT* Ku = K + (int64_t)u * ld_unit;
+  double* out = part + ((int64_t)u * nch + c) * kPartDoubles;
+  if (wave & 1)
+    cov_wave<1, KT, VEC>(Ku, ld_tok, t0, t1, wave >> 1, red, out);
+  else
+    cov_wave<0, KT, VEC>(Ku, ld_tok, t0, t1, wave >> 1, red, out);
+}
+
+// Covariance and mean of a unit from its chunks' sums, added in chunk order
+// (tile blockIdx.x; thread (r, lane) as the accumulators lie: row r4 + 4 r of
+// block bi, column of block bj).
+template <typename KT>
+__global__ __launch_bounds__(256) void klt_reduce_kernel(const KT* __restrict__ K, int64_t ld_unit,
+                                                        const int64_t* __restrict__ n, int64_t n_cap, int nch,
+                                                        const double* __restrict__ part, double* __restrict__ cov,
+                                                        float* __restrict__ mu_out) {
+  const int u = blockIdx.y, t = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int bi = tile_row(t), bj = tile_col(t);
+  const int i = 8 * ((lane >> 4) + 4 * (tid >> 6)) + bi, j = 8 * (lane & 15) + bj;
+  int64_t nu = n[u];
+  if (nu < 0 || nu > n_cap) nu = 0;  // flagged by the covariance pass
+  double s = 0.0, si = 0.0, sj = 0.0;
+  if (nu > 0) {
+    const double* pu = part + (int64_t)u * nch * kPartDoubles;
+#pragma unroll 8
+    for (int c = 0; c < nch; ++c) {
+      s += pu[c * kPartDoubles + t * 256 + tid];
+      si += pu[c * kPartDoubles + kCovTiles * 256 + i];
+      sj += pu[c * kPartDoubles + kCovTiles * 256 + j];
+    }
+    const double inv = 1.0 / (double)nu;
+    s *= inv;
+    si *= inv;
+    sj *= inv;
+  }
+  const double v = s - si * sj;
+  cov[((int64_t)u * kD + i) * kD + j] = v;
+  if (bi != bj) cov[((int64_t)u * kD + j) * kD + i] = v;
+  if (i == j) mu_out[(int64_t)u * kD + i] = nu > 0 ? (float)((double)key_at(K + (int64_t)u * ld_unit + i) + si) : 0.0f;
+}
+
+__global__ __launch_bounds__(kEigThreads) void klt_eig_kernel(const double* __restrict__ cov,
+                                                             float* __restrict__ V_out,
                                                              float* __restrict__ lam_out) {
   __shared__ float A[kD * kEigPitch];
   __shared__ float V[kD * kEigPitch];
   __shared__ float rc[kD / 2], rs[kD / 2];
   __shared__ int rp[kD / 2], rq[kD / 2];
   const int u = blockIdx.x, tid = threadIdx.x;
-  int64_t nu = n[u];
-  if (nu < 0 || nu > n_cap) nu = 0;
-  const double inv = nu > 0 ? 1.0 / (double)nu : 0.0;
-  // ---- covariance and mean from the chunk partials, summed in chunk order ----
   for (int e = tid; e < kD * kD; e += kEigThreads) {
-    double s = 0.0;
-    for (int x = 0; x < kCalChunks; ++x) s += cpart[((int64_t)u * kCalChunks + x) * kD * kD + e];
     const int j = e / kD, l = e % kD;
-    A[j * kEigPitch + l] = (float)(s * inv);
+    A[j * kEigPitch + l] = (float)cov[(int64_t)u * kD * kD + e];
     V[j * kEigPitch + l] = j == l ? 1.0f : 0.0f;
-  }
-  if (tid < kD) {
-    double s = 0.0;
-    for (int x = 0; x < kCalChunks; ++x) s += msum[((int64_t)u * kCalChunks + x) * kD + tid];
-    mu_out[(int64_t)u * kD + tid] = (float)(s * inv);
   }
   __syncthreads();
   // ---- cyclic Jacobi: rounds of 64 disjoint pairs (circle method on 128 indices) ----
@@ -243,34 +354,6 @@ __global__ __launch_bounds__(kEigThreads) void klt_eig_kernel(const int64_t* __r
 // DPP operand: no LDS, no scalar moves, four tokens' chains interleaved.
 // 8 x 131072 fp16 keys: 0.98 ms, of which the two operations are 0.87 (V and
 // the keys through LDS, one wave per SIMD, before: 2.70 ms).
-template <typename KT, bool VEC>
-struct RotRow {  // 8 consecutive channels of one token, as read
-  uint32_t w[2 * sizeof(KT)];
-  __device__ __forceinline__ void load(const KT* p) {
-    if constexpr (VEC) {
-#pragma unroll
-      for (int i = 0; i < (int)sizeof(KT) / 2; ++i) {
-        const uint4 r = reinterpret_cast<const uint4*>(p)[i];
-        w[4 * i] = r.x; w[4 * i + 1] = r.y; w[4 * i + 2] = r.z; w[4 * i + 3] = r.w;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if constexpr (sizeof(KT) == 4) {
-          w[e] = *(const __attribute__((address_space(1))) uint32_t*)(p + e);
-        } else {
-          const uint32_t h = *(const __attribute__((address_space(1))) uint16_t*)(p + e);
-          w[e >> 1] = (e & 1) ? w[e >> 1] | (h << 16) : h;
-        }
-      }
-    }
-  }
-  __device__ __forceinline__ float at(int e) const {
-    if constexpr (sizeof(KT) == 4) return __uint_as_float(w[e]);
-    return half_bits_to_float((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
-  }
-};
-
 // acc[t] += pr[t], then pr[t] = d[t] of lane X of each row of 16 times v.  The
 // four additions stand first, so that a register written just before has the
 // two wait states that a DPP read needs.
@@ -317,7 +400,7 @@ __global__ __launch_bounds__(kRotThreads, 2) void klt_rotate_keys_kernel(const K
   const int64_t t1 = t0 + chunk / 2 < nu ? t0 + chunk / 2 : nu;
   if (t0 >= t1) return;
   const KT* Ku = K + (int64_t)u * ld_unit + 8 * x;
-  RotRow<KT, VEC> row[kRotTokens];
+  KeyRow<KT, VEC> row[kRotTokens];
 #pragma unroll
   for (int t = 0; t < kRotTokens; ++t) row[t].load(Ku + (t0 + t < t1 ? t0 + t : t1 - 1) * ld_tok);
   float m[8], v[kD];
@@ -377,21 +460,28 @@ fathom_status launch_klt_calibrate(const void* K, fathom_dtype kdt, int64_t ld_t
                                    const int64_t* n, int64_t n_cap, int U, float* mu, float* V, float* lam, void* ws,
                                    uint32_t* st, hipStream_t s) {
   if (U == 0) return FATHOM_OK;
-  double* msum = reinterpret_cast<double*>(ws);
-  const size_t ms = ((size_t)U * kCalChunks * kD * sizeof(double) + 255) & ~(size_t)255;
-  double* cpart = reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + ms);
-  const dim3 g((unsigned)kCalChunks, (unsigned)U);
-  if (kdt == FATHOM_F32) {
-    const float* Kf = reinterpret_cast<const float*>(K);
-    hipLaunchKernelGGL(klt_mean_kernel<float>, g, dim3(kCalThreads), 0, s, Kf, ld_tok, ld_unit, n, n_cap, msum, st);
-    hipLaunchKernelGGL(klt_cov_kernel<float>, g, dim3(kCalThreads), 0, s, Kf, ld_tok, ld_unit, n, n_cap, msum, cpart);
-  } else {
-    const __half* Kh = reinterpret_cast<const __half*>(K);
-    hipLaunchKernelGGL(klt_mean_kernel<__half>, g, dim3(kCalThreads), 0, s, Kh, ld_tok, ld_unit, n, n_cap, msum, st);
-    hipLaunchKernelGGL(klt_cov_kernel<__half>, g, dim3(kCalThreads), 0, s, Kh, ld_tok, ld_unit, n, n_cap, msum,
-                       cpart);
-  }
-  hipLaunchKernelGGL(klt_eig_kernel, dim3((unsigned)U), dim3(kEigThreads), 0, s, n, n_cap, msum, cpart, mu, V, lam);
+  double* cov = reinterpret_cast<double*>(ws);
+  double* part = cov + (size_t)U * kD * kD;
+  const int nch = cal_chunks(U, n_cap);
+  const dim3 g((unsigned)nch, (unsigned)U), gr((unsigned)kCovTiles, (unsigned)U);
+  // 16-byte loads of a lane's 8 channels when every row start is 16-byte aligned
+  const int64_t vec = kdt == FATHOM_F32 ? 4 : 8;
+  const bool al = (reinterpret_cast<uintptr_t>(K) & 15) == 0 && ld_tok % vec == 0 && ld_unit % vec == 0;
+  const float* Kf = reinterpret_cast<const float*>(K);
+  const __half* Kh = reinterpret_cast<const __half*>(K);
+  if (kdt == FATHOM_F32 && al)
+    hipLaunchKernelGGL((klt_cov_kernel<float, true>), g, dim3(kCovThreads), 0, s, Kf, ld_tok, ld_unit, n, n_cap, part, st);
+  else if (kdt == FATHOM_F32)
+    hipLaunchKernelGGL((klt_cov_kernel<float, false>), g, dim3(kCovThreads), 0, s, Kf, ld_tok, ld_unit, n, n_cap, part, st);
+  else if (al)
+    hipLaunchKernelGGL((klt_cov_kernel<__half, true>), g, dim3(kCovThreads), 0, s, Kh, ld_tok, ld_unit, n, n_cap, part, st);
+  else
+    hipLaunchKernelGGL((klt_cov_kernel<__half, false>), g, dim3(kCovThreads), 0, s, Kh, ld_tok, ld_unit, n, n_cap, part, st);
+  if (kdt == FATHOM_F32)
+    hipLaunchKernelGGL(klt_reduce_kernel<float>, gr, dim3(256), 0, s, Kf, ld_unit, n, n_cap, nch, part, cov, mu);
+  else
+    hipLaunchKernelGGL(klt_reduce_kernel<__half>, gr, dim3(256), 0, s, Kh, ld_unit, n, n_cap, nch, part, cov, mu);
+  hipLaunchKernelGGL(klt_eig_kernel, dim3((unsigned)U), dim3(kEigThreads), 0, s, cov, V, lam);
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;
 }

@@ -104,3 +104,41 @@ def test_rotate_keys_runs(kdt, U, cap, pad):
         ref = oracle.klt_rotate_keys(K[u, dev(rows), :D].cpu().numpy(), mu[u], V[u])
         assert np.array_equal(got.view(np.uint32), ref.view(np.uint32)), (u, n)
         assert bool((out[u, n:] == 7.0).all())  # rows past n are left as they were
+
+
+@pytest.mark.parametrize("kdt", [np.float32, np.float16])
+@pytest.mark.parametrize("U,cap,pad,offset", [(1, 1, 0, 0.0), (3, 259, 3, 1.0), (9, 1030, 0, 300.0), (1, 20011, 8, 1.0)])
+def test_calibrate_chunks(kdt, U, cap, pad, offset):
+    """Calibration over 1 to 54 chunks per unit with ragged last steps of four
+    tokens, empty, one-key and rank-deficient units, a mean far from zero, and
+    strides that rule out 16-byte loads.  Bounds, with L the largest eigenvalue:
+    fp32 mean; |eigenvalue error|, |C v - lambda v| and |V^T V - I| of an fp32
+    Jacobi (128 x 128, backward error a few hundred units in the last place):
+    2e-5 L, 1e-4 L, 1e-5."""
+    rng = np.random.default_rng(U * 1000 + cap)
+    A = rng.standard_normal((D, D)) * np.geomspace(3.0, 0.05, D)
+    ns = rng.integers(0, cap + 1, U)
+    ns[0] = cap
+    if U > 2:
+        ns[1:3] = [0, 2]
+    K = rng.standard_normal((U, cap, D + pad))
+    K[:, :, :D] = K[:, :, :D] @ A.T + offset * rng.standard_normal(D)
+    K = K.astype(kdt)
+    st = F.new_status()
+    mu, V, lam = (t.cpu().numpy().astype(np.float64) for t in
+                  F.fathom_klt_calibrate(dev(K)[:, :, :D], dev(ns.astype(np.int64)), dev_status=st))
+    assert status(st) == 0
+    for u in range(U):
+        k = K[u, :ns[u], :D].astype(np.float64)
+        m = k.mean(0) if len(k) else np.zeros(D)
+        C = (k - m).T @ (k - m) / max(len(k), 1)
+        w = np.linalg.eigvalsh(C)[::-1]
+        L = max(w[0], 1e-300)
+        assert np.abs(mu[u] - m).max() <= 1.2e-7 * np.abs(m).max() + 1e-30
+        assert np.abs(lam[u] - w).max() <= 2e-5 * L and (np.diff(lam[u]) <= 0).all()
+        assert np.abs(C @ V[u] - V[u] * lam[u]).max() <= 1e-4 * L
+        assert np.abs(V[u].T @ V[u] - np.eye(D)).max() <= 1e-5
+        if ns[u] <= 1:
+            assert (V[u] == np.eye(D)).all() and (lam[u] == 0).all()
+        else:
+            assert (V[u][np.abs(V[u]).argmax(0), np.arange(D)] > 0).all()
