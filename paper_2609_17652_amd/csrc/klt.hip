@@ -8,12 +8,10 @@
 //   klt_cov_kernel    chunks of the keys: fp64 sums of y and y y^T, y the keys
 //                     shifted by the unit's first, on the fp64 matrix cores.
 //   klt_reduce_kernel the chunks' sums in chunk order: mean and covariance.
-//   klt_eig_kernel    one 1024-thread workgroup per unit: cyclic Jacobi in
-//                     fp32 with the matrix and the basis in LDS -- each sweep is 127 rounds
-//                     of 64 disjoint rotations (round-robin pairing), applied
-//                     to rows, then columns and the basis -- and finally the
-//                     columns ordered by eigenvalue (descending) with each
-//                     column's largest-magnitude entry made positive.
+//   klt_eig_kernel    one workgroup per unit: Cholesky factor in fp64, cyclic
+//                     one-sided Jacobi on it in fp32, eigenvalues in fp64, and
+//                     finally the columns ordered by eigenvalue (descending)
+//                     with each column's largest-magnitude entry made positive.
 // fathom_klt_rotate_keys (prefill) and fathom_klt_rotate_q (per step) compute
 // in fp32 in a fixed order: d_j = fl(k_j - mu_j) (no mean for q), then for
 // j = 0 .. D-1: acc_c = fl(acc_c + fl(d_j V[j][c])), no fused multiply-add, so
@@ -26,9 +24,14 @@ namespace fathom {
 
 constexpr size_t kCalUnitBytes = (size_t)32 * kD * (kD + 1) * sizeof(double);  // calibration workspace of one unit
 constexpr int kCalChunks = 54;        // token chunks per unit in the calibration sums, at most (they fit the above)
-constexpr int kEigThreads = 1024;
-constexpr int kEigPitch = kD + 1;     // LDS row pitch (column sweeps are conflict free)
-constexpr int kJacobiSweeps = 12;     // fp32 cyclic Jacobi on 128 x 128 converges in fewer
+constexpr int kEigThreads = 512;
+constexpr int kJacobiSweeps = 16;     // at most; covariances of 128 channels take 3 to 8
+// A pair whose cosine is below 1.4e-6 (the rounding of a dot product) is not
+// rotated.  The sweeps end when every rotation of a sweep was of a cosine below
+// 1e-4 by a tangent below 2^-10: what the up to 127 rotations of a column leave
+// of its other pairs' cosines is then about sqrt(127) * 1e-7.
+constexpr float kJacobiSkip2 = 2e-12f, kJacobiTol2 = 1e-8f, kJacobiTan = 0x1p-10f;
+constexpr double kCholShift = 1e-7;   // of the trace
 constexpr int kRotThreads = 256;
 constexpr int kRotTokens = 4;         // tokens a wave rotates at a time
 
@@ -257,91 +260,383 @@ __global__ __launch_bounds__(256) void klt_reduce_kernel(const KT* __restrict__ 
   if (i == j) mu_out[(int64_t)u * kD + i] = nu > 0 ? (float)((double)key_at(K + (int64_t)u * ld_unit + i) + si) : 0.0f;
 }
 
-__global__ __launch_bounds__(kEigThreads) void klt_eig_kernel(const double* __restrict__ cov,
-                                                             float* __restrict__ V_out,
-                                                             float* __restrict__ lam_out) {
-  __shared__ float A[kD * kEigPitch];
-  __shared__ float V[kD * kEigPitch];
-  __shared__ float rc[kD / 2], rs[kD / 2];
-  __shared__ int rp[kD / 2], rq[kD / 2];
-  const int u = blockIdx.x, tid = threadIdx.x;
-  for (int e = tid; e < kD * kD; e += kEigThreads) {
-    const int j = e / kD, l = e % kD;
-    A[j * kEigPitch + l] = (float)cov[(int64_t)u * kD * kD + e];
-    V[j * kEigPitch + l] = j == l ? 1.0f : 0.0f;
+// ---- eigen-decomposition: one-sided Jacobi on a Cholesky factor ----
+// C + delta I = L L^T (pivoted, fp64; delta = 1e-7 of the trace keeps every
+// column of L well above zero for a singular C and leaves the eigenvectors
+// as they are).  Rotations of L's columns until all are orthogonal turn them
+// into multiples of the eigenvectors: one 128 x 128 fp32 matrix, no separate
+// basis, and only columns are ever combined, so a pair of columns stays in the
+// registers of 8 lanes (16 rows each) and its dot product is 16 multiply-adds
+// and three DPP additions.  The eigenvalues are Rayleigh quotients of the
+// result with the fp64 covariance.
+//
+// The order of rotations: the 128 columns are 16 blocks of 8; each of the 8
+// waves holds two blocks, one as "top" and one as "bottom" columns, lane group i
+// pairing top i with bottom i ^ r for r = 0 .. 7 (the bottom columns move
+// between lane groups along a Gray code).  Then the blocks move to the next
+// wave through LDS (circle method, 15 meetings a sweep); at the first meeting of
+// a sweep the wave also pairs its 16 columns among themselves, by permlane
+// swaps of half of the top with half of the bottom columns.
+// What bounds it: the rotations' VALU work on one CU per unit (a sweep of 127
+// rounds takes 49 us; 9 sweeps for the decaying spectrum measured) and the
+// serial steps of the factorisation (about 0.11 ms).  8 units: 0.62 ms
+// (two-sided Jacobi with matrix and basis in LDS, three barriers a round and 12
+// fixed sweeps, before: 5.6 ms).
+__device__ __forceinline__ float dpp_xor1(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float dpp_xor2(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float dpp_half_mirror(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
+}
+// Sum over a group of 8 lanes, in every lane.
+__device__ __forceinline__ float sum8(float v) {
+  v = __fadd_rn(v, dpp_xor1(v));
+  v = __fadd_rn(v, dpp_xor2(v));
+  return __fadd_rn(v, dpp_half_mirror(v));
+}
+
+// Largest value of the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));
+  auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max(r[0], r[1]);
+  r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return max(r[0], r[1]);
+}
+
+// 1 / sqrt(x): the hardware's estimate and two Newton steps (x > 0).
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y = __fma_rn(__dmul_rn(0.5, y), __fma_rn(-__dmul_rn(x, y), y, 1.0), y);
+  return y;
+}
+
+constexpr int kColRows = 16;  // rows of a column per lane
+
+// A column across 8 lanes: its values are scale * v, |column|^2 = norm.
+struct JacobiCol {
+  float v[kColRows], norm, scale, inv;
+};
+
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+  if constexpr (M == 8) return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true));
+  return __shfl_xor(v, M, kWave);
+}
+template <int M>
+__device__ __forceinline__ void move_col(JacobiCol& c) {
+#pragma unroll
+  for (int e = 0; e < kColRows; ++e) c.v[e] = lane_xor<M>(c.v[e]);
+  c.norm = lane_xor<M>(c.norm);
+  c.scale = lane_xor<M>(c.scale);
+  c.inv = lane_xor<M>(c.inv);
+}
+
+// Top columns of the upper half of each 2M lanes against bottom columns of the lower half.
+template <int M>
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  if constexpr (M == 8) {
+    const int t = __float_as_int(a);
+    a = __int_as_float(__builtin_amdgcn_update_dpp(t, __float_as_int(b), 0x128, 0xF, 0xC, false));
+    b = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(b), t, 0x128, 0xF, 0x3, false));
+  } else {
+    const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false)
+                           : __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  }
+}
+template <int M>
+__device__ __forceinline__ void swap_cols(JacobiCol& a, JacobiCol& b) {
+#pragma unroll
+  for (int e = 0; e < kColRows; ++e) swap_halves<M>(a.v[e], b.v[e]);
+  swap_halves<M>(a.norm, b.norm);
+  swap_halves<M>(a.scale, b.scale);
+  swap_halves<M>(a.inv, b.inv);
+}
+
+// Rotate the pair (p, q) orthogonal; true if another sweep has to follow.  (Norms
+// are at least delta, so a_pq above the skipped cosines keeps its square.)
+__device__ __forceinline__ bool rotate_pair(JacobiCol& p, JacobiCol& q) {
+  float d0 = 0.0f, d1 = 0.0f;
+#pragma unroll
+  for (int e = 0; e < kColRows; e += 2) {
+    d0 = __fmaf_rn(p.v[e], q.v[e], d0);
+    d1 = __fmaf_rn(p.v[e + 1], q.v[e + 1], d1);
+  }
+  const float apq = __fmul_rn(sum8(__fadd_rn(d0, d1)), __fmul_rn(p.scale, q.scale));
+  // t = tan of the smaller rotation angle: 2 a_pq / (d + sign(d) sqrt(d^2 + 4 a_pq^2)), d = a_qq - a_pp
+  const float d = __fsub_rn(q.norm, p.norm), a2 = __fadd_rn(apq, apq);
+  const float r = __builtin_amdgcn_sqrtf(__fmaf_rn(a2, a2, __fmul_rn(d, d)));
+  const float den = __fadd_rn(d, __builtin_copysignf(r, d));
+  const float cos2 = __fmul_rn(apq, apq), len2 = __fmul_rn(p.norm, q.norm);
+  const float t = cos2 < __fmul_rn(kJacobiSkip2, len2) ? 0.0f : __fmul_rn(a2, __builtin_amdgcn_rcpf(den));
+  const float c = __builtin_amdgcn_rsqf(__fmaf_rn(t, t, 1.0f));
+  const float fp = __fmul_rn(t, __fmul_rn(q.scale, p.inv)), fq = __fmul_rn(t, __fmul_rn(p.scale, q.inv));
+#pragma unroll
+  for (int e = 0; e < kColRows; ++e) {
+    const float x = p.v[e];
+    p.v[e] = __fmaf_rn(-fp, q.v[e], x);
+    q.v[e] = __fmaf_rn(fq, x, q.v[e]);
+  }
+  const bool big = cos2 > __fmul_rn(kJacobiTol2, len2) || fabsf(t) > kJacobiTan;
+  p.norm = __fmaf_rn(-t, apq, p.norm);
+  q.norm = __fmaf_rn(t, apq, q.norm);
+  const float ic = __fmul_rn(__fmaf_rn(t, t, 1.0f), c);  // 1 / c
+  p.scale = __fmul_rn(p.scale, c);
+  q.scale = __fmul_rn(q.scale, c);
+  p.inv = __fmul_rn(p.inv, ic);
+  q.inv = __fmul_rn(q.inv, ic);
+  return big;
+}
+
+// Columns in LDS: 128 rows each; the 32-row quarters of odd columns change
+// places in pairs, so that two columns' 16-byte reads use all banks.
+__device__ __forceinline__ int col_addr(int col, int quarter, int li) {
+  return col * kD + ((quarter ^ (col & 1)) << 5) + 4 * li;
+}
+__device__ __forceinline__ void load_col(const float* X, int col, int li, JacobiCol& c) {
+  float n = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kColRows / 4; ++i) {
+    const float4 v = *reinterpret_cast<const float4*>(&X[col_addr(col, i, li)]);
+    c.v[4 * i] = v.x; c.v[4 * i + 1] = v.y; c.v[4 * i + 2] = v.z; c.v[4 * i + 3] = v.w;
+  }
+#pragma unroll
+  for (int e = 0; e < kColRows; ++e) n = __fmaf_rn(c.v[e], c.v[e], n);
+  c.norm = sum8(n);
+  c.scale = c.inv = 1.0f;
+}
+__device__ __forceinline__ void store_col(float* X, int col, int li, const JacobiCol& c) {
+#pragma unroll
+  for (int i = 0; i < kColRows / 4; ++i)
+    *reinterpret_cast<float4*>(&X[col_addr(col, i, li)]) =
+        make_float4(__fmul_rn(c.v[4 * i], c.scale), __fmul_rn(c.v[4 * i + 1], c.scale),
+                    __fmul_rn(c.v[4 * i + 2], c.scale), __fmul_rn(c.v[4 * i + 3], c.scale));
+}
+
+__global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* __restrict__ cov,
+                                                                float* __restrict__ V_out,
+                                                                float* __restrict__ lam_out) {
+  __shared__ __attribute__((aligned(16))) float X[2][kD * kD];  // columns; at the end one holds the basis as rows
+  __shared__ double colj[kD], diag[kD], lam[kD];
+  __shared__ int order[kD];
+  __shared__ int again[2];
+  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double* Cu = cov + (int64_t)u * kD * kD;
+  // thread (rg, cg) owns rows 8 rg .., columns 4 cg .. of what is left of the matrix
+  const int rg = tid >> 5, cg = tid & 31;
+  double a[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const v4f64 v = *reinterpret_cast<const v4f64*>(Cu + (8 * rg + i) * kD + 4 * cg);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[i][j] = v[j];
+      if (8 * rg + i == 4 * cg + j) diag[8 * rg + i] = a[i][j];
+    }
   }
   __syncthreads();
-  // ---- cyclic Jacobi: rounds of 64 disjoint pairs (circle method on 128 indices) ----
+  double tr = diag[lane] + diag[lane + 64];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) tr += __shfl_xor(tr, m, kWave);
+  float* Vo = V_out + (int64_t)u * kD * kD;
+  if (tr == 0.0) {  // no keys, or all equal: every basis is one, the identity is given
+    for (int e = tid; e < kD * kD; e += kEigThreads) Vo[e] = e / kD == e % kD ? 1.0f : 0.0f;
+    if (tid < kD) lam_out[(int64_t)u * kD + tid] = 0.0f;
+    return;
+  }
+  // ---- pivoted Cholesky of C / trace + delta I; the factor's column k goes to X[0] ----
+  const double itr = 1.0 / tr;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[i][j] = a[i][j] * itr + (8 * rg + i == 4 * cg + j ? kCholShift : 0.0);
+  __syncthreads();
+  double dg = 0.0;  // thread x < 128: what is left of diagonal x, negative once used
+  if (tid < kD) {
+    dg = diag[tid] * itr + kCholShift;
+    diag[tid] = dg;
+  }
+  __syncthreads();
+  for (int k = 0; k < kD; ++k) {
+    // the largest diagonal (to 16 mantissa bits) is the pivot; every wave finds it
+    uint32_t key = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double v = diag[lane + 64 * h];
+      const uint32_t kk = v < 0.0 ? 0u : (__float_as_uint((float)v) & 0x7FFFFF80u) | (uint32_t)(lane + 64 * h);
+      key = key > kk ? key : kk;
+    }
+    key = wave_max_u32(key);
+    const int j = __builtin_amdgcn_readfirstlane((int)(key & 127u));
+    if (cg == (j >> 2)) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double a0 = a[i][0], a1 = a[i][1], a2 = a[i][2], a3 = a[i][3];  // values: no indexing of registers
+        const double lo = (j & 1) ? a1 : a0, hi = (j & 1) ? a3 : a2;
+        colj[8 * rg + i] = (j & 2) ? hi : lo;
+      }
+    }
+    __syncthreads();
+    const double is = rsqrt_f64(colj[j]);
+    double lr[8], lc[4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lr[i] = colj[8 * rg + i] * is;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lc[i] = colj[4 * cg + i] * is;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) a[i][jj] = __fma_rn(-lr[i], lc[jj], a[i][jj]);
+    if (tid < kD) {
+      const double l = dg < 0.0 ? 0.0 : colj[tid] * is;  // rows used before hold nothing
+      X[0][col_addr(k, tid >> 5, 0) + (tid & 31)] = (float)l;
+      dg = tid == j ? -1.0 : dg < 0.0 ? dg : fmax(dg - l * l, 0.0);
+      diag[tid] = dg;
+    }
+    __syncthreads();
+  }
+  // ---- Jacobi sweeps ----
+  const int gi = lane >> 3, li = lane & 7;
+  // slots of this wave's blocks now, and where they go after a meeting
+  const int s0 = wave, s1 = 15 - wave;
+  const int t0 = s0 == 0 ? 0 : s0 + 1, t1 = s1 == 15 ? 1 : s1 + 1;
+  if (tid < 2) again[tid] = 0;
+  int buf = 0;
   for (int sweep = 0; sweep < kJacobiSweeps; ++sweep) {
-    for (int r = 0; r < kD - 1; ++r) {
-      if (tid < kD / 2) {
-        const int i = tid;
-        const int p = i == 0 ? kD - 1 : (r + i) % (kD - 1);
-        const int q = i == 0 ? r : (r - i + (kD - 1)) % (kD - 1);
-        const double apq = A[p * kEigPitch + q];
-        double c = 1.0, s = 0.0;
-        if (apq != 0.0) {
-          // the rotation that zeroes a_pq: tau = (a_qq - a_pp) / (2 a_pq),
-          // t the smaller root of t^2 + 2 tau t - 1 = 0
-          const double tau = ((double)A[q * kEigPitch + q] - (double)A[p * kEigPitch + p]) / (2.0 * apq);
-          const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + t * t);
-          s = t * c;
-        }
-        rc[i] = (float)c;
-        rs[i] = (float)s;
-        rp[i] = p;
-        rq[i] = q;
+    bool big = false;
+    for (int meet = 0; meet < 15; ++meet) {
+      JacobiCol p, q;
+      load_col(X[buf], 8 * s0 + gi, li, p);
+      load_col(X[buf], 8 * s1 + gi, li, q);
+      big |= rotate_pair(p, q);
+      move_col<8>(q);
+      big |= rotate_pair(p, q);
+      move_col<16>(q);
+      big |= rotate_pair(p, q);
+      move_col<8>(q);
+      big |= rotate_pair(p, q);
+      move_col<32>(q);
+      big |= rotate_pair(p, q);
+      move_col<8>(q);
+      big |= rotate_pair(p, q);
+      move_col<16>(q);
+      big |= rotate_pair(p, q);
+      move_col<8>(q);
+      big |= rotate_pair(p, q);
+      if (meet == 0) {  // the pairs inside the two blocks: 4 + 2 + 1 rounds
+        swap_cols<32>(p, q);
+        big |= rotate_pair(p, q);
+        move_col<8>(q);
+        big |= rotate_pair(p, q);
+        move_col<16>(q);
+        big |= rotate_pair(p, q);
+        move_col<8>(q);
+        big |= rotate_pair(p, q);
+        swap_cols<16>(p, q);
+        big |= rotate_pair(p, q);
+        move_col<8>(q);
+        big |= rotate_pair(p, q);
+        swap_cols<8>(p, q);
+        big |= rotate_pair(p, q);
       }
+      buf ^= 1;
+      store_col(X[buf], 8 * t0 + gi, li, p);
+      store_col(X[buf], 8 * t1 + gi, li, q);
+      if (meet == 14 && __ballot(big) && lane == 0) again[sweep & 1] = 1;
       __syncthreads();
-      // rows p, q: A <- J^T A
-      for (int e = tid; e < (kD / 2) * kD; e += kEigThreads) {
-        const int i = e / kD, x = e % kD;
-        const float c = rc[i], s = rs[i];
-        float* ap = &A[rp[i] * kEigPitch + x];
-        float* aq = &A[rq[i] * kEigPitch + x];
-        const float a = *ap, b = *aq;
-        *ap = c * a - s * b;
-        *aq = s * a + c * b;
-      }
-      __syncthreads();
-      // columns p, q: A <- A J, V <- V J
-      for (int e = tid; e < (kD / 2) * kD; e += kEigThreads) {
-        const int i = e / kD, x = e % kD;
-        const float c = rc[i], s = rs[i];
-        const int p = rp[i], q = rq[i];
-        const float a = A[x * kEigPitch + p], b = A[x * kEigPitch + q];
-        A[x * kEigPitch + p] = c * a - s * b;
-        A[x * kEigPitch + q] = s * a + c * b;
-        const float va = V[x * kEigPitch + p], vb = V[x * kEigPitch + q];
-        V[x * kEigPitch + p] = c * va - s * vb;
-        V[x * kEigPitch + q] = s * va + c * vb;
-      }
-      __syncthreads();
+    }
+    if (again[sweep & 1] == 0) break;  // nothing was left to rotate but what this sweep did
+    if (tid == 0) again[(sweep & 1) ^ 1] = 0;
+  }
+  __syncthreads();
+  // ---- unit columns, as rows of the basis in the other buffer ----
+  const float* Xf = X[buf];
+  float* Vs = X[buf ^ 1];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int col = 8 * wave + gi + 64 * h;
+    double s = 0.0;
+    float v[kColRows];
+#pragma unroll
+    for (int e = 0; e < kColRows; ++e) {
+      v[e] = Xf[col_addr(col, e >> 2, li) + (e & 3)];
+      s = __fma_rn((double)v[e], (double)v[e], s);
+    }
+#pragma unroll
+    for (int m = 1; m < 8; m <<= 1) s += __shfl_xor(s, m, kWave);
+    const double is = 1.0 / sqrt(s);
+#pragma unroll
+    for (int e = 0; e < kColRows; ++e) {
+      const int row = 32 * (e >> 2) + 4 * li + (e & 3);
+      Vs[row * kD + (col ^ (4 * ((row >> 2) & 7)))] = (float)((double)v[e] * is);
     }
   }
-  // ---- order by eigenvalue (descending, ties by index), fix signs, write ----
+  __syncthreads();
+  // ---- eigenvalues: v^T C v / v^T v in fp64; wave w forms C V for columns
+  // 16 w .. 16 w + 15 (C is symmetric: its rows serve as the A operand's columns) ----
+  {
+    const int i16 = lane & 15, g = lane >> 4, c = 16 * wave + i16;
+    auto basis = [&](int row) { return (double)Vs[row * kD + (c ^ (4 * ((row >> 2) & 7)))]; };
+    v4f64 w[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) w[t] = (v4f64){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int k = 0; k < kD; k += 4) {
+      const double b = basis(k + g);
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        w[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Cu[(k + g) * kD + 16 * t + i16], b, w[t], 0, 0, 0);
+    }
+    double num = 0.0, den = 0.0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double v = basis(16 * t + 4 * r + g);
+        num = __fma_rn(v, w[t][r], num);
+        den = __fma_rn(v, v, den);
+      }
+    num += __shfl_xor(num, 16, kWave);
+    den += __shfl_xor(den, 16, kWave);
+    num += __shfl_xor(num, 32, kWave);
+    den += __shfl_xor(den, 32, kWave);
+    if (g == 0) lam[c] = num / den;
+  }
+  __syncthreads();
+  // ---- order by eigenvalue (descending, ties by position), fix signs, write ----
   if (tid < kD) {
     const int c = tid;
-    const float lc = A[c * kEigPitch + c];
+    const float lc = (float)lam[c];
     int rank = 0;
     for (int x = 0; x < kD; ++x) {
-      const float lx = A[x * kEigPitch + x];
+      const float lx = (float)lam[x];
       rank += (lx > lc) || (lx == lc && x < c);
     }
-    int jm = 0;
-    float best = -1.0f;
-    for (int j = 0; j < kD; ++j) {
-      const float a = fabsf(V[j * kEigPitch + c]);
-      if (a > best) {
-        best = a;
-        jm = j;
+    float best = -1.0f, at = 0.0f;
+    for (int i = 0; i < kD; ++i) {
+      const float v = Vs[i * kD + (c ^ (4 * ((i >> 2) & 7)))];
+      if (fabsf(v) > best) {
+        best = fabsf(v);
+        at = v;
       }
     }
-    const float sg = V[jm * kEigPitch + c] < 0.0f ? -1.0f : 1.0f;
-    float* vo = V_out + (int64_t)u * kD * kD;
-    for (int j = 0; j < kD; ++j) vo[j * kD + rank] = sg * V[j * kEigPitch + c];
-    lam_out[(int64_t)u * kD + rank] = lc;
+    order[rank & (kD - 1)] = at < 0.0f ? c | kD : c;
+    lam_out[(int64_t)u * kD + (rank & (kD - 1))] = lc;
+  }
+  __syncthreads();
+  for (int e = tid; e < kD * kD; e += kEigThreads) {
+    const int i = e / kD, o = order[e % kD];
+    const float v = Vs[i * kD + ((o & (kD - 1)) ^ (4 * ((i >> 2) & 7)))];
+    Vo[e] = (o & kD) ? -v : v;
   }
 }
 
