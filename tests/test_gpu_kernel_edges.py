@@ -142,3 +142,81 @@ def test_calibrate_chunks(kdt, U, cap, pad, offset):
             assert (V[u] == np.eye(D)).all() and (lam[u] == 0).all()
         else:
             assert (V[u][np.abs(V[u]).argmax(0), np.arange(D)] > 0).all()
+
+
+def topk_rows(rng, kind, n):
+    if kind == "narrow":  # one binade: every digit has to be refined
+        return (1000.0 + rng.standard_normal(n) * 0.01).astype(np.float32)
+    if kind == "equal":  # more equal scores than a list holds, few above them
+        s = np.full(n, 2.5, np.float32)
+        s[rng.integers(0, max(n, 1), 40 if n else 0)] = 3.0
+        return s
+    if kind == "late":  # the equal scores at the threshold only in the last third
+        s = -np.abs(rng.standard_normal(n)).astype(np.float32)
+        s[2 * n // 3:] = 0.0
+        s[n // 2:n // 2 + 9] = -0.0
+        return s
+    if kind == "cluster":  # equal scores inside the list: the row is sorted
+        return np.where(rng.random(n) < 0.01, np.float32(4.0), rng.standard_normal(n)).astype(np.float32)
+    s = rng.standard_normal(n).astype(np.float32)
+    s[rng.random(n) < 0.01] = np.nan
+    s[rng.random(n) < 0.01] = np.inf
+    return s
+
+
+@pytest.mark.parametrize("kind", ["narrow", "equal", "late", "cluster", "special"])
+@pytest.mark.parametrize("k,lo,tail", [(1, 0, 0), (500, 4, 32), (2048, 0, 0), (8192, 3, 1)])
+def test_topk_refinement(kind, k, lo, tail):
+    """fathom_topk where rows take one, two or three digits, where the equal
+    scores at the threshold do not fit the list (index order decides), where a
+    list holds many equal scores, and at the ends of chunks of 4096: indices and
+    values equal to the oracle's."""
+    rng = np.random.default_rng(k)
+    ns = [40961, 20000, 4096, lo + tail + 1, 8193]
+    ld = 40970
+    s = np.zeros((len(ns), 2, ld), np.float32)
+    for u, n in enumerate(ns):
+        for h in range(2):
+            s[u, h, :n] = topk_rows(rng, kind, n)
+    st = F.new_status()
+    idx, val = F.fathom_topk(dev(s), dev(np.array(ns, np.int64)), k, lo, tail, dev_status=st)
+    flags, want = status(st), 0
+    idx, val = idx.cpu().numpy(), val.cpu().numpy()
+    for u, n in enumerate(ns):
+        for h in range(2):
+            oi, ov, ost = oracle.topk(s[u, h, :n], k, lo, tail)
+            want |= ost
+            assert np.array_equal(idx[u, h], oi), (u, h)
+            assert np.array_equal(val[u, h], ov, equal_nan=True), (u, h)
+    assert flags == want
+
+
+@pytest.mark.parametrize("G,qdt", [(1, np.float32), (3, np.float16), (4, np.float16), (8, np.float32)])
+@pytest.mark.parametrize("U,nb_cap", [(43, 90), (2, 19)])
+def test_scan_stages(G, qdt, U, nb_cap):
+    """fathom_scan with four blocks and one block a wave, 0 to 128 active channels
+    (none to four stages), every depth, ragged ends and a score row shorter than
+    the keys; bit-exact to the oracle's fp32 order."""
+    rng = np.random.default_rng(G * 100 + U)
+    cap = nb_cap * 64
+    ns = rng.integers(1, cap + 1, U)
+    ns[0], ns[1] = cap, 1025
+    K = torch.randn((U, cap, D), device=DEV)
+    planes, scales = F.fathom_pack(K, dev(ns.astype(np.int64)), nb_cap=nb_cap)
+    q = rng.standard_normal((U, G, D)).astype(qdt)
+    depths = rng.integers(0, 5, (U, D)).astype(np.uint8)
+    depths[rng.random((U, D)) < 0.4] = 0
+    depths[0], depths[1] = 0, 0
+    depths[0, [0, 63, 64, 127]] = [1, 2, 3, 4]
+    if U > 2:
+        depths[2], depths[3, :], depths[4, :65] = 4, 0, 1
+    ld = cap - 70
+    st = F.new_status()
+    s = F.fathom_scan(planes, scales, dev(ns.astype(np.int64)), dev(q), dev(depths), ld_s=ld, dev_status=st)
+    assert status(st) == 0
+    for u in range(min(U, 8)):
+        n = int(ns[u])
+        ref = oracle.scores_f32(planes[u].cpu().numpy().view(np.uint64), scales[u].cpu().numpy().view(np.uint16), n,
+                                q[u].astype(np.float32), depths[u])
+        m = min(n, ld)
+        assert np.array_equal(s[u, :, :m].cpu().numpy().view(np.uint32), ref[:, :m].view(np.uint32)), u
