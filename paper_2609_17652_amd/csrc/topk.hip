@@ -1,14 +1,27 @@
 // fathom_topk: Sec. 2 (top-k decoding) -- per query head, the k largest
 // scores over an eligible window, ordered by (score desc, index asc).
 //
-// Exact radix select on an order-preserving uint32 key (score_key):
-//   3 x (histogram pass over the row + pivot) on digits of 11, 11 and 10 bits
-//   find the k-th largest key T and how many keys equal to T must be taken;
-//   a count pass, a per-row prefix over chunks and a write pass then collect
-//   every key > T and the lowest-index keys == T in index order (so ties go to
-//   the lower index without sorting the row); a bitonic sort in LDS orders
-//   the k winners.  Rows are split into chunks of kChunk elements so that a
-//   launch has many workgroups even for a few rows.
+// Exact radix select on an order-preserving uint32 key (score_key), digits of
+// 12, 10 and 10 bits, that stops refining as soon as the keys not yet ruled
+// out fit a list of lcap entries (about 4k + 2048):
+//   - a pass over the row either histograms the next digit (the workgroup that
+//     arrives last at a row picks the digit holding the k-th key), or, once
+//     the row's remaining keys fit, collects them (key, index) into its list.
+//     Each row decides for itself; a row that is done leaves the later passes at
+//     once.  Scores spread over a few binades take one histogram and one
+//     collection: the scores are read twice.
+//   - the rank pass orders the lists and writes the top k: 8 workgroups a row
+//     share its output positions by a counting sort on interpolated
+//     sub-buckets, so that only keys sharing a sub-bucket are compared.
+//     Lists with many equal keys are sorted by one workgroup instead.
+//   - more equal keys at the threshold than a list holds: the list gets the
+//     keys above, and the rank pass takes the first equal ones in index order.
+// Rows are split into chunks of kChunk elements so that a launch has many
+// workgroups even for a few rows.  32 rows of 131072 scores, k = 1024: 46 us
+// in 6 launches (13 launches with three histograms and single-thread pivots,
+// count, scan and write passes and a bitonic sort, before: 106 us).
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace fathom {
@@ -16,40 +29,49 @@ namespace fathom {
 constexpr int kTopkThreads = 256;
 constexpr int kPerThread = 16;
 constexpr int kChunk = kTopkThreads * kPerThread;  // 4096 elements per workgroup
-constexpr int kBins = 2048;
+constexpr int kDigits = 3;
+constexpr int kBins = 4096;
+constexpr int kNever = 1 << 30;
 
 struct RowState {
-  uint32_t prefix;  // digits fixed so far (the final threshold key T after 3 passes)
-  uint32_t mask;    // bits of `prefix` that are fixed
-  int32_t need;     // how many still to take among keys matching `prefix`
-  int32_t total_gt; // number of eligible keys > T (after the count scan)
+  uint32_t prefix;   // digits fixed so far
+  uint32_t mask;     // bits of `prefix` that are fixed
+  int32_t need;      // how many still to take among keys matching `prefix`
+  int32_t collect;   // the pass that collects the row's keys >= prefix (kNever: not known yet)
+  uint32_t strict;   // collect only keys > prefix (the equal ones do not fit)
+  uint32_t arrived;  // workgroups that have added their histogram
+  uint32_t count;    // keys in the list
+  uint32_t k;        // k once the first digit is known
 };
 
 struct TopkWs {
-  uint32_t* hist;  // [R][kBins]
-  RowState* state; // [R]
-  uint32_t* cnt;   // [R][nchunks][2]
-  uint64_t* sel;   // [R][k] composite (key << 32 | ~idx)
+  uint32_t* hist;   // [R][kBins]
+  RowState* state;  // [R]
+  uint64_t* list;   // [R][lcap] composites (key << 32 | ~index), any order
+  int lcap;
 };
 
 static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static inline int64_t topk_chunks(int64_t max_n) { return (max_n + kChunk - 1) / kChunk; }
 
-size_t topk_ws_bytes(int R, int64_t max_n, int k) {
-  const int64_t nch = topk_chunks(max_n) > 0 ? topk_chunks(max_n) : 1;
-  return align_up((size_t)R * kBins * 4) + align_up((size_t)R * sizeof(RowState)) +
-         align_up((size_t)R * nch * 2 * 4) + align_up((size_t)R * k * 8);
+static inline int topk_lcap(int k) {
+  const int c = 4 * k + 2048;
+  return c < 2 * FATHOM_MAX_K ? c : 2 * FATHOM_MAX_K;
 }
 
-static TopkWs carve(void* ws, int R, int64_t max_n, int k) {
-  const int64_t nch = topk_chunks(max_n) > 0 ? topk_chunks(max_n) : 1;
+size_t topk_ws_bytes(int R, int64_t, int k) {
+  return align_up((size_t)R * kBins * 4) + align_up((size_t)R * sizeof(RowState)) +
+         align_up((size_t)R * topk_lcap(k) * 8);
+}
+
+static TopkWs carve(void* ws, int R, int k) {
   char* p = reinterpret_cast<char*>(ws);
   TopkWs w;
   w.hist = reinterpret_cast<uint32_t*>(p); p += align_up((size_t)R * kBins * 4);
   w.state = reinterpret_cast<RowState*>(p); p += align_up((size_t)R * sizeof(RowState));
-  w.cnt = reinterpret_cast<uint32_t*>(p); p += align_up((size_t)R * nch * 2 * 4);
-  w.sel = reinterpret_cast<uint64_t*>(p);
+  w.list = reinterpret_cast<uint64_t*>(p);
+  w.lcap = topk_lcap(k);
   return w;
 }
 
@@ -67,262 +89,360 @@ __device__ __forceinline__ RowRange row_range(const int64_t* n, int u, int64_t c
   return r;
 }
 
-__global__ void topk_init_kernel(RowState* __restrict__ state, uint32_t* __restrict__ hist, int k) {
+__global__ __launch_bounds__(1024) void topk_init_kernel(RowState* __restrict__ state, uint4* __restrict__ hist,
+                                                         int k) {
   const int r = blockIdx.x;
-  for (int b = threadIdx.x; b < kBins; b += blockDim.x) hist[(int64_t)r * kBins + b] = 0u;
+  hist[(int64_t)r * (kBins / 4) + threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
   if (threadIdx.x == 0) {
-    state[r].prefix = 0u;
-    state[r].mask = 0u;
-    state[r].need = k;
-    state[r].total_gt = 0;
+    RowState s = {};
+    s.need = k;
+    s.collect = kNever;
+    state[r] = s;
   }
 }
+static_assert(kBins == 4 * 1024, "topk_init_kernel clears 4 bins per thread");
 
-// histogram of digit (key >> shift) & (2^bits - 1) over eligible keys matching the prefix
-__global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const float* __restrict__ scores, int64_t ld_s,
-                                                                 const int64_t* __restrict__ n, int G,
-                                                                 int64_t lo, int64_t tail, int shift, int bits,
-                                                                 const RowState* __restrict__ state,
-                                                                 uint32_t* __restrict__ hist,
-                                                                 uint32_t* __restrict__ st, int first) {
+// Pass `pass` over the scores (see above).  Every workgroup of a row sees the
+// state the pass before left, and only the one that arrives last changes it.
+__global__ __launch_bounds__(kTopkThreads) void topk_pass_kernel(const float* __restrict__ scores, int64_t ld_s,
+                                                                 const int64_t* __restrict__ n, int G, int64_t lo,
+                                                                 int64_t tail, int pass, TopkWs ws,
+                                                                 uint32_t* __restrict__ st) {
   __shared__ uint32_t h[kBins];
-  const int r = blockIdx.y, u = r / G, tid = threadIdx.x;
-  const RowRange rr = row_range(n, u, ld_s, lo, tail, (first && blockIdx.x == 0 && tid == 0) ? st : nullptr);
-  const int64_t c0 = rr.lo + (int64_t)blockIdx.x * kChunk;
+  __shared__ uint32_t part[kTopkThreads / kWave];
+  __shared__ int s_digit;
+  __shared__ uint32_t s_above, s_last;
+  const int r = blockIdx.y, u = r / G, tid = threadIdx.x, lane = tid & 63;
+  RowState* S = ws.state + r;
+  const int collect = S->collect;
+  if (collect < pass) return;
+  const RowRange rr = row_range(n, u, ld_s, lo, tail, (pass == 0 && blockIdx.x == 0 && tid == 0) ? st : nullptr);
+  const int64_t step = (int64_t)gridDim.x * kChunk;  // a workgroup takes every gridDim.x-th chunk
+  int64_t c0 = rr.lo + (int64_t)blockIdx.x * kChunk;
   if (c0 >= rr.hi) return;
-  const uint32_t prefix = state[r].prefix, mask = state[r].mask;
-  const uint32_t dmask = (1u << bits) - 1u;
-  for (int b = tid; b < kBins; b += kTopkThreads) h[b] = 0u;
-  __syncthreads();
+  const uint32_t prefix = S->prefix;
   const float* row = scores + (int64_t)r * ld_s;
-  bool nonfinite = false;
-#pragma unroll 4
-  for (int e = 0; e < kPerThread; ++e) {
-    const int64_t i = c0 + (int64_t)e * kTopkThreads + tid;
-    if (i < rr.hi) {
-      const float s = row[i];
-      if (first && !(fabsf(s) <= 3.402823466e38f)) nonfinite = true;
-      const uint32_t key = score_key(s);
-      if ((key & mask) == prefix) atomicAdd(&h[(key >> shift) & dmask], 1u);
+  float v[kPerThread];
+  auto load = [&]() {
+#pragma unroll
+    for (int e = 0; e < kPerThread; ++e) {
+      const int64_t i = c0 + (int64_t)e * kTopkThreads + tid;
+      v[e] = row[i < rr.hi ? i : rr.hi - 1];
     }
-  }
-  if (first && __ballot(nonfinite) && (tid & 63) == 0) set_status(st, FATHOM_DEV_NONFINITE);
-  __syncthreads();
-  uint32_t* gh = hist + (int64_t)r * kBins;
-  for (int b = tid; b < kBins; b += kTopkThreads)
-    if (h[b]) atomicAdd(&gh[b], h[b]);
-}
-
-// find the digit holding the need-th largest remaining key; clear the histogram
-__global__ __launch_bounds__(kTopkThreads) void topk_pivot_kernel(int shift, int bits, RowState* __restrict__ state,
-                                                                  uint32_t* __restrict__ hist) {
-  __shared__ uint32_t part[kTopkThreads];
-  __shared__ uint32_t hs[kBins];
-  const int r = blockIdx.x, tid = threadIdx.x;
-  const int nb = 1 << bits;
-  uint32_t* gh = hist + (int64_t)r * kBins;
-  for (int b = tid; b < kBins; b += kTopkThreads) {
-    hs[b] = gh[b];
-    gh[b] = 0u;
-  }
-  __syncthreads();
-  // thread t owns digits [nb - (t+1)*per, nb - t*per), i.e. top-down order
-  const int per = nb / kTopkThreads;
-  const int top = nb - tid * per;
-  uint32_t mine = 0;
-  for (int d = top - 1; d >= top - per; --d) mine += hs[d];
-  part[tid] = mine;
-  __syncthreads();
-  if (tid == 0) {
-    const int need = state[r].need;
-    uint32_t above = 0;
-    int digit = 0;
-    uint32_t above_digit = 0;
-    bool found = false;
-    for (int t = 0; t < kTopkThreads && !found; ++t) {
-      if (above + part[t] >= (uint32_t)need) {
-        const int tp = nb - t * per;
-        for (int d = tp - 1; d >= tp - per; --d) {
-          if (above + hs[d] >= (uint32_t)need) {
-            digit = d;
-            above_digit = above;
-            found = true;
-            break;
-          }
-          above += hs[d];
+  };
+  if (collect == pass) {
+    const bool strict = S->strict != 0;
+    uint64_t* list = ws.list + (int64_t)r * ws.lcap;
+    for (; c0 < rr.hi; c0 += step) {
+      load();
+      uint32_t take = 0;
+      int mine = 0;
+#pragma unroll
+      for (int e = 0; e < kPerThread; ++e) {
+        const uint32_t key = score_key(v[e]);
+        const bool in = c0 + (int64_t)e * kTopkThreads + tid < rr.hi && (strict ? key > prefix : key >= prefix);
+        take |= (uint32_t)in << e;
+        mine += in;
+      }
+      if (__ballot(take != 0) == 0) continue;
+      int inc = mine;  // positions: one reservation per wave
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += x;
+      }
+      uint32_t base = 0;
+      if (lane == 63) base = atomicAdd(&S->count, (uint32_t)inc);
+      base = __shfl(base, 63, kWave) + (uint32_t)(inc - mine);
+#pragma unroll
+      for (int e = 0; e < kPerThread; ++e) {
+        if (take & (1u << e)) {
+          const int64_t i = c0 + (int64_t)e * kTopkThreads + tid;
+          // the histograms bound the count; the test only keeps a changed input inside the list
+          if (base < (uint32_t)ws.lcap) list[base] = ((uint64_t)score_key(v[e]) << 32) | (uint64_t)(~(uint32_t)i);
+          ++base;
         }
-      } else {
-        above += part[t];
       }
     }
-    if (!found) {  // fewer candidates than needed: take all of them
-      digit = 0;
-      above_digit = above - hs[0];
-    }
-    state[r].prefix |= (uint32_t)digit << shift;
-    state[r].mask |= (uint32_t)(nb - 1) << shift;
-    state[r].need = need - (int32_t)above_digit;
+    return;
   }
-}
-
-// per chunk: number of eligible keys > T and == T
-__global__ __launch_bounds__(kTopkThreads) void topk_count_kernel(const float* __restrict__ scores, int64_t ld_s,
-                                                                  const int64_t* __restrict__ n, int G,
-                                                                  int64_t lo, int64_t tail, int64_t nch,
-                                                                  const RowState* __restrict__ state,
-                                                                  uint32_t* __restrict__ cnt) {
-  __shared__ uint32_t red[2][kTopkThreads / kWave];
-  const int r = blockIdx.y, u = r / G, tid = threadIdx.x;
-  const RowRange rr = row_range(n, u, ld_s, lo, tail, nullptr);
-  const int64_t c0 = rr.lo + (int64_t)blockIdx.x * kChunk;
-  const uint32_t T = state[r].prefix;
-  const float* row = scores + (int64_t)r * ld_s;
-  int gt = 0, eq = 0;
-  for (int e = 0; e < kPerThread; ++e) {
-    const int64_t i = c0 + (int64_t)e * kTopkThreads + tid;
-    if (i < rr.hi) {
-      const uint32_t key = score_key(row[i]);
-      gt += key > T;
-      eq += key == T;
+  const int shift = pass == 0 ? 20 : pass == 1 ? 10 : 0, nb = pass == 0 ? 4096 : 1024;
+  const uint32_t mask = S->mask;
+  for (int b = tid; b < nb; b += kTopkThreads) h[b] = 0u;
+  __syncthreads();
+  bool nonfinite = false;
+  for (; c0 < rr.hi; c0 += step) {
+    load();
+#pragma unroll
+    for (int e = 0; e < kPerThread; ++e) {
+      if (c0 + (int64_t)e * kTopkThreads + tid < rr.hi) {
+        if (!(fabsf(v[e]) <= 3.402823466e38f)) nonfinite = true;
+        const uint32_t key = score_key(v[e]);
+        if ((key & mask) == prefix) atomicAdd(&h[(key >> shift) & (uint32_t)(nb - 1)], 1u);
+      }
     }
   }
-  gt = wave_sum_int(gt);
-  eq = wave_sum_int(eq);
-  if ((tid & 63) == 0) {
-    red[0][tid >> 6] = gt;
-    red[1][tid >> 6] = eq;
-  }
+  if (pass == 0 && __ballot(nonfinite) && lane == 0) set_status(st, FATHOM_DEV_NONFINITE);
+  __syncthreads();
+  uint32_t* gh = ws.hist + (int64_t)r * kBins;
+  // The counts are only ever touched by device-scope atomics, so an addition is
+  // done once its old value has come back: no fence, whose write-back of the L2
+  // by every workgroup took 100 us.
+  uint32_t back = 0;
+#pragma unroll 4
+  for (int b = tid; b < nb; b += kTopkThreads)
+    if (h[b]) back |= atomicAdd(&gh[b], h[b]);
+  asm volatile("" ::"v"(back) : "memory");
   __syncthreads();
   if (tid == 0) {
-    uint32_t a = 0, b = 0;
-    for (int w = 0; w < kTopkThreads / kWave; ++w) {
-      a += red[0][w];
-      b += red[1][w];
-    }
-    cnt[((int64_t)r * nch + blockIdx.x) * 2 + 0] = a;
-    cnt[((int64_t)r * nch + blockIdx.x) * 2 + 1] = b;
+    const int64_t chunks = (rr.hi - rr.lo + kChunk - 1) / kChunk;
+    const uint32_t groups = chunks < (int64_t)gridDim.x ? (uint32_t)chunks : gridDim.x;
+    s_last = atomicAdd(&S->arrived, 1u) + 1u == groups;
   }
-}
-
-// exclusive prefix over chunks (in index order), per row
-__global__ void topk_scan_kernel(int64_t nch, RowState* __restrict__ state, uint32_t* __restrict__ cnt) {
-  const int r = blockIdx.x;
-  if (threadIdx.x != 0) return;
-  uint32_t a = 0, b = 0;
-  uint32_t* c = cnt + (int64_t)r * nch * 2;
-  for (int64_t ch = 0; ch < nch; ++ch) {
-    const uint32_t x = c[2 * ch], y = c[2 * ch + 1];
-    c[2 * ch] = a;
-    c[2 * ch + 1] = b;
-    a += x;
-    b += y;
-  }
-  state[r].total_gt = (int32_t)a;
-}
-
-// write keys > T, then the first `need` keys == T in index order, to sel[r][*]
-__global__ __launch_bounds__(kTopkThreads) void topk_write_kernel(const float* __restrict__ scores, int64_t ld_s,
-                                                                  const int64_t* __restrict__ n, int G,
-                                                                  int64_t lo, int64_t tail, int64_t nch, int k,
-                                                                  const RowState* __restrict__ state,
-                                                                  const uint32_t* __restrict__ cnt,
-                                                                  uint64_t* __restrict__ sel) {
-  __shared__ uint32_t wt[2][kTopkThreads / kWave];
-  const int r = blockIdx.y, u = r / G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const RowRange rr = row_range(n, u, ld_s, lo, tail, nullptr);
-  const int64_t c0 = rr.lo + (int64_t)blockIdx.x * kChunk;
-  if (c0 >= rr.hi) return;
-  const uint32_t T = state[r].prefix;
-  const int32_t need = state[r].need, total_gt = state[r].total_gt;
-  uint32_t base_gt = cnt[((int64_t)r * nch + blockIdx.x) * 2 + 0];
-  uint32_t base_eq = cnt[((int64_t)r * nch + blockIdx.x) * 2 + 1];
-  const float* row = scores + (int64_t)r * ld_s;
-  uint64_t* out = sel + (int64_t)r * k;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int e = 0; e < kPerThread; ++e) {
-    const int64_t i = c0 + (int64_t)e * kTopkThreads + tid;
-    uint32_t key = 0;
-    bool g = false, q = false;
-    if (i < rr.hi) {
-      key = score_key(row[i]);
-      g = key > T;
-      q = key == T;
-    }
-    const uint64_t bg = __ballot(g), bq = __ballot(q);
-    if (lane == 0) {
-      wt[0][wave] = (uint32_t)__popcll(bg);
-      wt[1][wave] = (uint32_t)__popcll(bq);
-    }
-    __syncthreads();
-    uint32_t og = base_gt, oq = base_eq, tg = 0, tq = 0;
-    for (int w = 0; w < kTopkThreads / kWave; ++w) {
-      if (w < wave) {
-        og += wt[0][w];
-        oq += wt[1][w];
-      }
-      tg += wt[0][w];
-      tq += wt[1][w];
-    }
-    const uint64_t comp = ((uint64_t)key << 32) | (uint64_t)(~(uint32_t)i);
-    if (g) out[og + __popcll(bg & lt_mask)] = comp;
-    if (q) {
-      const uint32_t rank = oq + (uint32_t)__popcll(bq & lt_mask);
-      if ((int32_t)rank < need) out[total_gt + rank] = comp;
-    }
-    base_gt += tg;
-    base_eq += tq;
-    __syncthreads();
-  }
-}
-
-// order the winners by (key desc, index asc); empty slots (0) -> (-1, NaN)
-__global__ __launch_bounds__(1024) void topk_sort_kernel(const float* __restrict__ scores, int64_t ld_s, int k,
-                                                         const uint64_t* __restrict__ sel, int32_t* __restrict__ idx,
-                                                         float* __restrict__ val, uint32_t* __restrict__ st) {
-  extern __shared__ uint64_t buf[];
-  const int r = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
-  int P = 1;
-  while (P < k) P <<= 1;
-  const uint64_t* in = sel + (int64_t)r * k;
-  // sel was cleared before the write pass: unwritten slots are 0, the lowest value
-  for (int i = tid; i < P; i += nt) buf[i] = i < k ? in[i] : 0ull;
   __syncthreads();
-  for (int size = 2; size <= P; size <<= 1) {
+  if (!s_last) return;
+  for (int b = tid; b < nb; b += kTopkThreads) {
+    h[b] = __hip_atomic_load(&gh[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    gh[b] = 0u;  // for the next pass
+  }
+  __syncthreads();
+  const int need = S->need;
+  find_crossing(h, nb, (uint32_t)need, part, &s_digit, &s_above);
+  if (tid == 0) {
+    // keys above the digit's own: all of the k wanted so far but `need`, and s_above
+    const int left = need - (int)s_above, k = pass > 0 ? (int)S->k : need;
+    const uint32_t fits = (uint32_t)(k - left) + h[s_digit];
+    S->k = (uint32_t)k;
+    S->prefix = prefix | (uint32_t)s_digit << shift;
+    S->mask = mask | (uint32_t)(nb - 1) << shift;
+    S->need = left;
+    S->arrived = 0u;
+    if (fits <= (uint32_t)ws.lcap) {
+      S->collect = pass + 1;
+    } else if (pass == kDigits - 1) {
+      S->collect = pass + 1;
+      S->strict = 1u;
+    }
+  }
+}
+
+// ---------------------------------------------------------------- ranks
+constexpr int kRankT = 512;
+constexpr int kRankShare = 8;     // workgroups per row
+constexpr int kRankMaxSub = 4096; // sub-buckets at most
+constexpr int kRankGroup = 4096;  // keys one workgroup groups at most
+constexpr int kRankSame = 64;     // keys of one sub-bucket at most (else the row is sorted)
+constexpr int kRankRegs = 8;      // list entries per thread kept in registers
+
+static inline size_t rank_lds_keys(int lcap) {  // composites: a workgroup's group, or a whole list to sort
+  size_t p = kRankGroup;
+  while (p < (size_t)lcap) p <<= 1;
+  return p;
+}
+
+// Bitonic sort of buf[0..P) into descending order.
+__device__ void sort_desc(uint64_t* buf, int P) {
+  for (int size = 2; size <= P; size <<= 1)
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = tid; i < P; i += nt) {
-        const int j = i ^ stride;
-        if (j > i) {
-          const bool desc = (i & size) == 0;
-          const uint64_t a = buf[i], b = buf[j];
-          if (desc ? (a < b) : (a > b)) {
-            buf[i] = b;
-            buf[j] = a;
-          }
+      for (int x = threadIdx.x; x < P / 2; x += kRankT) {
+        const int i = ((x & ~(stride - 1)) << 1) | (x & (stride - 1));
+        const uint64_t a = buf[i], b = buf[i + stride];
+        if ((i & size) == 0 ? a < b : a > b) {
+          buf[i] = b;
+          buf[i + stride] = a;
         }
       }
       __syncthreads();
     }
-  }
-  bool shortfall = false;
-  const float* row = scores + (int64_t)r * ld_s;
-  for (int i = tid; i < k; i += nt) {
-    const uint64_t c = buf[i];
-    if (c == 0ull) {
-      idx[(int64_t)r * k + i] = -1;
-      if (val) val[(int64_t)r * k + i] = __uint_as_float(0x7FC00000u);
-      shortfall = true;
-    } else {
-      const int32_t ii = (int32_t)(~(uint32_t)(c & 0xFFFFFFFFull));
-      idx[(int64_t)r * k + i] = ii;
-      if (val) val[(int64_t)r * k + i] = row[ii];
-    }
-  }
-  if (__syncthreads_or(shortfall) && tid == 0) set_status(st, FATHOM_DEV_TOPK_SHORT);
 }
 
-__global__ void topk_clear_sel_kernel(uint64_t* __restrict__ sel, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < total) sel[i] = 0ull;
+__global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restrict__ scores, int64_t ld_s,
+                                                           const int64_t* __restrict__ n, int G, int R, int64_t lo,
+                                                           int64_t tail, int k, TopkWs ws, int32_t* __restrict__ idx,
+                                                           float* __restrict__ val, uint32_t* __restrict__ st) {
+  extern __shared__ __attribute__((aligned(16))) uint64_t grp[];
+  __shared__ uint32_t hist[kRankMaxSub + 1];
+  __shared__ uint32_t red[3][kRankT / kWave];
+  __shared__ uint32_t s_first[kRankShare + 1];
+  __shared__ uint32_t s_fill;
+  // a row's workgroups on one XCD (workgroups are dealt to the 8 XCDs in turn): its list comes into one L2
+  const int r = (int)(blockIdx.x / (8 * kRankShare)) * 8 + (int)(blockIdx.x % 8);
+  const int z = (int)(blockIdx.x / 8) % kRankShare;
+  if (r >= R) return;
+  const int u = r / G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t* list = ws.list + (int64_t)r * ws.lcap;
+  uint64_t pv[kRankRegs];
+#pragma unroll
+  for (int x = 0; x < kRankRegs; ++x) {  // entries past the count are read but not used
+    const int e = tid + kRankT * x;
+    pv[x] = e < ws.lcap ? list[e] : 0ull;
+  }
+  const RowState S = ws.state[r];
+  const float* row = scores + (int64_t)r * ld_s;
+  const uint32_t c = S.count < (uint32_t)ws.lcap ? S.count : (uint32_t)ws.lcap;
+  auto emit = [&](uint32_t rank, uint64_t v) {
+    const int32_t i = (int32_t)(~(uint32_t)v);
+    idx[(int64_t)r * k + rank] = i;
+    if (val) val[(int64_t)r * k + rank] = row[i];
+  };
+  if (S.strict) {  // the keys above, then the first equal ones in index order
+    if (z != 0) return;
+    const RowRange rr = row_range(n, u, ld_s, lo, tail, nullptr);
+    int P = 1;
+    while (P < k) P <<= 1;
+    for (uint32_t e = tid; e < (uint32_t)P; e += kRankT) grp[e] = e < c ? list[e] : 0ull;
+    if (tid == 0) s_fill = c;
+    __syncthreads();
+    for (int64_t b = rr.lo; b < rr.hi && s_fill < (uint32_t)k; b += kRankT * kRankRegs) {
+      const int64_t i0 = b + tid * kRankRegs;  // eight in a row per thread: thread order is index order
+      uint32_t eq = 0;
+#pragma unroll
+      for (int x = 0; x < kRankRegs; ++x)
+        if (i0 + x < rr.hi && score_key(row[i0 + x]) == S.prefix) eq |= 1u << x;
+      const int mine = __popc(eq);
+      int inc = mine;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += y;
+      }
+      if (lane == 63) red[0][wave] = (uint32_t)inc;
+      __syncthreads();
+      uint32_t at = s_fill + (uint32_t)(inc - mine), sum = 0;
+      for (int x = 0; x < kRankT / kWave; ++x) {
+        if (x < wave) at += red[0][x];
+        sum += red[0][x];
+      }
+#pragma unroll
+      for (int x = 0; x < kRankRegs; ++x)
+        if (eq & (1u << x)) {
+          if (at < (uint32_t)k) grp[at] = ((uint64_t)S.prefix << 32) | (uint64_t)(~(uint32_t)(i0 + x));
+          ++at;
+        }
+      __syncthreads();  // s_fill and red read by all
+      if (tid == 0) s_fill += sum;
+      __syncthreads();
+    }
+    sort_desc(grp, P);
+    for (int e = tid; e < k; e += kRankT) emit((uint32_t)e, grp[e]);
+    return;
+  }
+  const uint32_t K = c < (uint32_t)k ? c : (uint32_t)k;
+  if (z == 0 && K < (uint32_t)k) {  // fewer eligible keys than k
+    for (int e = (int)K + tid; e < k; e += kRankT) {
+      idx[(int64_t)r * k + e] = -1;
+      if (val) val[(int64_t)r * k + e] = __uint_as_float(0x7FC00000u);
+    }
+    if (tid == 0) set_status(st, FATHOM_DEV_TOPK_SHORT);
+  }
+  if (K == 0) return;
+  auto each = [&](auto fn) {  // every list entry
+#pragma unroll
+    for (int x = 0; x < kRankRegs; ++x)
+      if (tid + kRankT * x < (int)c) fn(pv[x]);
+    for (uint32_t e = tid + kRankT * kRankRegs; e < c; e += kRankT) fn(list[e]);
+  };
+  int ns = 64;  // sub-buckets: a power of two, at least the entries
+  while (ns < (int)c && ns < kRankMaxSub) ns <<= 1;
+  for (int x = tid; x <= ns; x += kRankT) hist[x] = 0u;
+  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+  each([&](uint64_t v) {
+    const uint32_t key = (uint32_t)(v >> 32);
+    kmin = key < kmin ? key : kmin;
+    kmax = key > kmax ? key : kmax;
+  });
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const uint32_t a = __shfl_xor(kmin, m, kWave), b = __shfl_xor(kmax, m, kWave);
+    kmin = a < kmin ? a : kmin;
+    kmax = b > kmax ? b : kmax;
+  }
+  if (lane == 0) {
+    red[0][wave] = kmin;
+    red[1][wave] = kmax;
+  }
+  __syncthreads();
+  for (int x = 0; x < kRankT / kWave; ++x) {
+    kmin = red[0][x] < kmin ? red[0][x] : kmin;
+    kmax = red[1][x] > kmax ? red[1][x] : kmax;
+  }
+  // sub-bucket: floor((kmax - key) * scale), not decreasing as the key falls
+  const float scale = kmax > kmin ? (float)(ns - 1) / (float)(kmax - kmin) : 0.0f;
+  auto sub_of = [&](uint64_t v) {
+    const int sb = (int)__fmul_rn((float)(kmax - (uint32_t)(v >> 32)), scale);
+    return sb < ns - 1 ? sb : ns - 1;
+  };
+  each([&](uint64_t v) { atomicAdd(&hist[sub_of(v)], 1u); });
+  __syncthreads();
+  // exclusive prefix in place (thread t owns a run of ns / kRankT sub-buckets, or one), hist[ns] = c
+  const int per = ns / kRankT > 0 ? ns / kRankT : 1, x0 = tid * per;
+  uint32_t run = 0, most = 0;
+  for (int x = x0; x < x0 + per && x < ns; ++x) {
+    run += hist[x];
+    most = hist[x] > most ? hist[x] : most;
+  }
+  uint32_t inc = run;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(inc, o, kWave);
+    if (lane >= o) inc += y;
+    const uint32_t m = __shfl_xor(most, o, kWave);
+    most = m > most ? m : most;
+  }
+  if (lane == 63) {
+    red[0][wave] = inc;
+    red[2][wave] = most;
+  }
+  if (tid <= kRankShare && (uint32_t)tid * K / kRankShare == 0u) s_first[tid] = 0u;
+  __syncthreads();
+  uint32_t acc = inc - run;
+  for (int x = 0; x < kRankT / kWave; ++x) {
+    if (x < wave) acc += red[0][x];
+    most = red[2][x] > most ? red[2][x] : most;
+  }
+  for (int x = x0; x < x0 + per && x < ns; ++x) {
+    const uint32_t hx = hist[x];
+    hist[x] = acc;
+    // part y starts at the first sub-bucket whose first position is at least y K / parts:
+    // after the one whose positions cross that bound
+#pragma unroll
+    for (int y = 1; y <= kRankShare; ++y) {
+      const uint32_t b = (uint32_t)y * K / kRankShare;
+      if (acc < b && acc + hx >= b) s_first[y] = (uint32_t)x + 1u;
+    }
+    acc += hx;
+  }
+  if (tid == 0) hist[ns] = c;
+  __syncthreads();
+  bool sorted = most > (uint32_t)kRankSame;
+  for (int y = 0; y < kRankShare; ++y) sorted |= hist[s_first[y + 1]] - hist[s_first[y]] > (uint32_t)kRankGroup;
+  if (sorted) {  // the same for every workgroup of the row: the first sorts the whole list
+    if (z != 0) return;
+    int P = 1;
+    while (P < (int)c) P <<= 1;
+    for (uint32_t e = tid; e < (uint32_t)P; e += kRankT) grp[e] = e < c ? list[e] : 0ull;
+    __syncthreads();
+    sort_desc(grp, P);
+    for (uint32_t e = tid; e < K; e += kRankT) emit(e, grp[e]);
+    return;
+  }
+  const int s0 = (int)s_first[z], s1 = (int)s_first[z + 1];
+  if (s0 == s1) return;
+  const uint32_t start = hist[s0], share = hist[s1] - start;
+  __syncthreads();  // every bound read before hist[s0 .. s1) serve as cursors
+  each([&](uint64_t v) {  // group by sub-bucket; hist[s] ends at the group's end
+    const int sb = sub_of(v);
+    if (sb >= s0 && sb < s1) grp[atomicAdd(&hist[sb], 1u) - start] = v;
+  });
+  __syncthreads();
+  for (uint32_t e = tid; e < share; e += kRankT) {
+    const uint64_t v = grp[e];
+    const int sb = sub_of(v);
+    const uint32_t g0 = sb > s0 ? hist[sb - 1] : start, g1 = hist[sb];
+    uint32_t rank = g0;
+    for (uint32_t x = g0; x < g1; ++x) rank += grp[x - start] > v;
+    if (rank < K) emit(rank, v);
+  }
 }
 
 fathom_status launch_topk(const float* scores, int64_t ld_s, const int64_t* n, int U, int G, int k,
@@ -331,26 +451,16 @@ fathom_status launch_topk(const float* scores, int64_t ld_s, const int64_t* n, i
   const int R = U * G;
   if (R == 0) return FATHOM_OK;
   const int64_t nch = topk_chunks(ld_s) > 0 ? topk_chunks(ld_s) : 1;
-  TopkWs w = carve(ws, R, ld_s, k);
-  hipLaunchKernelGGL(topk_init_kernel, dim3(R), dim3(256), 0, s, w.state, w.hist, k);
-  const int shifts[3] = {21, 10, 0}, bits[3] = {11, 11, 10};
-  for (int pass = 0; pass < 3; ++pass) {
-    hipLaunchKernelGGL(topk_hist_kernel, dim3((unsigned)nch, (unsigned)R), dim3(kTopkThreads), 0, s, scores,
-                       ld_s, n, G, lo, tail, shifts[pass], bits[pass], w.state, w.hist, st, pass == 0 ? 1 : 0);
-    hipLaunchKernelGGL(topk_pivot_kernel, dim3(R), dim3(kTopkThreads), 0, s, shifts[pass], bits[pass], w.state,
-                       w.hist);
-  }
-  hipLaunchKernelGGL(topk_count_kernel, dim3((unsigned)nch, (unsigned)R), dim3(kTopkThreads), 0, s, scores, ld_s,
-                     n, G, lo, tail, nch, w.state, w.cnt);
-  hipLaunchKernelGGL(topk_scan_kernel, dim3(R), dim3(64), 0, s, nch, w.state, w.cnt);
-  const int64_t total = (int64_t)R * k;
-  hipLaunchKernelGGL(topk_clear_sel_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, w.sel, total);
-  hipLaunchKernelGGL(topk_write_kernel, dim3((unsigned)nch, (unsigned)R), dim3(kTopkThreads), 0, s, scores, ld_s,
-                     n, G, lo, tail, nch, k, w.state, w.cnt, w.sel);
-  int P = 1;
-  while (P < k) P <<= 1;
-  hipLaunchKernelGGL(topk_sort_kernel, dim3(R), dim3(1024), (size_t)P * 8, s, scores, ld_s, k, w.sel, idx, val,
-                     st);
+  const TopkWs w = carve(ws, R, k);
+  hipLaunchKernelGGL(topk_init_kernel, dim3(R), dim3(1024), 0, s, w.state, reinterpret_cast<uint4*>(w.hist), k);
+  // Up to 2048 workgroups in the first two passes (a merged histogram each), 256
+  // in the later ones, which most rows leave at once.
+  const int64_t most = std::max(2048 / R, 8), few = std::max(256 / R, 8);
+  for (int pass = 0; pass <= kDigits; ++pass)
+    hipLaunchKernelGGL(topk_pass_kernel, dim3((unsigned)std::min(nch, pass < 2 ? most : few), (unsigned)R),
+                       dim3(kTopkThreads), 0, s, scores, ld_s, n, G, lo, tail, pass, w, st);
+  hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)((R + 7) / 8 * 8 * kRankShare)), dim3(kRankT),
+                     rank_lds_keys(w.lcap) * 8, s, scores, ld_s, n, G, R, lo, tail, k, w, idx, val, st);
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;
 }
