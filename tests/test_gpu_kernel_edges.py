@@ -220,3 +220,39 @@ def test_scan_stages(G, qdt, U, nb_cap):
                                 q[u].astype(np.float32), depths[u])
         m = min(n, ld)
         assert np.array_equal(s[u, :, :m].cpu().numpy().view(np.uint32), ref[:, :m].view(np.uint32)), u
+
+
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_alloc_depths_extremes(G):
+    """Importances from subnormal to 1e38, equal and zero ones, and every budget's
+    ends: the 32-bit candidate keys and the early end of the search against the
+    oracle's exact candidates; top-r ranks with equal weights."""
+    rng = np.random.default_rng(G)
+    U = 9
+    q = rng.standard_normal((U, G, D)).astype(np.float32)
+    var = np.exp(rng.standard_normal((U, D))).astype(np.float32)
+    var[1] = np.exp(rng.uniform(-103, 80, D)).astype(np.float32)      # subnormal to huge
+    q[2], var[2] = 1.0, 1.0                                            # all equal
+    q[3] = np.round(q[3])                                              # many equal, many zero
+    var[3] = 4.0 ** rng.integers(-3, 4, D)
+    var[4] = 0.0
+    var[5, 1:] = 0.0
+    var[6, ::2] = 0.0
+    q[7] *= np.float32(1e-22)                                          # squares in the subnormals
+    q[8] *= np.float32(1e18)
+    for B in (0, 1, 2, 47, 128, 500, 511, 512):
+        st = F.new_status()
+        d, th = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, B, dev_status=st)
+        d, th, flags = d.cpu().numpy(), th.cpu().numpy(), status(st)
+        want = 0
+        for u in range(U):
+            od, oth, ost = oracle.alloc_waterfill(q[u], var[u], B)
+            want |= ost
+            assert np.array_equal(d[u], od), (B, u)
+            assert th[u] == np.float32(oth), (B, u)
+        assert flags == want
+    for r in (0, 1, 63, 127, 128):
+        d, th = F.fathom_alloc_depths(dev(q), None, F.FATHOM_UNIFORM_TOPR, r)
+        for u in range(U):
+            od = oracle.alloc_topr(q[u], r)[0]
+            assert np.array_equal(d[u].cpu().numpy(), od), (r, u)
