@@ -11,11 +11,16 @@
 
 namespace fathom {
 
-constexpr int kCG = 20;          // row groups at most (5 slices of 4)
-constexpr int kCC = 4 * kCG;     // cells at most
-constexpr int kCA = 80;          // active channels at most
+// Two sizes: CellPlan for units of at most 80 cells (20 row groups, 5 slices
+// of 4), whose filter's LDS has no room for more, and CellPlanWide for up to
+// 128 (every channel of a unit, or 32 channels at 4 planes).
+constexpr int kCC = 80, kCCWide = 128;  // cells at most
 
-struct alignas(16) CellPlan {
+template <int CC>
+struct alignas(16) CellPlanT {
+  static constexpr int kCG = CC / 4;  // row groups at most
+  static constexpr int kCC = CC;      // cells at most
+  static constexpr int kCA = CC;      // active channels at most
   int A, rg, C, ok;        // active channels, row groups, cells, the unit fits this pass
   int np[4];               // cells of plane p: the channels of depth > p
   int base[5];             // first cell of plane p (base[4] = C)
@@ -30,13 +35,17 @@ struct alignas(16) CellPlan {
   uint8_t pj[kCA];         // proxy index -> channel
   uint8_t py[kCA];         // proxy index -> ascending position (q of proxy x: qa[py[x]])
 };
+using CellPlan = CellPlanT<kCC>;
+using CellPlanWide = CellPlanT<kCCWide>;
 constexpr uint32_t kCPad = 0xFFFFu;
 
 typedef unsigned int PlanWord __attribute__((ext_vector_type(4)));  // plans move 16 bytes a thread and step
-constexpr int kPlanWords = (int)((sizeof(CellPlan) + 15) / 16);
+template <class Plan>
+constexpr int kPlanWords = (int)((sizeof(Plan) + 15) / 16);
 constexpr int kPlanSteps = 2;  // copy steps of 256 threads
-static_assert(sizeof(CellPlan) % 16 == 0 && sizeof(CellPlan) <= kPlanBytes, "a unit's plan fits its workspace slot");
-static_assert(kPlanWords <= kPlanSteps * kFT, "two 16-byte words per thread copy a plan");
+static_assert(sizeof(CellPlan) % 16 == 0 && sizeof(CellPlanWide) % 16 == 0 && sizeof(CellPlanWide) <= kPlanBytes,
+              "a unit's plan fits its workspace slot");
+static_assert(kPlanWords<CellPlanWide> <= kPlanSteps * kFT, "two 16-byte words per thread copy a plan");
 
 // ---------------------------------------------------------------- plan
 // Depth and q of channel tid (< 128), read by the kernel before its other
@@ -63,7 +72,8 @@ __device__ __forceinline__ CellPre cell_load(const FusedArgs& a, int u) {
 
 // Builds the plan of unit u (all threads of the workgroup).  P.ok is false
 // when the unit exceeds this pass's limits or has no active channel.
-__device__ __forceinline__ void cell_plan(CellPlan& P, const FusedArgs& a, const CellPre& pre) {
+template <class Plan>
+__device__ __forceinline__ void cell_plan(Plan& P, const FusedArgs& a, const CellPre& pre) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, G = a.G;
   __shared__ int cnt[2][kPlanes + 1];
   __shared__ int sact[kD];  // proxy index -> channel j | depth << 8
@@ -94,7 +104,7 @@ __device__ __forceinline__ void cell_plan(CellPlan& P, const FusedArgs& a, const
 #pragma unroll
   for (int p = 0; p < kPlanes; ++p) base[p + 1] = base[p] + np[p];
   const int C = base[kPlanes], rg = (C + 3) >> 2;
-  const bool ok = G <= 4 && A > 0 && A <= kCA && C <= kCC;
+  const bool ok = G <= 4 && A > 0 && A <= Plan::kCA && C <= Plan::kCC;
   if (tid == 0) {
     P.A = A;
     P.rg = rg;
@@ -141,7 +151,7 @@ __device__ __forceinline__ void cell_plan(CellPlan& P, const FusedArgs& a, const
   // uses -q 2^-p, so every cell shares one rounding constant per group and
   // head (the scaling is exact unless q 2^-p is subnormal, and then the cell's
   // weight is 0 either way: |q a16 2^-p| < 2^-110 is far below delta / 2)
-  if (tid < kCC) {
+  if (tid < Plan::kCC) {
     const int c = tid, g = c >> 2, k = c & 3;
     int p = 0;
 #pragma unroll

@@ -1,6 +1,7 @@
-// Full pass of fathom_scan_topk for units of at most 80 cells (one per
-// active channel and plane: every unit of at most 80 depth bits, so every
-// unit under water-filling at B <= 80 and uniform depth at r <= 16): an int8
+// Full pass of fathom_scan_topk for units of at most 128 cells (one per
+// active channel and plane: every unit of at most 128 depth bits, so every
+// unit under water-filling at B <= 128 and uniform depth at r <= 32, given the
+// caller's bound; of at most 64 without one): an int8
 // MFMA proxy of every key's four head
 // scores over its plane bits, exact re-scoring of the keys the proxy's bound
 // cannot exclude, and the appends of keys with exact score >= tau to their
@@ -17,8 +18,8 @@
 //   |s - delta (S - Wsum / 2)| <= delta cells / 4 + (A^2 127 2^-24) delta
 // (weight rounding, then the A roundings of the fp32 chain), plus A 2^-120
 // for subnormal results.  A key is a candidate for head h iff
-// S >= thr = floor((floor(2 (tau - E) / delta) - 1 + Wsum) / 2).  At three
-// and five slices the weights have two levels, W' = 128 W + W_lo in units
+// S >= thr = floor((floor(2 (tau - E) / delta) - 1 + Wsum) / 2).  At three,
+// five and eight slices the weights have two levels, W' = 128 W + W_lo in units
 // of delta / 128 (the bound's cell term shrinks by 128).
 //
 // Layout.  Cells are ordered plane-major without padding (plane p's cells are
@@ -53,29 +54,34 @@ constexpr int kSv = 8;           // survivors per head buffered in LDS before a 
 
 // Geometry of an instantiation with NS slices of 4 row groups (16 cells):
 // NS = 3 serves units of at most 48 cells, NS = 4 of at most 64, NS = 5 of
-// at most 80.  The scale ring holds one row of C + 2 halfs per block (an odd
+// at most 80, NS = 8 of at most 128 (two workgroups per CU, 217 VGPRs, 80,608
+// bytes of LDS: the 2^20-token layer at 32 channels of 4 planes takes 91.6 us,
+// 204 us in the wide pass with its tau pass).  The scale ring holds one row of C + 2 halfs per block (an odd
 // number of dwords, so the lanes of a re-scoring batch fall in different
 // banks) for Slots groups; three workgroups per CU fit the LDS with 6 slots
 // at NS = 3 (a wave's 6 groups of the 2^20-token layer: no flush before its
 // end), 3 at NS = 4 and 2 at NS = 5 with a queue of 32 candidates (the
 // space of the second-level weights; 24 candidates with 3 slots ran as
-// fast, 48 with 1 slot 19 % slower).  NS = 3 and 5 have two-level weights
-// (at NS = 5 the MFMA loop runs slice by slice so that one slice's two
+// fast, 48 with 1 slot 19 % slower).  NS = 3, 5 and 8 have two-level
+// weights (from NS = 5 the MFMA loop runs slice by slice so that one slice's two
 // weight sets are live at a time); NS = 4 keeps one level.  A lane stages K plane words per quad: 4 cells of its row group up to
-// NS = 4, at NS = 5 the cells lane / 4 + 16 k, k < 5.
+// NS = 4, beyond the cells lane / 4 + 16 k, k < NS.
 template <int NS>
 struct CGeo {
-  static_assert(NS >= 3 && NS <= 5, "three to five slices");
+  static_assert((NS >= 3 && NS <= 5) || NS == 8, "three to five slices, or eight");
   static constexpr int G = 4 * NS;
   static constexpr int C = 4 * G;
   static constexpr int Slots = NS == 3 ? 6 : NS == 4 ? 3 : 2;
   static constexpr int SclRow = C + 2;
   static constexpr bool Fine = NS != 4;  // two-level weights (slice-outer at five slices, so the registers fit them)
-  static constexpr int Q = NS == 5 ? 32 : 64;  // queued candidates per wave; re-scored at a quad boundary once full
-  static constexpr int K = NS == 5 ? 5 : 4;    // plane words a lane stages per quad
+  static constexpr int Q = NS == 8 ? 40 : NS == 5 ? 32 : 64;  // queued candidates per wave; re-scored at a quad boundary once full
+  static constexpr int K = NS > 4 ? NS : 4;    // plane words a lane stages per quad
+  static constexpr int PerCU = NS == 8 ? 2 : 3;  // workgroups per CU
 };
+template <int NS>
+using FPlan = CellPlanT<(NS > 5 ? kCCWide : kCC)>;
 // Fine weights W' = 128 W + W_lo count in units of delta / 128; |W'| <=
-// 127 * 128 + 64, so |S'| < 2^21 for up to 80 cells: thresholds are clamped
+// 127 * 128 + 64, so |S'| < 2^21 for up to 128 cells: thresholds are clamped
 // to +-2^21 and an accumulator stays below 2^29.
 constexpr int kCThrMax = 1 << 21;
 constexpr int kCWaves = 4;       // waves per workgroup
@@ -114,7 +120,7 @@ __device__ __forceinline__ uint64_t lanes_below(int lane) { return lane == 0 ? 0
 
 // ---------------------------------------------------------------- scales
 // Lane c (< C) holds the 8 scales of cell c's channel (scale row jrow) for the
-// group at block sb0, two blocks a dword, and at NS = 5 lane l also those of
+// group at block sb0, two blocks a dword, and from NS = 5 lane l also those of
 // cell 64 + l (row jrow2), read through a buffer descriptor over the unit's
 // scale rows (zero past them, and for cells >= C; the lanes of one channel's
 // cells read the same bytes).  With 16-byte aligned rows
@@ -178,7 +184,7 @@ struct CDel {
 // its channel's scale, so the plane-0 cell of proxy channel x is cell x) and
 // returns delta of head `hq` (every lane: its own head for the weights).  qv:
 // q of cell `lane`'s channel for the four heads (0 past the cells), qv2 that
-// of cell 64 + lane (NS = 5).
+// of cell 64 + lane (from NS = 5).
 __device__ __forceinline__ uint32_t cscl_absmax(const uint32_t (&v)[kCSB / 2]) {
   uint32_t mx = 0u;
 #pragma unroll
@@ -238,12 +244,12 @@ __device__ __forceinline__ CDel cscl_commit(const CScl<NS>& r, FilterLds<NS>& L,
 // Lane (block bq = lane & 3 of the quad) loads the plane words of K cells for
 // its block through a buffer descriptor over the unit's planes, and stores
 // them as raw[cell][bq]: up to NS = 4 the 4 cells of row group g = lane >> 2,
-// at NS = 5 the cells lane / 4 + 16 k.  Pad cells (and row groups past the
+// beyond the cells lane / 4 + 16 k.  Pad cells (and row groups past the
 // unit's) read past the descriptor's range, which returns zero; every other
 // load stays inside the unit.
 template <int NS>
 __device__ __forceinline__ int cstage_cell(int lane, int k) {
-  return CGeo<NS>::K == 5 ? (lane >> 2) + 16 * k : 4 * (lane >> 2) + k;
+  return (CGeo<NS>::K > 4) ? (lane >> 2) + 16 * k : 4 * (lane >> 2) + k;
 }
 template <int NS>
 struct CStage {
@@ -260,17 +266,17 @@ struct CRaw {
 // 40) bytes) added it stays past the range without wrapping (4104 nb_cap +
 // 320 < 2^32 for nb_cap < kOneNbMax).
 template <int NS>
-__device__ __forceinline__ void cstage_setup(CStage<NS>& S, const CellPlan& P, const FusedArgs& a, uint64_t ubase,
+__device__ __forceinline__ void cstage_setup(CStage<NS>& S, const FPlan<NS>& P, const FusedArgs& a, uint64_t ubase,
                                              uint32_t ub) {
   const int lane = threadIdx.x & 63, g = lane >> 2, bq = lane & 3;
   const uint32_t alo = (uint32_t)cuni((int)(uint32_t)ubase), ahi = (uint32_t)cuni((int)(uint32_t)(ubase >> 32));
   S.rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)ahi << 32) | alo), (short)0,
                                           (int)(uint32_t)cuni((int)ub), kRawBufferFlags);
-  if constexpr (CGeo<NS>::K == 5) {
+  if constexpr ((CGeo<NS>::K > 4)) {
     // cell c's row: half c & 1 of word (c >> 1) & 1 of row group c >> 2
     // (kCPad for every cell past the unit's)
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
+    for (int k = 0; k < CGeo<NS>::K; ++k) {
       const int c = cstage_cell<NS>(lane, k);
       const uint32_t row = (P.rrow[c >> 2][(c >> 1) & 1] >> (16 * (c & 1))) & 0xFFFFu;
       S.boff[k] = row != kCPad ? (row * (uint32_t)a.nb_cap + (uint32_t)bq) * 8u : ub;
@@ -304,9 +310,9 @@ __device__ __forceinline__ void cstage_issue(CRaw<NS>& R, const CStage<NS>& S, i
 template <int NS>
 __device__ __forceinline__ void cstage_write(const CRaw<NS>& R, FilterLds<NS>& L) {
   const int lane = threadIdx.x & 63, g = lane >> 2, bq = lane & 3;
-  if constexpr (CGeo<NS>::K == 5) {
+  if constexpr ((CGeo<NS>::K > 4)) {
 #pragma unroll
-    for (int k = 0; k < 5; ++k) L.raw[cstage_cell<NS>(lane, k)][bq] = R.w[k];
+    for (int k = 0; k < CGeo<NS>::K; ++k) L.raw[cstage_cell<NS>(lane, k)][bq] = R.w[k];
   } else if (g < CGeo<NS>::G) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) L.raw[4 * g + k][bq] = R.w[k];
@@ -345,7 +351,7 @@ struct CHead {
 };
 
 template <int NS>
-__device__ __forceinline__ void cquad_weights(const CellPlan& P, FilterLds<NS>& L, const CHead& H, int slot, int sbq) {
+__device__ __forceinline__ void cquad_weights(const FPlan<NS>& P, FilterLds<NS>& L, const CHead& H, int slot, int sbq) {
   const int lane = threadIdx.x & 63, b = lane >> 4, h = (lane >> 2) & 3, part = lane & 3;
   const uint16_t* srow = &L.scl[slot][sbq + b][0];
   // every read first: row groups g = part + 4 k, cells 4 g .. 4 g + 3
@@ -427,7 +433,7 @@ __device__ __forceinline__ void cappend(FilterLds<NS>& L, const FusedArgs& a, in
 // the chain runs over the active channels ascending (padded to a multiple of
 // 4 with q = 0, which leaves every score unchanged).
 template <int NS>
-__device__ __forceinline__ void crescore(const CellPlan& P, FilterLds<NS>& L, const FusedArgs& a, int u, int nq, int (&svn)[4]) {
+__device__ __forceinline__ void crescore(const FPlan<NS>& P, FilterLds<NS>& L, const FusedArgs& a, int u, int nq, int (&svn)[4]) {
   const int lane = threadIdx.x & 63, G = a.G;
   const bool on = lane < nq;
   const int e = on ? lane : 0;
@@ -551,7 +557,7 @@ struct CGroups {
   int ctr;        // the pool counter of this wave: word ctr of the pool counters (-1: no pool)
 };
 template <bool VEC, int NS, class Ready>
-__device__ __forceinline__ void cwave_run(const CellPlan& P, FilterLds<NS>& L, const FusedArgs& a, int u, const CGroups& gs,
+__device__ __forceinline__ void cwave_run(const FPlan<NS>& P, FilterLds<NS>& L, const FusedArgs& a, int u, const CGroups& gs,
                                           int nbu, int lo, int hi, Ready&& ready) {
   using Geo = CGeo<NS>;
   const int lane = threadIdx.x & 63;
@@ -567,7 +573,7 @@ __device__ __forceinline__ void cwave_run(const CellPlan& P, FilterLds<NS>& L, c
   const int cxl = P.cx[lane];                  // cell `lane`'s channel (proxy index)
   const int srow = lane < C ? P.pj[cxl] : 0;   // its scale row
   const int yl = P.py[cxl];                    // its ascending position (q: qa[yl])
-  // cell 64 + lane's channel (NS = 5; read from the plan where needed, so
+  // cell 64 + lane's channel (from NS = 5; read from the plan where needed, so
   // that no register holds it across the loop)
   auto cell2 = [&]() -> int { return Geo::C > kWave && lane + kWave < C ? P.cx[kWave + lane] : 0; };
   // as a transpose source: cell (l & 15) >> 1 of pair 0, block l >> 4
@@ -620,7 +626,7 @@ __device__ __forceinline__ void cwave_run(const CellPlan& P, FilterLds<NS>& L, c
       xr[2 * pp] = (uint32_t)v.x;
       xr[2 * pp + 1] = (uint32_t)v.y;
     }
-    if constexpr (Geo::Fine && NS == 5) {
+    if constexpr (Geo::Fine && NS >= 5) {
       // slices outer: one slice's W and W_lo live at a time, the W chain of
       // each position kept apart and scaled by 128 into the W_lo chain
       v4i ah[4];
@@ -764,7 +770,7 @@ __device__ __forceinline__ void cwave_run(const CellPlan& P, FilterLds<NS>& L, c
         const bool on = lane < C;
         qv[0] = on ? q4.x : 0.0f; qv[1] = on ? q4.y : 0.0f; qv[2] = on ? q4.z : 0.0f; qv[3] = on ? q4.w : 0.0f;
       }
-      float qv2[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // cell 64 + lane's (NS = 5)
+      float qv2[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // cell 64 + lane's (from NS = 5)
       int srow2 = 0;
       if constexpr (Geo::C > kWave) {
         const int x2 = cell2();
@@ -875,13 +881,17 @@ __device__ __forceinline__ float ctau(const FusedArgs& a, const float (&sv)[kCTa
 // pool.  With fewer than 2 static groups per wave every group is static.
 // Units of another class (uovf[u] >> 1 != 1: the wide pass, or no filter) and
 // rows computed exactly return at once.
-// Three workgroups per CU: LDS is handed out in 1280-byte units, so a
-// workgroup may hold at most 42 of them (a 53,984-byte build ran two per CU).
-constexpr size_t kCLdsMax = 42 * 1280;
+// Three workgroups per CU (two at eight slices): LDS is handed out in
+// 1280-byte units, 128 a CU, so a workgroup may hold at most 42 (64) of them (a
+// 53,984-byte build ran two per CU).
+template <int NS>
+constexpr size_t kCLdsMax = 128 / CGeo<NS>::PerCU * 1280;
 template <bool VEC, int NS>
-__global__ __launch_bounds__(kCThreads, 3) void fused_filter_kernel(FusedArgs a, int U, int W) {
-  static_assert(sizeof(CellPlan) + kCWaves * sizeof(FilterLds<NS>) <= kCLdsMax, "three workgroups per CU");
-  __shared__ CellPlan P;
+__global__ __launch_bounds__(kCThreads, CGeo<NS>::PerCU) void fused_filter_kernel(FusedArgs a, int U, int W) {
+  using Plan = FPlan<NS>;
+  constexpr int kPlanWords = fathom::kPlanWords<Plan>;
+  static_assert(sizeof(Plan) + kCWaves * sizeof(FilterLds<NS>) <= kCLdsMax<NS>, "three (two) workgroups per CU");
+  __shared__ Plan P;
   __shared__ FilterLds<NS> WL[kCWaves];
   const int u = (int)(blockIdx.x % (unsigned)U), x = (int)(blockIdx.x / (unsigned)U);
   const int tid = threadIdx.x, wave = cuni(tid >> 6), lane = tid & 63, G = a.G;
@@ -948,30 +958,29 @@ __global__ __launch_bounds__(kCThreads, 3) void fused_filter_kernel(FusedArgs a,
   cwave_run<VEC, NS>(P, WL[wave], a, u, gs, (int)nbu, (int)lo, (int)hi, ready);
 }
 
-// Workgroups per unit: about kFResident of them over all units (three per
-// CU, one round), and no more than one group per wave.
-constexpr int64_t kFResident = 3 * 256;
-void launch_filter(const FusedArgs& fa, int U, int max_cells, hipStream_t s) {
+// Workgroups per unit: about one round over all units (three or two per CU),
+// and no more than one group per wave.
+template <int NS>
+static void launch_filter_ns(const FusedArgs& fa, int U, hipStream_t s) {
   const int64_t ngr = (fa.nb_cap + kCSB - 1) / kCSB;
-  int64_t W = kFResident / U;
+  int64_t W = (int64_t)CGeo<NS>::PerCU * 256 / U;
   const int64_t wmax = (ngr + kCWaves - 1) / kCWaves;
   if (W > wmax) W = wmax;
   if (W < 1) W = 1;
   const dim3 grid((unsigned)(W * U));
   // 16-byte aligned scale rows: one 16-byte scale load per lane and group
   const bool vec = (fa.nb_cap & 7) == 0 && (reinterpret_cast<uintptr_t>(fa.scales) & 15) == 0;
-  // three slices when no unit can have more than 48 cells, five when units
-  // of up to 80 cells take the filter (fa.ccap), else four
-  if (max_cells > 0 && max_cells <= CGeo<3>::C) {
-    if (vec) hipLaunchKernelGGL((fused_filter_kernel<true, 3>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
-    else hipLaunchKernelGGL((fused_filter_kernel<false, 3>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
-  } else if (fa.ccap > CGeo<4>::C) {
-    if (vec) hipLaunchKernelGGL((fused_filter_kernel<true, 5>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
-    else hipLaunchKernelGGL((fused_filter_kernel<false, 5>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
-  } else {
-    if (vec) hipLaunchKernelGGL((fused_filter_kernel<true, 4>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
-    else hipLaunchKernelGGL((fused_filter_kernel<false, 4>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
-  }
+  if (vec) hipLaunchKernelGGL((fused_filter_kernel<true, NS>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
+  else hipLaunchKernelGGL((fused_filter_kernel<false, NS>), grid, dim3(kCThreads), 0, s, fa, U, (int)W);
+}
+
+// Three slices when no unit can have more than 48 cells; eight or five when
+// units of up to 128 or 80 cells take the filter (fa.ccap); else four.
+void launch_filter(const FusedArgs& fa, int U, int max_cells, hipStream_t s) {
+  if (max_cells > 0 && max_cells <= CGeo<3>::C) launch_filter_ns<3>(fa, U, s);
+  else if (fa.ccap > CGeo<5>::C) launch_filter_ns<8>(fa, U, s);
+  else if (fa.ccap > CGeo<4>::C) launch_filter_ns<5>(fa, U, s);
+  else launch_filter_ns<4>(fa, U, s);
 }
 
 }  // namespace fathom

@@ -710,10 +710,10 @@ __device__ __forceinline__ uint32_t unit_class(const FusedArgs& a, const int (&s
                                                int64_t hi) {
   const int A = sc[1] + sc[2] + sc[3] + sc[4];
   if (!(a.G <= 4 && A > 0 && hi - lo > a.ws.cap)) return 0u;
-  // the launched cell filter takes at most kCA channels and a.ccap cells (one
+  // the launched cell filter takes at most a.ccap cells (one
   // per active channel and plane)
   const int cells = sc[1] + 2 * sc[2] + 3 * sc[3] + 4 * sc[4];
-  if (A <= kCA && cells <= a.ccap && a.nb_cap < kOneNbMax) return 1u;
+  if (cells <= a.ccap && a.nb_cap < kOneNbMax) return 1u;  // (A <= cells)
   const uint32_t cls = (uint32_t)((A + 15) >> 4);
   return cls <= (uint32_t)kNarrow ? (uint32_t)(kNarrow + 1) : cls;
 }
@@ -802,18 +802,25 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
   row_window(a, u, &nu, &lo, &hi, false);
   if (blockIdx.x == 0) {  // the unit's call state and its cell plan for the filter, while the words load
     unit_reset(a, u, t, lo, hi);
-    __shared__ CellPlan P;
     CellPre pre;
     pre.t = t;
 #pragma unroll
     for (int h = 0; h < 4; ++h) pre.q[h] = qv[h];
-    cell_plan(P, a, pre);
+    // the plan is built where the samples' words go later (the barrier before
+    // those are written comes after the plan is stored)
+    static_assert(sizeof(CellPlanWide) <= offsetof(SampleLds, sc), "the plan ends before S.cnt");
+    auto build = [&](auto& plan) {
+      cell_plan(plan, a, pre);
 #pragma unroll
-    for (int i = 0; i < kPlanSteps; ++i) {
-      const int w = tid + kFT * i;
-      if (w < kPlanWords)
-        gstore(reinterpret_cast<PlanWord*>(a.ws.plan + (size_t)u * kPlanBytes) + w, reinterpret_cast<const PlanWord*>(&P)[w]);
-    }
+      for (int i = 0; i < kPlanSteps; ++i) {
+        const int w = tid + kFT * i;
+        if (w < (int)(sizeof(plan) / 16))
+          gstore(reinterpret_cast<PlanWord*>(a.ws.plan + (size_t)u * kPlanBytes) + w,
+                 reinterpret_cast<const PlanWord*>(&plan)[w]);
+      }
+    };
+    if (a.ccap > kCC) build(reinterpret_cast<CellPlanWide&>(S));
+    else build(reinterpret_cast<CellPlan&>(S));
   }
   if (hi - lo <= a.ws.cap) return;  // computed directly by the exact pass
   // the active channels in ascending order
@@ -1853,14 +1860,14 @@ fathom_status launch_scan_topk_fused(const uint64_t* planes, const uint16_t* sca
   fa.k = k;
   fa.ws = fused_carve(ws, U * G, U, nb_cap, k);
   fa.st = st;
-  fa.ccap = max_unit_bits > 64 && max_unit_bits <= 80 ? 80 : 64;
+  fa.ccap = max_unit_bits > 64 && max_unit_bits <= kCC ? kCC : max_unit_bits > kCC && max_unit_bits <= kCCWide ? kCCWide : 64;
   const int R = U * G;
   const bool f16 = qdt == FATHOM_F16;
-  // a unit with at most 80 depth bits has at most 80 cells and channels:
+  // a unit with at most 128 depth bits has at most 128 cells and channels:
   // with such a bound the cell filter takes every unit, and the wide
   // launches are skipped.  (A unit above the caller's bound is left to the
   // exact rows of the select pass.)
-  const bool wide = !(max_unit_bits > 0 && max_unit_bits <= kCC && nb_cap < kOneNbMax);
+  const bool wide = !(max_unit_bits > 0 && max_unit_bits <= kCCWide && nb_cap < kOneNbMax);
   if (G <= 4)
     hipLaunchKernelGGL(fused_sample_kernel, dim3((unsigned)fa.ws.s_quads, (unsigned)U), dim3(kFT), 0, s, fa);
   // narrow: the cell filter finds tau itself and the sample pass sets the

@@ -148,7 +148,7 @@ struct FusedArgs {
   int k;
   FusedWs ws;
   uint32_t* st;
-  int ccap;  // cells at most of a unit the cell filter takes (64, or 80 when the call's units have 65 to 80 bits)
+  int ccap;  // cells at most of a unit the cell filter takes (64; 80 or 128 when the caller bounds its units at 65 to 80 or 81 to 128 bits)
 };
 
 __device__ __forceinline__ uint64_t lanemask_lt(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }

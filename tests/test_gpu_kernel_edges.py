@@ -256,3 +256,57 @@ def test_alloc_depths_extremes(G):
         for u in range(U):
             od = oracle.alloc_topr(q[u], r)[0]
             assert np.array_equal(d[u].cpu().numpy(), od), (r, u)
+
+
+def depth_row(rng, spec):
+    """Depths with spec = {depth: channel count} on channels drawn at random."""
+    d = np.zeros(D, np.uint8)
+    ch = rng.permutation(D)
+    at = 0
+    for t, c in spec.items():
+        d[ch[at:at + c]] = t
+        at += c
+    return d
+
+
+@pytest.mark.parametrize("G,qdt", [(4, np.float16), (3, np.float32), (1, np.float32)])
+def test_scan_topk_81_to_128_cells(G, qdt):
+    """Units of 81 to 128 depth bits in the cell filter at eight slices (the
+    caller bounds the bits by 128): 32 channels at 4 planes, 128 one-plane
+    channels (every channel of the unit), 81 cells (a ragged last row group), 100
+    channels of mixed depth, water-filling at 96 bits, and units of few cells
+    beside them; odd block strides, a window with lo and tail, k = 1 and 300.  The
+    filter serves them (no fallback flag at k = 300); without a bound the same
+    units take the wide pass.  Both bit-exact to the oracle."""
+    ns = [70000, 23456, 40001, 30000, 50000, 64, 20000, 30001]
+    rng = np.random.default_rng(300 + G)
+    U, cap = len(ns), max(ns)
+    K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
+    n = dev(np.array(ns, np.int64))
+    q = rng.standard_normal((U, G, D)).astype(qdt)
+    var = np.exp(2 * rng.standard_normal((U, D))).astype(np.float32)
+    dn = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, 96)[0].cpu().numpy()
+    specs = {0: {4: 32}, 1: {1: 128}, 2: {4: 17, 1: 13}, 3: {1: 72, 2: 28}, 4: {4: 31, 3: 1, 1: 1}, 5: {4: 32},
+             7: {2: 3}}
+    for u, spec in specs.items():
+        dn[u] = depth_row(rng, spec)
+    assert [int(dn[u].sum()) for u in specs] == [128, 128, 81, 128, 128, 128, 6]
+    assert dn[6].sum() <= 96
+    for nb_cap in (1094, 1101):
+        planes, scales = F.fathom_pack(K, n, nb_cap=nb_cap)
+        P, S = planes.cpu().numpy().view(np.uint64), scales.cpu().numpy().view(np.uint16)
+        ref = [oracle.scores_f32(P[u], S[u], ns[u], q[u].astype(np.float32), dn[u]) for u in range(U)]
+        for k, lo, tail in [(300, 0, 0), (300, 4, 32), (1, 0, 0)]:
+            want = [[oracle.topk(ref[u][h], k, lo, tail) for h in range(G)] for u in range(U)]
+            for bound in (128, 0):
+                st = F.new_status()
+                idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), dev(dn), k, lo, tail, dev_status=st,
+                                              max_unit_bits=bound)
+                s = status(st)
+                assert s & ~(F.FATHOM_DEV_TOPK_SHORT | F.FATHOM_DEV_TOPK_FALLBACK) == 0, (bound, hex(s))
+                assert k == 1 or not s & F.FATHOM_DEV_TOPK_FALLBACK, (bound, lo)
+                for u in range(U):
+                    for h in range(G):
+                        oi, ov, _ = want[u][h]
+                        assert np.array_equal(idx[u, h].cpu().numpy(), oi), (bound, k, u, h)
+                        assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (bound, k, u, h)
