@@ -22,6 +22,8 @@ constexpr int kWaveRows = 32;                         // row-list positions per 
 constexpr int kRowSteps = kWaveRows / 4;              // 4 rows per load instruction
 constexpr int kMaxSinkLocal = 1024;
 constexpr int kPart = kD + 2;  // per chunk: m, d, o[D]
+constexpr int kCombThreads = 512;
+constexpr int kCombGroups = kCombThreads / kD;
 
 static inline int attn_chunks(int k, int n_sink, int n_local) {
   return (n_sink + n_local + k + kWaveRows - 1) / kWaveRows;
@@ -49,27 +51,34 @@ __device__ __forceinline__ uint4 load8h(const uint16_t* p) {
   return make_uint4(gload_u32(p), gload_u32(p + 2), gload_u32(p + 4), gload_u32(p + 6));
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const void* __restrict__ q, fathom_dtype qdt,
-                                                                  const uint16_t* __restrict__ Krows,
-                                                                  const uint16_t* __restrict__ Vrows, int64_t ld_tok,
-                                                                  int64_t ld_unit, const int64_t* __restrict__ n,
-                                                                  int G, const int32_t* __restrict__ idx, int k,
-                                                                  int n_sink, int n_local, float sm_scale, int S,
-                                                                  float* __restrict__ ws, uint32_t* __restrict__ st) {
-  const int r = blockIdx.y, u = r / G, h = r % G;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = blockIdx.x * kAttnWaves + wave;  // this wave's chunk
-  if (c >= S) return;
-  int64_t nu = *(const __attribute__((address_space(1))) int64_t*)(n + u);
+// What a wave needs of a call: head h of unit u, its row r = u G + h.
+struct AttnArgs {
+  const void* q;
+  fathom_dtype qdt;
+  const uint16_t *Krows, *Vrows;
+  int64_t ld_tok, ld_unit;
+  const int64_t* n;
+  int G;
+  const int32_t* idx;
+  int k, n_sink, n_local;
+  float sm_scale;
+  uint32_t* st;
+};
+
+// One chunk of row r by one wave: put(0, m), put(1, d) and put(2 + c, o_c).
+template <bool VEC, class Put>
+__device__ __forceinline__ void attn_chunk(const AttnArgs& a, int r, int c, Put put) {
+  const int u = r / a.G, h = r % a.G, lane = threadIdx.x & 63;
+  const int n_sink = a.n_sink, n_local = a.n_local, k = a.k, G = a.G;
+  const int64_t ld_tok = a.ld_tok;
+  int64_t nu = *(const __attribute__((address_space(1))) int64_t*)(a.n + u);
   if (nu < 0) {
-    if (lane == 0 && c == 0) set_status(st, FATHOM_DEV_BAD_N);
+    if (lane == 0 && c == 0) set_status(a.st, FATHOM_DEV_BAD_N);
     nu = 0;
   }
   const int64_t ns = n_sink < nu ? n_sink : nu;
   const int64_t l0 = nu - n_local > ns ? nu - n_local : ns;
   const int64_t nloc = nu - l0;
-  float* wp = ws + ((int64_t)r * S + c) * kPart;
   // ---- the row of each of the wave's positions (lane x < 32: position x) ----
   int32_t myrow = -1;
   if (lane < kWaveRows) {
@@ -79,15 +88,15 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const void* __
     } else if (p < ns + nloc) {
       myrow = (int32_t)(l0 + (p - ns));
     } else if (p - ns - nloc < k) {
-      const int32_t v = *(const __attribute__((address_space(1))) int32_t*)(idx + (int64_t)r * k + (p - ns - nloc));
+      const int32_t v = *(const __attribute__((address_space(1))) int32_t*)(a.idx + (int64_t)r * k + (p - ns - nloc));
       if (v >= ns && v < l0) myrow = v;
     }
   }
   // ---- K and V of the rows: lane group g = lane / 16 takes position 4 s + g,
   // lane x = lane mod 16 channels 8x .. 8x + 7 ----
   const int g = lane >> 4, x = lane & 15;
-  const uint16_t* Ku = Krows + (int64_t)u * ld_unit + 8 * x;
-  const uint16_t* Vu = Vrows + (int64_t)u * ld_unit + 8 * x;
+  const uint16_t* Ku = a.Krows + (int64_t)u * a.ld_unit + 8 * x;
+  const uint16_t* Vu = a.Vrows + (int64_t)u * a.ld_unit + 8 * x;
   int32_t row[kRowSteps];
   uint4 kv[kRowSteps], vv[kRowSteps];
 #pragma unroll
@@ -104,7 +113,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const void* __
   {
     const int64_t qo = ((int64_t)u * G + h) * kD + 8 * x;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) qv[e] = load_q(q, qdt, qo + e);
+    for (int e = 0; e < 8; ++e) qv[e] = load_q(a.q, a.qdt, qo + e);
   }
   // ---- logits ----
   float z[kRowSteps];
@@ -120,15 +129,15 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const void* __
     }
 #pragma unroll
     for (int m = 1; m < 16; m <<= 1) d = __fadd_rn(d, __shfl_xor(d, m, kWave));
-    z[s] = row[s] >= 0 ? __fmul_rn(d, sm_scale) : -__builtin_huge_valf();
+    z[s] = row[s] >= 0 ? __fmul_rn(d, a.sm_scale) : -__builtin_huge_valf();
     zm = fmaxf(zm, z[s]);
   }
   zm = fmaxf(zm, __shfl_xor(zm, 16, kWave));
   zm = fmaxf(zm, __shfl_xor(zm, 32, kWave));
   if (zm == -__builtin_huge_valf()) {  // no row in this chunk
     if (lane == 0) {
-      gstore_f(wp, zm);
-      gstore_f(wp + 1, 0.0f);
+      put(0, zm);
+      put(1, 0.0f);
     }
     return;
   }
@@ -157,11 +166,61 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const void* __
   }
   if (lane < 16) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) gstore_f(wp + 2 + 8 * x + e, o[e]);
+    for (int e = 0; e < 8; ++e) put(2 + 8 * x + e, o[e]);
   }
   if (lane == 0) {
-    gstore_f(wp, zm);
-    gstore_f(wp + 1, den);
+    put(0, zm);
+    put(1, den);
+  }
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(AttnArgs a, int S, float* __restrict__ ws) {
+  const int r = blockIdx.y, c = blockIdx.x * kAttnWaves + (threadIdx.x >> 6);  // this wave's chunk
+  if (c >= S) return;
+  float* wp = ws + ((int64_t)r * S + c) * kPart;
+  attn_chunk<VEC>(a, r, c, [&](int i, float v) { gstore_f(wp + i, v); });
+}
+
+// Rows of at most kRowChunks chunks (one wave each): one workgroup takes the
+// whole row and combines its chunks' partials in LDS, in the order of the
+// combine kernel (the same bits), so there is no second launch and no workspace
+// traffic.  One KV head at k = 64: 5.1 us of kernel time against 6.5 in two
+// launches; 32 rows at k = 500 (16 chunks) the same time in one launch as in
+// two; at 32 chunks, two a wave, a row's CU is the bound: 17.7 us against 11.0.
+constexpr int kRowChunks = 16;
+constexpr int kRowThreads = 1024;
+template <bool VEC>
+__global__ __launch_bounds__(kRowThreads) void attn_row_kernel(AttnArgs a, int S, float* __restrict__ out) {
+  __shared__ float part[kRowChunks][kPart];
+  __shared__ float em[kRowChunks], po[kCombGroups][kD];
+  const int r = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  for (int c = tid >> 6; c < S; c += nt >> 6)
+    attn_chunk<VEC>(a, r, c, [&](int i, float v) { part[c][i] = v; });
+  __syncthreads();
+  float M = -__builtin_huge_valf();
+  for (int c = 0; c < S; ++c) M = fmaxf(M, part[c][0]);
+  if (M == -__builtin_huge_valf()) {  // no row at all
+    if (tid < kD) gstore_f(out + (int64_t)r * kD + tid, 0.0f);
+    return;
+  }
+  if (tid < S) em[tid] = part[tid][0] == -__builtin_huge_valf() ? 0.0f : expf(__fsub_rn(part[tid][0], M));
+  __syncthreads();
+  for (int x = tid; x < kCombGroups * kD; x += nt) {
+    const int gi = x / kD, ch = x % kD;
+    float o = 0.0f;
+    for (int c = gi; c < S; c += kCombGroups)
+      if (em[c] != 0.0f) o = __fmaf_rn(em[c], part[c][2 + ch], o);  // empty chunks wrote no o
+    po[gi][ch] = o;
+  }
+  __syncthreads();
+  if (tid < kD) {
+    float den = 0.0f;
+    for (int c = 0; c < S; ++c) den = __fmaf_rn(em[c], part[c][1], den);
+    float acc = 0.0f;
+#pragma unroll
+    for (int g = 0; g < kCombGroups; ++g) acc = __fadd_rn(acc, po[g][tid]);
+    gstore_f(out + (int64_t)r * kD + tid, acc / den);
   }
 }
 
@@ -169,8 +228,6 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(const void* __
 // One 512-thread workgroup per head: the chunk maxima and sums go to LDS, then
 // four groups of 128 threads (one channel each) take every fourth chunk, with
 // kCombBatch chunks' loads in flight at a time.
-constexpr int kCombThreads = 512;
-constexpr int kCombGroups = kCombThreads / kD;
 constexpr int kCombBatch = 16;
 constexpr int kMaxChunks = (kMaxSinkLocal + FATHOM_MAX_K + kWaveRows - 1) / kWaveRows;
 __global__ __launch_bounds__(kCombThreads) void attn_combine_kernel(const float* __restrict__ ws, int S,
@@ -235,17 +292,23 @@ fathom_status launch_sparse_attn(const void* q, fathom_dtype qdt, const uint16_t
   if (U == 0) return FATHOM_OK;
   int S = attn_chunks(k, n_sink, n_local);
   if (S < 1) S = 1;
-  float* w = reinterpret_cast<float*>(ws);
-  const dim3 grid((unsigned)((S + kAttnWaves - 1) / kAttnWaves), (unsigned)(U * G));
+  const AttnArgs a = {q, qdt, Krows, Vrows, ld_tok, ld_unit, n, G, idx, k, n_sink, n_local, sm_scale, st};
   // 16-byte row loads when every row start is 16-byte aligned
   const bool vec = ((reinterpret_cast<uintptr_t>(Krows) | reinterpret_cast<uintptr_t>(Vrows)) & 15) == 0 &&
                    (ld_tok & 7) == 0 && (ld_unit & 7) == 0;
-  if (vec)
-    hipLaunchKernelGGL(attn_chunk_kernel<true>, grid, dim3(kAttnThreads), 0, s, q, qdt, Krows, Vrows, ld_tok,
-                       ld_unit, n, G, idx, k, n_sink, n_local, sm_scale, S, w, st);
-  else
-    hipLaunchKernelGGL(attn_chunk_kernel<false>, grid, dim3(kAttnThreads), 0, s, q, qdt, Krows, Vrows, ld_tok,
-                       ld_unit, n, G, idx, k, n_sink, n_local, sm_scale, S, w, st);
+  // (with more rows than CUs a 16-wave workgroup per row gains nothing: 512 rows
+  // of 16 chunks take 29.2 us against 28.1)
+  if (S <= kRowChunks / 2 || (S <= kRowChunks && U * G <= 256)) {
+    const dim3 threads(S <= 4 ? 256 : S <= 8 ? 512 : kRowThreads);
+    if (vec) hipLaunchKernelGGL(attn_row_kernel<true>, dim3((unsigned)(U * G)), threads, 0, s, a, S, out);
+    else hipLaunchKernelGGL(attn_row_kernel<false>, dim3((unsigned)(U * G)), threads, 0, s, a, S, out);
+    FATHOM_LAUNCH_CHECK();
+    return FATHOM_OK;
+  }
+  float* w = reinterpret_cast<float*>(ws);
+  const dim3 grid((unsigned)((S + kAttnWaves - 1) / kAttnWaves), (unsigned)(U * G));
+  if (vec) hipLaunchKernelGGL(attn_chunk_kernel<true>, grid, dim3(kAttnThreads), 0, s, a, S, w);
+  else hipLaunchKernelGGL(attn_chunk_kernel<false>, grid, dim3(kAttnThreads), 0, s, a, S, w);
   hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)(U * G)), dim3(kCombThreads), 0, s, w, S, out);
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;

@@ -310,3 +310,30 @@ def test_scan_topk_81_to_128_cells(G, qdt):
                         oi, ov, _ = want[u][h]
                         assert np.array_equal(idx[u, h].cpu().numpy(), oi), (bound, k, u, h)
                         assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (bound, k, u, h)
+
+
+@pytest.mark.parametrize("k", [0, 1, 92, 128, 220, 257, 476, 512, 513])
+@pytest.mark.parametrize("U", [3, 70])
+def test_sparse_attn_row_lists(k, U):
+    """Row lists of 1 to 17 chunks on both sides of the one-workgroup rule (at most
+    8 chunks, or 16 with at most 256 rows), with sink and local rows, skipped
+    entries, a short unit, an empty unit and empty chunks.  Bound: the oracle's,
+    1e-5 of the softmax-weighted mean of |V|, at most 1e-5 max |V|."""
+    rng = np.random.default_rng(k + U)
+    G, cap = 4, 700
+    ns = rng.integers(1, cap + 1, U)
+    ns[:3] = [cap, 40, 0]
+    K = rng.standard_normal((U, cap, D)).astype(np.float16)
+    V = rng.standard_normal((U, cap, D)).astype(np.float16)
+    q = rng.standard_normal((U, G, D)).astype(np.float32)
+    for sink, local in [(0, 0), (4, 32)]:
+        idx = np.full((U, G, k), -1, np.int32)
+        for u in range(U):
+            for h in range(G):
+                m = min(k, int(ns[u]))
+                idx[u, h, rng.permutation(k)[:m]] = rng.permutation(int(ns[u]))[:m]
+        idx[0, 0, : min(k, 64)] = -1  # a head whose first chunks are empty
+        out = F.fathom_sparse_attn(dev(q), dev(K), dev(V), dev(ns.astype(np.int64)), dev(idx), sink, local).cpu().numpy()
+        for u in [0, 1, 2, U - 1]:
+            ref = oracle.sparse_attn(q[u], K[u, :ns[u]], V[u, :ns[u]], idx[u], sink, local, 1 / np.sqrt(D))
+            assert np.abs(out[u] - ref).max() <= 1e-5 * np.abs(V[u].astype(np.float32)).max(), (u, sink)
