@@ -765,6 +765,7 @@ __device__ __forceinline__ void unit_reset(const FusedArgs& a, int u, int t, int
 // call state (unit_reset) and builds the unit's cell plan for the filter in
 // the workspace while its plane words load.
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u8 __attribute__((ext_vector_type(4), aligned(8)));  // two plane words: rows are 8-byte aligned
 struct alignas(16) SampleLds {
   uint32_t act[kD];                  // ascending position -> channel | depth << 8 (0 on padding)
   float q[kD][4];                    // q by ascending position and head (0 past G and on padding)
@@ -788,15 +789,36 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
   }
   // this channel's words and scales for the workgroup's blocks (0 past the store)
   const int64_t blk0 = (int64_t)blockIdx.x * a.ws.s_stride * kQB;
-  uint64_t wd[kQB][kPlanes];
-  uint16_t scv[kQB];
+  uint64_t wd[kQB][kPlanes] = {};
+  uint16_t scv[kQB] = {};
+  if (tid < kD && t > 0) {
+    const uint64_t* wp = a.planes + ((int64_t)u * kD + tid) * kPlanes * a.nb_cap + blk0;
+    const uint16_t* sp = a.scales + ((int64_t)u * kD + tid) * a.nb_cap + blk0;
+    if (blk0 + kQB <= a.nb_cap) {  // a plane's four words as two 16-byte loads
 #pragma unroll
-  for (int b = 0; b < kQB; ++b) {
-    const bool inb = tid < kD && t > 0 && blk0 + b < a.nb_cap;
-    scv[b] = inb ? gload(a.scales + ((int64_t)u * kD + tid) * a.nb_cap + blk0 + b) : (uint16_t)0;
+      for (int p = 0; p < kPlanes; ++p) {
+        if (p < t) {
+          const auto* w2 = reinterpret_cast<const __attribute__((address_space(1))) v4u8*>(
+              (const __attribute__((address_space(1))) uint64_t*)(wp + (int64_t)p * a.nb_cap));
+          const v4u8 x = w2[0], y = w2[1];
+          wd[0][p] = ((uint64_t)x.y << 32) | x.x;
+          wd[1][p] = ((uint64_t)x.w << 32) | x.z;
+          wd[2][p] = ((uint64_t)y.y << 32) | y.x;
+          wd[3][p] = ((uint64_t)y.w << 32) | y.z;
+        }
+      }
 #pragma unroll
-    for (int p = 0; p < kPlanes; ++p)
-      wd[b][p] = inb && p < t ? gload(a.planes + (((int64_t)u * kD + tid) * kPlanes + p) * a.nb_cap + blk0 + b) : 0ull;
+      for (int b = 0; b < kQB; ++b) scv[b] = gload(sp + b);
+    } else {
+#pragma unroll
+      for (int b = 0; b < kQB; ++b) {
+        if (blk0 + b >= a.nb_cap) continue;
+        scv[b] = gload(sp + b);
+#pragma unroll
+        for (int p = 0; p < kPlanes; ++p)
+          if (p < t) wd[b][p] = gload(wp + (int64_t)p * a.nb_cap + b);
+      }
+    }
   }
   int64_t nu, lo, hi;
   row_window(a, u, &nu, &lo, &hi, false);
@@ -1101,13 +1123,20 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 // its own parts instead; every part reaches the same decision from the same
 // histogram.  The parts of a row run on one XCD (workgroups are dealt to the
 // 8 XCDs in turn), so the list is read once into that XCD's L2.
+// Every part reads the whole list and builds the whole histogram, so with more
+// rows than one round of the chip holds at 8 parts (3 workgroups a CU) a row has
+// one part up to k = 1024 and two up to k = 2048, where a part's share (k over
+// the parts and what survived past k, about k / 4) stays well inside kRankCap.
+// 512 rows at k = 1024: 39.5 us with 8 parts, 21.5 with 4, 14.2 with 2, 10.0
+// with one.
 constexpr int kRankParts = 8;
+constexpr int kRankRound = 3 * 256;
 constexpr int kRankThreads = 512;   // the rank pass's workgroup (the select pass's is kXThreads)
 constexpr int kRankPer = 8;      // survivors per thread read with the count (the rest re-read)
 constexpr int kRankCap = 4096;   // survivors one part orders at most
 constexpr int kRankSub = 4096;   // sub-buckets at most
 constexpr int kRankXcd = 8;
-template <int T>
+template <int T, int kRankParts>
 struct RankShared {
   uint32_t s_red[2][T / kWave], s_part[T / kWave];
   uint32_t s_first[kRankParts + 1];  // part z: sub-buckets [s_first[z], s_first[z + 1])
@@ -1120,9 +1149,9 @@ struct RankShared {
 // and kRankSub + 1 counts, 16-byte aligned.  Returns true when a part's share
 // exceeds kRankCap after all (many equal scores): the row is then computed
 // exactly.
-template <int T>
+template <int T, int kRankParts>
 __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict__ idx, float* __restrict__ val,
-                          uint64_t* grp, uint32_t* hist, RankShared<T>& RS) {
+                          uint64_t* grp, uint32_t* hist, RankShared<T, kRankParts>& RS) {
   constexpr int kRankThreads = T;  // threads of the calling workgroup
   auto& s_red = RS.s_red;
   auto& s_part = RS.s_part;
@@ -1710,18 +1739,19 @@ __device__ __forceinline__ bool row_exact(const FusedArgs& a, int r) {
 // whose share is too large marks the row for the exact rows of the select
 // pass that follows (tau = -inf, which every part of the row writes alike,
 // before any of them writes a position).
+template <int kRankParts>
 __global__ __launch_bounds__(kRankThreads) void fused_rank_kernel(FusedArgs a, int R, int32_t* __restrict__ idx,
                                                                  float* __restrict__ val) {
   __shared__ uint64_t grp[kRankCap];
   __shared__ __align__(16) uint32_t hist[kRankSub + 4];
-  __shared__ RankShared<kRankThreads> RS;
+  __shared__ RankShared<kRankThreads, kRankParts> RS;
   __shared__ int s_ex;
   const int b = (int)blockIdx.x, j = b / kRankXcd, z = j % kRankParts, r = (j / kRankParts) * kRankXcd + b % kRankXcd;
   if (r >= R) return;
   if (threadIdx.x == 0) s_ex = row_exact(a, r) ? 1 : 0;
   __syncthreads();
   if (s_ex) return;
-  if (rank_part<kRankThreads>(a, r, z, idx, val, grp, hist, RS) && threadIdx.x == 0) gstore(a.ws.tau + r, kNegInf);
+  if (rank_part<kRankThreads, kRankParts>(a, r, z, idx, val, grp, hist, RS) && threadIdx.x == 0) gstore(a.ws.tau + r, kNegInf);
 }
 
 // The select pass: ranks and exact rows in one launch when the rank parts fit
@@ -1738,7 +1768,7 @@ __global__ __launch_bounds__(kXThreads) void fused_select_kernel(FusedArgs a, in
                                                                  int32_t* __restrict__ idx, float* __restrict__ val) {
   extern __shared__ __align__(16) unsigned char xl[];
   __shared__ XShared S;
-  __shared__ RankShared<kXThreads> RS;
+  __shared__ RankShared<kXThreads, kRankParts> RS;
   __shared__ uint32_t cflg[kXThreads / 32];  // bit i: row r0 + i is computed exactly
   __shared__ int s_ex;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = (int)blockIdx.x;
@@ -1761,7 +1791,7 @@ __global__ __launch_bounds__(kXThreads) void fused_select_kernel(FusedArgs a, in
       __syncthreads();
       const bool ex = r < kXThreads ? ((cflg[r >> 5] >> (r & 31)) & 1u) != 0u : s_ex != 0;
       if (!ex) {
-        const bool over = rank_part<kXThreads>(a, r, z, idx, val, reinterpret_cast<uint64_t*>(xl),
+        const bool over = rank_part<kXThreads, kRankParts>(a, r, z, idx, val, reinterpret_cast<uint64_t*>(xl),
                                     reinterpret_cast<uint32_t*>(xl + (size_t)kRankCap * 8), RS);
         __syncthreads();
         if (over)
@@ -1887,7 +1917,13 @@ fathom_status launch_scan_topk_fused(const uint64_t* planes, const uint16_t* sca
     hipLaunchKernelGGL(fused_select_kernel, dim3(rank_wg > xg ? rank_wg : xg), dim3(kXThreads), kXLdsBytes, s, fa, R,
                        (int)rank_wg, idx, val);
   } else {
-    hipLaunchKernelGGL(fused_rank_kernel, dim3(rank_wg), dim3(kRankThreads), 0, s, fa, R, idx, val);
+    const unsigned rows8 = (unsigned)((R + kRankXcd - 1) / kRankXcd) * kRankXcd;
+    if (rows8 * kRankParts > kRankRound && k <= 1024)
+      hipLaunchKernelGGL(fused_rank_kernel<1>, dim3(rows8), dim3(kRankThreads), 0, s, fa, R, idx, val);
+    else if (rows8 * kRankParts > kRankRound && k <= 2048)
+      hipLaunchKernelGGL(fused_rank_kernel<2>, dim3(rows8 * 2), dim3(kRankThreads), 0, s, fa, R, idx, val);
+    else
+      hipLaunchKernelGGL(fused_rank_kernel<kRankParts>, dim3(rank_wg), dim3(kRankThreads), 0, s, fa, R, idx, val);
     hipLaunchKernelGGL(fused_select_kernel, dim3(xg), dim3(kXThreads), kXLdsBytes, s, fa, R, 0, idx, val);
   }
   FATHOM_LAUNCH_CHECK();

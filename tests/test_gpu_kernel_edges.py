@@ -337,3 +337,33 @@ def test_sparse_attn_row_lists(k, U):
         for u in [0, 1, 2, U - 1]:
             ref = oracle.sparse_attn(q[u], K[u, :ns[u]], V[u, :ns[u]], idx[u], sink, local, 1 / np.sqrt(D))
             assert np.abs(out[u] - ref).max() <= 1e-5 * np.abs(V[u].astype(np.float32)).max(), (u, sink)
+
+
+@pytest.mark.parametrize("k", [1, 1000, 1024, 1025, 2048, 2049])
+def test_scan_topk_many_rows(k):
+    """112 rows: more than one round of the chip at 8 rank parts a row, so 1, 2 or 8
+    parts by k; a unit with many equal scores (keys drawn from four blocks), one
+    whose ends are inside a sampled quad (odd stride), and windows.  Bit-exact to
+    the oracle."""
+    rng = np.random.default_rng(k)
+    U, G, cap = 28, 4, 24003
+    ns = rng.integers(16000, cap + 1, U)
+    ns[0] = cap
+    K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
+    K[1] = K[1, :256].repeat(94, 1)[:cap]
+    n = dev(ns.astype(np.int64))
+    planes, scales = F.fathom_pack(K, n)
+    q = rng.standard_normal((U, G, D)).astype(np.float16)
+    var = np.exp(2 * rng.standard_normal((U, D))).astype(np.float32)
+    d, _ = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, 48)
+    for lo, tail in [(0, 0), (4, 32)]:
+        st = F.new_status()
+        idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, lo, tail, dev_status=st, max_unit_bits=48)
+        assert status(st) & ~F.FATHOM_DEV_TOPK_FALLBACK == 0
+        for u in [0, 1, 2, 13, U - 1]:
+            ref = oracle.scores_f32(planes[u].cpu().numpy().view(np.uint64), scales[u].cpu().numpy().view(np.uint16),
+                                    int(ns[u]), q[u].astype(np.float32), d[u].cpu().numpy())
+            for h in range(G):
+                oi, ov, _ = oracle.topk(ref[h], k, lo, tail)
+                assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h, lo)
+                assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h, lo)
