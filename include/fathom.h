@@ -203,9 +203,10 @@ size_t fathom_topk_workspace_size(int U, int G, int64_t max_n, int k);
  *   ws       device workspace of at least
  *            fathom_scan_topk_workspace_size(U, G, max_n, k) bytes (any
  *            contents: every call sets the state it reads).
- * The filter that spares most keys their exact score serves units of at most
- * 4 query heads per KV head; with G > 4 every row takes the exact path (the
- * same outputs; TOPK_FALLBACK is raised).
+ * The filter that spares most keys their exact score takes 4 query heads of a
+ * unit at a time.  With G > 4 TOPK_FALLBACK is raised, and without a bound on
+ * the depth bits (fathom_scan_topk_ex) every row takes the exact path (the
+ * same outputs).
  * Device status: NONFINITE, TOPK_SHORT, TOPK_FALLBACK, BAD_N.
  */
 fathom_status fathom_scan_topk(const uint64_t* planes, const uint16_t* scales, const int64_t* n,

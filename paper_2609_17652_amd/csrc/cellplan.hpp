@@ -64,7 +64,7 @@ __device__ __forceinline__ CellPre cell_load(const FusedArgs& a, int u) {
     r.t = gload(a.depths + (int64_t)u * kD + tid);
 #pragma unroll
     for (int h = 0; h < 4; ++h)
-      if (h < G) r.q[h] = load_q(a.q, a.qdt, ((int64_t)u * G + h) * kD + tid);
+      if (h < G) r.q[h] = load_q(a.q, a.qdt, ((int64_t)u * a.GR + h) * kD + tid);
   }
   if (r.t > kPlanes) r.t = kPlanes;
   return r;

@@ -404,7 +404,7 @@ __device__ __forceinline__ void cquad_weights(const FPlan<NS>& P, FilterLds<NS>&
 // Appends survivors to the rows' lists: the nb[h] buffered ones of head h and
 // this lane's new one of head h when bit h of `keep` is set (composite
 // comp[h], rank[h] among the wave's new ones, c[h] of them).  One atomic
-// instruction reserves every head's range (lane h for row u G + h), so a
+// instruction reserves every head's range (lane h for row u GR + h), so a
 // flush costs one round trip whatever the number of heads.
 template <int NS>
 __device__ __forceinline__ void cappend(FilterLds<NS>& L, const FusedArgs& a, int u, const int (&nb)[4], const int (&c)[4],
@@ -412,13 +412,13 @@ __device__ __forceinline__ void cappend(FilterLds<NS>& L, const FusedArgs& a, in
   const int lane = threadIdx.x & 63, G = a.G;
   const int tot = lane == 0 ? nb[0] + c[0] : lane == 1 ? nb[1] + c[1] : lane == 2 ? nb[2] + c[2] : nb[3] + c[3];
   uint32_t base = 0u;
-  if (lane < G && tot > 0) base = gatomic_add(&a.ws.cnt[(u * G + lane) * kCntStride], (uint32_t)tot);
+  if (lane < G && tot > 0) base = gatomic_add(&a.ws.cnt[(u * a.GR + lane) * kCntStride], (uint32_t)tot);
   const uint32_t lcap = (uint32_t)a.ws.lcap;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
     if (nb[h] + c[h] == 0) continue;  // every head past G
     const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)base, h);
-    uint64_t* row = a.ws.cand + (int64_t)(u * G + h) * a.ws.lcap;
+    uint64_t* row = a.ws.cand + (int64_t)(u * a.GR + h) * a.ws.lcap;
     if (lane < nb[h] && b + (uint32_t)lane < lcap) gstore(&row[b + (uint32_t)lane], L.sv[h][lane]);
     const uint32_t pos = b + (uint32_t)nb[h] + (uint32_t)rank[h];
     if (((keep >> h) & 1u) && pos < lcap) gstore(&row[pos], comp[h]);
@@ -902,7 +902,7 @@ __global__ __launch_bounds__(kCThreads, CGeo<NS>::PerCU) void fused_filter_kerne
 #pragma unroll
   for (int i0 = 0; i0 < kCTauPer; ++i0) {
     const int i = lane + kWave * i0;
-    sv[i0] = i < nsm ? gload(a.ws.samp + (int64_t)(u * G + wave) * kSmpRow + i) : kNegInf;
+    sv[i0] = i < nsm ? gload(a.ws.samp + (int64_t)(u * a.GR + wave) * kSmpRow + i) : kNegInf;
   }
   // the unit's plan (built by the sample pass), up to two 16-byte words per thread
   static_assert(kCThreads == kFT, "the plan's copy steps");
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(kCThreads, CGeo<NS>::PerCU) void fused_filter_kerne
     if (wave < G) {
       if (lane == 0) {
         P.tau[wave] = tv;
-        if (x == 0) gstore(a.ws.tau + u * G + wave, tv);
+        if (x == 0) gstore(a.ws.tau + u * a.GR + wave, tv);
       }
     }
     __syncthreads();

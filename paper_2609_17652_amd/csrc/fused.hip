@@ -43,7 +43,7 @@
 //
 // Passes (launches): (1) sample: exact scores of every s-th quad, the 2
 // largest per (block, head), and per unit the rows' call state and the cell
-// plan; (2) tau, only for the wide pass or G > 4: per row the m-th largest
+// plan; (2) tau, only for the wide pass: per row the m-th largest
 // sample, m ~ 1.25 k sampled / eligible + 16 (the cell filter finds the same
 // tau itself); (3) the full pass: the cell filter, and the wide pass above
 // when launched; (4) select: 8 workgroups per row share out its top k
@@ -54,6 +54,7 @@
 // FATHOM_DEV_TOPK_FALLBACK), are computed from exact scores by a chunked
 // selection in the same launch.  The result never depends on tau; it only
 // decides how much work is saved.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 #include <mutex>
@@ -735,7 +736,7 @@ __device__ __forceinline__ void unit_reset(const FusedArgs& a, int u, int t, int
     for (int v = 1; v <= kPlanes; ++v) sc2[wave][v] = __popcll(bal[v]);
   }
   if (tid < G) {
-    const int r = u * G + tid;
+    const int r = u * a.GR + tid;
     gstore(a.ws.cnt + r * kCntStride, 0u);
     gstore(a.ws.xctl + 1 + r, 0u);
     gstore(a.ws.tau + r, kNegInf);
@@ -785,7 +786,7 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
     if (t > kPlanes) t = kPlanes;
 #pragma unroll
     for (int h = 0; h < 4; ++h)
-      if (h < G) qv[h] = load_q(a.q, a.qdt, ((int64_t)u * G + h) * kD + tid);
+      if (h < G) qv[h] = load_q(a.q, a.qdt, ((int64_t)u * a.GR + h) * kD + tid);
   }
   // this channel's words and scales for the workgroup's blocks (0 past the store)
   const int64_t blk0 = (int64_t)blockIdx.x * a.ws.s_stride * kQB;
@@ -822,6 +823,9 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
   }
   int64_t nu, lo, hi;
   row_window(a, u, &nu, &lo, &hi, false);
+  // units of more than 4 heads have always reported that the filter does not
+  // take all of their heads at once (rows computed directly do not)
+  if (a.GR > 4 && blockIdx.x == 0 && tid == 0 && hi - lo > a.ws.cap) set_status(a.st, FATHOM_DEV_TOPK_FALLBACK);
   if (blockIdx.x == 0) {  // the unit's call state and its cell plan for the filter, while the words load
     unit_reset(a, u, t, lo, hi);
     CellPre pre;
@@ -881,7 +885,7 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
   const int64_t blk = blk0 + wave;
   const int64_t key = blk * kBlockTokens + lane;
   const bool el = blk < nbu && key >= lo && key < hi;
-  float* dst = a.ws.samp + (int64_t)u * G * kSmpRow + (int64_t)blockIdx.x * kSmpW + 2 * wave;
+  float* dst = a.ws.samp + (int64_t)u * a.GR * kSmpRow + (int64_t)blockIdx.x * kSmpW + 2 * wave;
   if (__ballot(el) == 0ull) {  // no eligible key in the block
     if (lane < 2 * G) gstore(dst + (int64_t)(lane >> 1) * kSmpRow + (lane & 1), kNegInf);
     return;
@@ -942,7 +946,7 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
 
 // ---------------------------------------------------------------- pass 2
 // One workgroup of two waves per row (one thread per channel for the depth
-// count), launched for the wide full pass or G > 4 (the cell filter finds tau
+// count), launched for the wide full pass (the cell filter finds tau
 // itself).  Sets the row's call state as unit_reset does; tau = the m-th
 // largest sample, found by wave 0 with a bitwise search over order-preserving
 // keys and ballot counts.  Leaves the unit's class in uovf[u] for pass 3.
@@ -1125,12 +1129,13 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 // 8 XCDs in turn), so the list is read once into that XCD's L2.
 // Every part reads the whole list and builds the whole histogram, so with more
 // rows than one round of the chip holds at 8 parts (3 workgroups a CU) a row has
-// one part up to k = 1024 and two up to k = 2048, where a part's share (k over
-// the parts and what survived past k, about k / 4) stays well inside kRankCap.
+// one part up to k = 1024 and two up to k = 2048, whose workgroups order up to
+// kRankCapFew keys (two a CU): every list that 8 parts could order, and more.
 // 512 rows at k = 1024: 39.5 us with 8 parts, 21.5 with 4, 14.2 with 2, 10.0
 // with one.
 constexpr int kRankParts = 8;
 constexpr int kRankRound = 3 * 256;
+constexpr int kRankCapFew = 7936;
 constexpr int kRankThreads = 512;   // the rank pass's workgroup (the select pass's is kXThreads)
 constexpr int kRankPer = 8;      // survivors per thread read with the count (the rest re-read)
 constexpr int kRankCap = 4096;   // survivors one part orders at most
@@ -1147,7 +1152,7 @@ struct RankShared {
 // Part z of row r (every thread of the workgroup calls it, for a row whose
 // list holds its top k); grp and hist are LDS areas of kRankCap composites
 // and kRankSub + 1 counts, 16-byte aligned.  Returns true when a part's share
-// exceeds kRankCap after all (many equal scores): the row is then computed
+// exceeds its area after all (many equal scores): the row is then computed
 // exactly.
 template <int T, int kRankParts>
 __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict__ idx, float* __restrict__ val,
@@ -1290,7 +1295,8 @@ __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict_
   __syncthreads();
   bool over = false;
 #pragma unroll
-  for (int x = 0; x < kRankParts; ++x) over |= hist[s_first[x + 1]] - hist[s_first[x]] > (uint32_t)kRankCap;
+  for (int x = 0; x < kRankParts; ++x)
+    over |= hist[s_first[x + 1]] - hist[s_first[x]] > (uint32_t)(kRankParts < 8 ? kRankCapFew : kRankCap);
   if (over) return true;
   const int s0 = (int)s_first[z], s1 = (int)s_first[z + 1];
   if (s0 == s1) return false;
@@ -1327,7 +1333,7 @@ __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict_
 // so the result is the documented top k whatever the chunking.
 constexpr int kXThreads = 1024;
 constexpr int kXWaves = kXThreads / kWave;  // blocks scored per stage, one per wave
-constexpr int kXSlots = 4;                  // exact rows in flight (workgroups per chunk index)
+constexpr int kXSlots = 4;                  // exact rows in flight at least (workgroups per chunk index)
 constexpr int kXMaxCells = kD * kPlanes;    // (channel, plane) cells of a unit at most
 constexpr int kXPre = kXMaxCells * kXWaves / kXThreads;  // plane words staged per thread at most
 constexpr int kXPreS = kD * kXWaves / kXThreads;         // scales staged per thread at most
@@ -1742,7 +1748,7 @@ __device__ __forceinline__ bool row_exact(const FusedArgs& a, int r) {
 template <int kRankParts>
 __global__ __launch_bounds__(kRankThreads) void fused_rank_kernel(FusedArgs a, int R, int32_t* __restrict__ idx,
                                                                  float* __restrict__ val) {
-  __shared__ uint64_t grp[kRankCap];
+  __shared__ uint64_t grp[kRankParts < 8 ? kRankCapFew : kRankCap];
   __shared__ __align__(16) uint32_t hist[kRankSub + 4];
   __shared__ RankShared<kRankThreads, kRankParts> RS;
   __shared__ int s_ex;
@@ -1759,12 +1765,12 @@ __global__ __launch_bounds__(kRankThreads) void fused_rank_kernel(FusedArgs a, i
 // after the rank pass below.  Workgroup b < rank_wg is part z of row r of the
 // ranks above unless the row is computed exactly; a part that finds its
 // share too large computes the row's chunks z, z + kRankParts, ... itself.
-// Workgroup b < xch kXSlots then takes chunk b mod xch of the rows computed
-// exactly with list index s, s + kXSlots, ... (s = b / xch): it marks the
+// Workgroup b < xch slots then takes chunk b mod xch of the rows computed
+// exactly with list index s, s + slots, ... (s = b / xch): it marks the
 // rows 1024 at a time (the same marks in every workgroup: they follow from
 // the filter's counts, tau and flags) and counts them in row order.
 static_assert((size_t)kRankCap * 8 + ((size_t)kRankSub + 4) * 4 <= kXLdsBytes, "the rank part's LDS inside the exact part's");
-__global__ __launch_bounds__(kXThreads) void fused_select_kernel(FusedArgs a, int R, int rank_wg,
+__global__ __launch_bounds__(kXThreads) void fused_select_kernel(FusedArgs a, int R, int rank_wg, int slots,
                                                                  int32_t* __restrict__ idx, float* __restrict__ val) {
   extern __shared__ __align__(16) unsigned char xl[];
   __shared__ XShared S;
@@ -1800,7 +1806,7 @@ __global__ __launch_bounds__(kXThreads) void fused_select_kernel(FusedArgs a, in
     }
   }
   const int xch = a.ws.xch, zz = b % xch, s = b / xch;
-  if (s >= kXSlots) return;
+  if (s >= slots) return;
   if (R <= kXThreads && cnt0 <= s) return;  // no exact row for this workgroup (the usual case)
   int before = 0;  // rows computed exactly below r0
   for (int r0 = 0; r0 < R; r0 += kXThreads) {
@@ -1811,8 +1817,8 @@ __global__ __launch_bounds__(kXThreads) void fused_select_kernel(FusedArgs a, in
     __syncthreads();
     int cnt = 0;
     for (int x = 0; x < kXThreads / 32; ++x) cnt += __popc(cflg[x]);
-    // list indexes jl = s (mod kXSlots) among this run's rows
-    for (int jl = before + (s - before % kXSlots + kXSlots) % kXSlots; jl < before + cnt; jl += kXSlots) {
+    // list indexes jl = s (mod slots) among this run's rows
+    for (int jl = before + (s - before % slots + slots) % slots; jl < before + cnt; jl += slots) {
       int x = 0, left = jl - before;
       while (left >= __popc(cflg[x])) left -= __popc(cflg[x++]);
       uint32_t w = cflg[x];
@@ -1883,7 +1889,7 @@ fathom_status launch_scan_topk_fused(const uint64_t* planes, const uint16_t* sca
   fa.nb_cap = nb_cap;
   fa.q = q;
   fa.qdt = qdt;
-  fa.G = G;
+  fa.G = fa.GR = G;
   fa.depths = depths;
   fa.lo = lo;
   fa.tail = tail;
@@ -1898,24 +1904,46 @@ fathom_status launch_scan_topk_fused(const uint64_t* planes, const uint16_t* sca
   // launches are skipped.  (A unit above the caller's bound is left to the
   // exact rows of the select pass.)
   const bool wide = !(max_unit_bits > 0 && max_unit_bits <= kCCWide && nb_cap < kOneNbMax);
-  if (G <= 4)
-    hipLaunchKernelGGL(fused_sample_kernel, dim3((unsigned)fa.ws.s_quads, (unsigned)U), dim3(kFT), 0, s, fa);
-  // narrow: the cell filter finds tau itself and the sample pass sets the
-  // rows' state, so the tau pass runs only for the wide pass or G > 4
-  if (wide || G > 4) hipLaunchKernelGGL(fused_tau_kernel, dim3(R), dim3(kTauThreads), 0, s, fa);
-  if (G <= 4) {
-    dim3 gm((unsigned)fa.ws.nwg, (unsigned)U);
-    launch_filter(fa, U, max_unit_bits, s);
-    if (wide) {
-      if (f16) hipLaunchKernelGGL((fused_main_kernel<true, 8>), gm, dim3(kFT), 0, s, fa);
-      else hipLaunchKernelGGL((fused_main_kernel<false, 8>), gm, dim3(kFT), 0, s, fa);
+  // The filter takes 4 heads of a unit at a time: more than 4 run the sample
+  // pass and the cell filter once per 4 heads, on row pointers of their own
+  // (the unit's plan, pools and class serve one after the other).
+  // 8 units of 131072 keys and 8 heads at 48 bits: 63 us (every row exact, before:
+  // 2.05 ms).
+  // Without a bound of at most 128 bits more than 4 heads take the exact rows:
+  // the tau pass sets their state.
+  if (G > 4 && wide) {
+    hipLaunchKernelGGL(fused_tau_kernel, dim3(R), dim3(kTauThreads), 0, s, fa);
+  } else {
+    for (int h0 = 0; h0 < G; h0 += 4) {
+      FusedArgs fh = fa;
+      fh.G = G - h0 < 4 ? G - h0 : 4;
+      fh.q = reinterpret_cast<const char*>(q) + (size_t)h0 * kD * (f16 ? 2 : 4);
+      fh.ws.tau += h0;
+      fh.ws.cnt += (size_t)h0 * kCntStride;
+      fh.ws.cand += (size_t)h0 * fh.ws.lcap;
+      fh.ws.samp += (size_t)h0 * kSmpRow;
+      fh.ws.xctl += h0;
+      hipLaunchKernelGGL(fused_sample_kernel, dim3((unsigned)fa.ws.s_quads, (unsigned)U), dim3(kFT), 0, s, fh);
+      // the cell filter finds tau itself and the sample pass sets the rows'
+      // state, so the tau pass runs only for the wide pass
+      if (wide) hipLaunchKernelGGL(fused_tau_kernel, dim3(R), dim3(kTauThreads), 0, s, fh);
+      launch_filter(fh, U, max_unit_bits, s);
+      if (wide) {
+        const dim3 gm((unsigned)fa.ws.nwg, (unsigned)U);
+        if (f16) hipLaunchKernelGGL((fused_main_kernel<true, 8>), gm, dim3(kFT), 0, s, fh);
+        else hipLaunchKernelGGL((fused_main_kernel<false, 8>), gm, dim3(kFT), 0, s, fh);
+      }
     }
   }
   const unsigned rank_wg = (unsigned)((R + kRankXcd - 1) / kRankXcd) * kRankXcd * kRankParts;
-  const unsigned xg = (unsigned)fa.ws.xch * (unsigned)kXSlots;
+  // Rows of one or a few chunks: as many of them in flight as fill the chip once
+  // (their number is not known here, so no more than there are rows).  480 rows
+  // of 8000 keys at 96 bits, all exact: 0.45 ms (11.2 ms with 4 in flight).
+  const int slots = std::max(kXSlots, std::min(R, 256 / fa.ws.xch));
+  const unsigned xg = (unsigned)fa.ws.xch * (unsigned)slots;
   if (rank_wg <= (unsigned)device_cus(dev)) {  // the rank parts fit one round: ranks and exact rows in one launch
     hipLaunchKernelGGL(fused_select_kernel, dim3(rank_wg > xg ? rank_wg : xg), dim3(kXThreads), kXLdsBytes, s, fa, R,
-                       (int)rank_wg, idx, val);
+                       (int)rank_wg, slots, idx, val);
   } else {
     const unsigned rows8 = (unsigned)((R + kRankXcd - 1) / kRankXcd) * kRankXcd;
     if (rows8 * kRankParts > kRankRound && k <= 1024)
@@ -1924,7 +1952,7 @@ fathom_status launch_scan_topk_fused(const uint64_t* planes, const uint16_t* sca
       hipLaunchKernelGGL(fused_rank_kernel<2>, dim3(rows8 * 2), dim3(kRankThreads), 0, s, fa, R, idx, val);
     else
       hipLaunchKernelGGL(fused_rank_kernel<kRankParts>, dim3(rank_wg), dim3(kRankThreads), 0, s, fa, R, idx, val);
-    hipLaunchKernelGGL(fused_select_kernel, dim3(xg), dim3(kXThreads), kXLdsBytes, s, fa, R, 0, idx, val);
+    hipLaunchKernelGGL(fused_select_kernel, dim3(xg), dim3(kXThreads), kXLdsBytes, s, fa, R, 0, slots, idx, val);
   }
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;

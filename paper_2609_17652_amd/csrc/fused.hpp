@@ -142,7 +142,8 @@ struct FusedArgs {
   int64_t nb_cap;
   const void* q;
   fathom_dtype qdt;
-  int G;
+  int G;   // query heads of a unit that this launch takes (its q and row pointers start at the first of them)
+  int GR;  // query heads per unit: rows of unit u are u GR + h
   const uint8_t* depths;
   int64_t lo, tail;
   int k;

@@ -367,3 +367,33 @@ def test_scan_topk_many_rows(k):
                 oi, ov, _ = oracle.topk(ref[h], k, lo, tail)
                 assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h, lo)
                 assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h, lo)
+
+
+@pytest.mark.parametrize("G,qdt", [(5, np.float32), (6, np.float16), (8, np.float16)])
+@pytest.mark.parametrize("B", [48, 64, 80, 96, 200])
+def test_scan_topk_more_than_4_heads(G, qdt, B):
+    """5 to 8 query heads: the cell filter 4 heads at a time for every slice count
+    (and units above the bound, which are computed exactly), beside a unit that is
+    computed directly and an empty one; with and without a bound, which takes the
+    exact path.  Bit-exact to the oracle, and the fallback flag as documented."""
+    rng = np.random.default_rng(G * B)
+    ns = [40000, 23457, 2000, 0, 33000]
+    U, cap, k = len(ns), 40000, 300
+    K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
+    n = dev(np.array(ns, np.int64))
+    planes, scales = F.fathom_pack(K, n)
+    q = rng.standard_normal((U, G, D)).astype(qdt)
+    var = np.exp(2 * rng.standard_normal((U, D))).astype(np.float32)
+    d, _ = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, B)
+    P, S, dn = planes.cpu().numpy().view(np.uint64), scales.cpu().numpy().view(np.uint16), d.cpu().numpy()
+    ref = [oracle.scores_f32(P[u], S[u], ns[u], q[u].astype(np.float32), dn[u]) for u in range(U)]
+    for lo, tail in [(0, 0), (4, 32)]:
+        for bound in (min(B, 96), 0):
+            st = F.new_status()
+            idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, lo, tail, dev_status=st, max_unit_bits=bound)
+            assert status(st) == (F.FATHOM_DEV_TOPK_FALLBACK | F.FATHOM_DEV_TOPK_SHORT)
+            for u in range(U):
+                for h in range(G):
+                    oi, ov, _ = oracle.topk(ref[u][h], k, lo, tail)
+                    assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h, lo, bound)
+                    assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h, lo, bound)
