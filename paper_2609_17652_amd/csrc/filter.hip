@@ -817,8 +817,8 @@ __device__ __forceinline__ void cwave_run(const FPlan<NS>& P, FilterLds<NS>& L, 
 // k keys survive (else the row is computed exactly).  tau of a row is about
 // the m-th largest of its samples (the sample pass keeps the two largest
 // exact scores of every block of a sampled quad), m = ceil(1.25 k sampled /
-// eligible) + 16;
-// when fewer samples exist the smallest one is used if about 1.1 k keys are
+// eligible) + 16, or the median where the samples are the blocks' r-th largest
+// scores (sample_rank); when fewer samples exist the smallest one is used if about 1.1 k keys are
 // expected above it, else tau = -inf (no filter).  Wave w of a workgroup
 // finds tau of its unit's row w (w < G) from its lanes' 8 samples each: the
 // largest 16-bit prefix of the order-preserving keys with at least m samples
@@ -846,7 +846,8 @@ __device__ __forceinline__ float ctau(const FusedArgs& a, const float (&sv)[kCTa
   m_s = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_u(m_s), kWave - 1);
   const uint32_t m_e = (uint32_t)(hi - lo), kk = (uint32_t)a.k;
   uint32_t m = m_s > 0u ? (5u * kk * m_s + 4u * m_e - 1u) / (4u * m_e) + 16u : 0u;
-  if (m > (uint32_t)nv) m = 10ull * (uint64_t)nv * m_e >= 11ull * kk * m_s ? (uint32_t)nv : 0u;
+  if (sample_rank(a.k, hi - lo) > 0) m = ((uint32_t)nv + 1u) >> 1;  // the median
+  else if (m > (uint32_t)nv) m = 10ull * (uint64_t)nv * m_e >= 11ull * kk * m_s ? (uint32_t)nv : 0u;
   if (m == 0u) return kNegInf;
   // the leading bits shared by the largest and the smallest sample are the
   // answer's too (m <= nv): the search starts below them

@@ -758,7 +758,8 @@ __device__ __forceinline__ void unit_reset(const FusedArgs& a, int u, int t, int
 // scores of its keys (Sec. 3.2-3.3: prefix dequantisation, fma over the
 // active channels ascending from +0, as the re-scoring of the full pass);
 // per head, the two largest scores of each block are its samples (-inf where
-// the block has fewer eligible keys).  The thread of each active channel
+// the block has fewer eligible keys), or its r-th largest where k is a large
+// part of the keys (sample_rank).  The thread of each active channel
 // loads its plane words and scales for the workgroup's 4 blocks as soon as
 // it knows its depth and stores them in LDS by the channel's ascending
 // position; every lane then reads its block's words back as broadcasts and
@@ -935,6 +936,18 @@ __global__ __launch_bounds__(kFT) void fused_sample_kernel(FusedArgs a) {
     k2[h] = lane == (int)__builtin_ctzll(at) ? 0u : k1[h];  // the first lane holding the largest drops out
   }
   wave_max4_u(k2);
+  const int rank = sample_rank(a.k, hi - lo);
+  if (rank > 0) {  // the block's rank-th largest key instead, twice, rounded down to 16 bits
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      uint32_t pre = 0u;
+      for (int b = 31; b >= 16; --b) {
+        const uint32_t cand = pre | (1u << b);
+        if (__popcll(__ballot(k1[h] >= cand)) >= rank) pre = cand;
+      }
+      m1[h] = k2[h] = pre;
+    }
+  }
   if (lane < 2 * G) {
     const int h = lane >> 1;
     const uint32_t k = (lane & 1) ? (h == 0 ? k2[0] : h == 1 ? k2[1] : h == 2 ? k2[2] : k2[3])
@@ -1003,7 +1016,9 @@ __global__ __launch_bounds__(kTauThreads) void fused_tau_kernel(FusedArgs a) {
   for (int o = 32; o >= 1; o >>= 1) m_s += __shfl_xor(m_s, o, kWave);
   const int64_t m_e = hi - lo;
   int64_t m = m_s > 0 ? (5 * (int64_t)a.k * m_s + 4 * m_e - 1) / (4 * m_e) + 16 : 0;
-  if (m > nv) {
+  if (sample_rank(a.k, m_e) > 0) {
+    m = (nv + 1) >> 1;  // the samples are the blocks' r-th largest scores: the median
+  } else if (m > nv) {
     // the samples cannot reach rank m: the smallest sample is used only when
     // the keys expected above it (nv m_e / m_s) are at least 1.1 k, else the
     // row is left unfiltered (exact path) instead of filtered in vain

@@ -397,3 +397,36 @@ def test_scan_topk_more_than_4_heads(G, qdt, B):
                     oi, ov, _ = oracle.topk(ref[u][h], k, lo, tail)
                     assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h, lo, bound)
                     assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h, lo, bound)
+
+
+@pytest.mark.parametrize("k,bound", [(300, 48), (560, 48), (620, 48), (2048, 48), (4096, 48), (2048, 0), (4096, 128)])
+@pytest.mark.parametrize("clumped", [False, True])
+def test_scan_topk_large_k(k, bound, clumped):
+    """k from 1/110 to 1/8 of the keys: the samples of tau are a block's two largest
+    scores or its r-th largest (k above about 1/53), in the cell filter and the
+    wide pass.  With independent keys the filter serves every row (no fallback
+    flag); with the large scores in a few blocks it may not, and the result is the
+    same.  Bit-exact to the oracle."""
+    rng = np.random.default_rng(k)
+    U, G = 5, 4
+    ns = [32768, 32701, 40000, 36007, 33333]
+    cap = max(ns)
+    K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
+    if clumped:
+        K[:, :1000] *= 6.0
+    n = dev(np.array(ns, np.int64))
+    planes, scales = F.fathom_pack(K, n)
+    q = rng.standard_normal((U, G, D)).astype(np.float16)
+    var = np.exp(2 * rng.standard_normal((U, D))).astype(np.float32)
+    d, _ = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, 48 if bound == 48 else 100)
+    P, S, dn = planes.cpu().numpy().view(np.uint64), scales.cpu().numpy().view(np.uint16), d.cpu().numpy()
+    st = F.new_status()
+    idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, 4, 32, dev_status=st, max_unit_bits=bound)
+    assert status(st) & ~F.FATHOM_DEV_TOPK_FALLBACK == 0
+    assert clumped or status(st) == 0
+    for u in range(U):
+        ref = oracle.scores_f32(P[u], S[u], ns[u], q[u].astype(np.float32), dn[u])
+        for h in range(G):
+            oi, ov, _ = oracle.topk(ref[h], k, 4, 32)
+            assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h)
+            assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h)
