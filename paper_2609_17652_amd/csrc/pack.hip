@@ -152,12 +152,12 @@ __device__ __forceinline__ void load_item(const KT* __restrict__ Ku, int64_t ld_
   }
 }
 
-// Quantise an item.  word[s][p] and a16[s] belong to channel 4s + g of the
-// lane's kCh channels; vmask has the bits of the block's valid tokens.
-template <typename KT>
-__device__ __forceinline__ void quantise_item(uint4 (&r)[kRows], uint64_t vmask,
-                                              uint64_t (&word)[PackItem<KT>::kSets][kPlanes],
-                                              uint16_t (&a16)[PackItem<KT>::kSets], uint32_t& flags) {
+// Quantise sets S0 .. S0 + SN - 1 of an item.  word[s][p] and a16[s] belong to
+// channel 4 (S0 + s) + g of the lane's kCh channels; vmask has the bits of the
+// block's valid tokens.
+template <typename KT, int S0, int SN>
+__device__ __forceinline__ void quantise_item(uint4 (&r)[kRows], uint64_t vmask, uint64_t (&word)[SN][kPlanes],
+                                              uint16_t (&a16)[SN], uint32_t& flags) {
 #pragma unroll
   for (int t = 0; t < kRows; ++t) add_zero<KT>(r[t]);  // -0 counts as +0
   float m[PackItem<KT>::kCh];
@@ -173,10 +173,10 @@ __device__ __forceinline__ void quantise_item(uint4 (&r)[kRows], uint64_t vmask,
     }
   }
 #pragma unroll
-  for (int s = 0; s < PackItem<KT>::kSets; ++s) {
+  for (int s = 0; s < SN; ++s) {
     uint32_t x[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(m[4 * s + e]);
+    for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(m[4 * (S0 + s) + e]);
     transpose_rows(x);
     const float a = fmaxf(fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])),
                           fmaxf(__uint_as_float(x[2]), __uint_as_float(x[3])));
@@ -192,11 +192,11 @@ __device__ __forceinline__ void quantise_item(uint4 (&r)[kRows], uint64_t vmask,
     for (int e = 0; e < 4; ++e) {
       const float s4 = __uint_as_float(q4[e]), s2 = __fmul_rn(s4, 0.5f), s1 = __fmul_rn(s4, 0.25f);
 #pragma unroll
-      for (int t = 0; t < kRows; ++t) pin_channel<KT>(r[t], 4 * s + e);
+      for (int t = 0; t < kRows; ++t) pin_channel<KT>(r[t], 4 * (S0 + s) + e);
       uint32_t b0 = 0, b1 = 0, b2 = 0, b3 = 0;  // sign bits, the last token processed at bit 0
 #pragma unroll
       for (int t = kRows - 1; t >= 0; --t) {
-        const float v = item_value<KT>(r[t], 4 * s + e);
+        const float v = item_value<KT>(r[t], 4 * (S0 + s) + e);
         const float t1 = __builtin_copysignf(s4, v);
         const float d1 = __fsub_rn(v, t1);
         float d2, d3;
@@ -220,7 +220,7 @@ __device__ __forceinline__ void quantise_item(uint4 (&r)[kRows], uint64_t vmask,
         uint32_t nan = 0;
 #pragma unroll
         for (int t = 0; t < kRows; ++t) {
-          const float v = item_value<KT>(r[t], 4 * s + e);
+          const float v = item_value<KT>(r[t], 4 * (S0 + s) + e);
           if (v != v) nan |= 1u << t;
         }
         b0 &= ~nan;  // code 8: not negative, below every threshold above 0
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kPackThreads, 4) void pack_tile_kernel(const KT* __
     if (tok0 < nu) {
       uint4 r[kRows];
       load_item<KT>(Ku, ld_tok, tok0, nu, c, r);
-      quantise_item<KT>(r, valid_mask(nu - tok0), w, a16, flags);
+      quantise_item<KT, 0, P::kSets>(r, valid_mask(nu - tok0), w, a16, flags);
     } else {
 #pragma unroll
       for (int s = 0; s < P::kSets; ++s) {
@@ -326,14 +326,40 @@ __global__ __launch_bounds__(kPackThreads, 4) void pack_tile_kernel(const KT* __
   wave_status(st, flags);
 }
 
-template <typename KT>
+// Sets S0 .. S0 + SN - 1 of the item of block b from channel c of unit u, stored as they are.
+template <typename KT, int S0, int SN>
+__device__ __forceinline__ void direct_item(const KT* Ku, int64_t ld_tok, int64_t b, int64_t nu, int u, int c,
+                                            int64_t nb_cap, uint64_t* __restrict__ planes, uint16_t* __restrict__ scales,
+                                            uint32_t& flags) {
+  const int g = (threadIdx.x & 63) >> 4;
+  const int64_t tok0 = b * kBlockTokens;
+  uint64_t w[SN][kPlanes] = {};
+  uint16_t a16[SN] = {};
+  if (tok0 < nu) {
+    uint4 r[kRows];
+    load_item<KT>(Ku, ld_tok, tok0, nu, c, r);
+    quantise_item<KT, S0, SN>(r, valid_mask(nu - tok0), w, a16, flags);
+  }
+#pragma unroll
+  for (int s = 0; s < SN; ++s) {
+    const int64_t j = (int64_t)u * kD + c + 4 * (S0 + s) + g;
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) planes[(j * kPlanes + p) * nb_cap + b] = w[s][p];
+    scales[j * nb_cap + b] = a16[s];
+  }
+}
+
+// SPLIT: an item's sets of 4 channels a lane go to waves of their own.  An append
+// is one wave's latency: one unit's fp16 block takes 4.1 us, 5.7 in one wave.
+template <typename KT, bool SPLIT>
 __global__ __launch_bounds__(kWave) void pack_direct_kernel(const KT* __restrict__ K, int64_t ld_tok, int64_t ld_unit,
                                                            const int64_t* __restrict__ n,
                                                            const int64_t* __restrict__ n_old, int64_t max_blocks,
                                                            int64_t nb_cap, uint64_t* __restrict__ planes,
                                                            uint16_t* __restrict__ scales, uint32_t* __restrict__ st) {
   using P = PackItem<KT>;
-  const int u = blockIdx.y, lane = threadIdx.x, x = lane & 15, g = lane >> 4;
+  constexpr int kParts = SPLIT ? P::kSets : 1;  // waves per item
+  const int u = blockIdx.y, lane = threadIdx.x, x = lane & 15;
   const int64_t nu = unit_tokens(n, u, nb_cap * kBlockTokens, lane == 0 ? st : nullptr);
   // blocks [bs, be) of this unit are written: all of them, or (append) the
   // ones from the first block holding a new token
@@ -347,25 +373,18 @@ __global__ __launch_bounds__(kWave) void pack_direct_kernel(const KT* __restrict
     bs = no / kBlockTokens;
     be = (nu + kBlockTokens - 1) / kBlockTokens;
   }
-  const int64_t b = bs + blockIdx.x / P::kPerBlock;
+  const int it = (int)(blockIdx.x / kParts), part = (int)(blockIdx.x % kParts);
+  const int64_t b = bs + it / P::kPerBlock;
   if (b >= be) return;
-  const int c = (int)(blockIdx.x % P::kPerBlock) * 16 * P::kCh + x * P::kCh;
-  const int64_t tok0 = b * kBlockTokens;
-  uint64_t w[P::kSets][kPlanes] = {};
-  uint16_t a16[P::kSets] = {};
+  const int c = (it % P::kPerBlock) * 16 * P::kCh + x * P::kCh;
+  const KT* Ku = K + (int64_t)u * ld_unit;
   uint32_t flags = 0;
-  if (tok0 < nu) {
-    uint4 r[kRows];
-    load_item<KT>(K + (int64_t)u * ld_unit, ld_tok, tok0, nu, c, r);
-    quantise_item<KT>(r, valid_mask(nu - tok0), w, a16, flags);
-  }
-#pragma unroll
-  for (int s = 0; s < P::kSets; ++s) {
-    const int64_t j = (int64_t)u * kD + c + 4 * s + g;
-#pragma unroll
-    for (int p = 0; p < kPlanes; ++p) planes[(j * kPlanes + p) * nb_cap + b] = w[s][p];
-    scales[j * nb_cap + b] = a16[s];
-  }
+  if constexpr (kParts == 1)
+    direct_item<KT, 0, P::kSets>(Ku, ld_tok, b, nu, u, c, nb_cap, planes, scales, flags);
+  else if (part == 0)
+    direct_item<KT, 0, 1>(Ku, ld_tok, b, nu, u, c, nb_cap, planes, scales, flags);
+  else
+    direct_item<KT, 1, 1>(Ku, ld_tok, b, nu, u, c, nb_cap, planes, scales, flags);
   wave_status(st, flags);
 }
 
@@ -380,9 +399,13 @@ static void launch_pack_t(const KT* K, int64_t ld_tok, int64_t ld_unit, const in
     if (mb > nb_cap) mb = nb_cap;
   }
   const int64_t tiles = (nb_cap + kTileBlocks - 1) / kTileBlocks;
-  if (n_old || tiles * U < kDirectTiles)
-    hipLaunchKernelGGL(pack_direct_kernel<KT>, dim3((unsigned)(mb * PackItem<KT>::kPerBlock), (unsigned)U), dim3(kWave),
-                       0, s, K, ld_tok, ld_unit, n, n_old, mb, nb_cap, planes, scales, st);
+  const unsigned items = (unsigned)(mb * PackItem<KT>::kPerBlock);
+  if (n_old)
+    hipLaunchKernelGGL((pack_direct_kernel<KT, true>), dim3(items * PackItem<KT>::kSets, (unsigned)U), dim3(kWave), 0, s,
+                       K, ld_tok, ld_unit, n, n_old, mb, nb_cap, planes, scales, st);
+  else if (tiles * U < kDirectTiles)
+    hipLaunchKernelGGL((pack_direct_kernel<KT, false>), dim3(items, (unsigned)U), dim3(kWave), 0, s, K, ld_tok, ld_unit,
+                       n, n_old, mb, nb_cap, planes, scales, st);
   else
     hipLaunchKernelGGL(pack_tile_kernel<KT>, dim3((unsigned)tiles, (unsigned)U), dim3(kPackThreads), 0, s, K, ld_tok,
                        ld_unit, n, nb_cap, planes, scales, st);
