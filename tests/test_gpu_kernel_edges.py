@@ -430,3 +430,40 @@ def test_scan_topk_large_k(k, bound, clumped):
             oi, ov, _ = oracle.topk(ref[h], k, 4, 32)
             assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h)
             assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h)
+
+
+@pytest.mark.parametrize("G", [4, 6])
+def test_scan_topk_sample_steps(G):
+    """Sample steps of 1 to 4 planes on both sides of the 64th active channel and
+    with 1 to 4 channels in the last step; windows whose lo and n leave most
+    sampled quads without a key, units below lo.  k is small beside the windows,
+    so the filter serves every row of at most 4 heads (no fallback flag: a sample
+    above its key's score would leave fewer than k survivors).  Bit-exact to the
+    oracle."""
+    rng = np.random.default_rng(40 + G)
+    ns = [60000, 27000, 60000, 20011, 33, 52345, 60000]
+    U, cap, k = len(ns), max(ns), 30
+    tail_of = [[1, 2, 1, 3], [4], [2, 2, 4, 1, 1, 1, 1, 3, 3], [1, 1, 4, 4, 1], [3, 1, 1], [2], [4, 3]]
+    dn = np.zeros((U, D), np.uint8)
+    for u, tl in enumerate(tail_of):
+        seq = [1] * (66 if u % 2 == 0 else 3) + tl
+        dn[u, np.sort(rng.permutation(D)[:len(seq)])] = seq
+    K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
+    n = dev(np.array(ns, np.int64))
+    q = rng.standard_normal((U, G, D)).astype(np.float16)
+    planes, scales = F.fathom_pack(K, n)
+    P, S = planes.cpu().numpy().view(np.uint64), scales.cpu().numpy().view(np.uint16)
+    ref = [oracle.scores_f32(P[u], S[u], ns[u], q[u].astype(np.float32), dn[u]) for u in range(U)]
+    for lo, tail in [(0, 0), (20000, 100), (24575, 1)]:
+        for bound in (128, 0):
+            st = F.new_status()
+            idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), dev(dn), k, lo, tail, dev_status=st,
+                                          max_unit_bits=bound)
+            s = status(st)
+            assert s & ~(F.FATHOM_DEV_TOPK_SHORT | F.FATHOM_DEV_TOPK_FALLBACK) == 0, hex(s)
+            assert G > 4 or not s & F.FATHOM_DEV_TOPK_FALLBACK, (lo, bound)
+            for u in range(U):
+                for h in range(G):
+                    oi, ov, _ = oracle.topk(ref[u][h], k, lo, tail)
+                    assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h, lo, bound)
+                    assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h, lo, bound)
