@@ -24,9 +24,9 @@
 // unit, whose words collect in LDS and leave as 128-byte runs per (channel,
 // plane).  70 KB of LDS and 128 VGPRs: two workgroups, 4 waves per SIMD (8
 // blocks a workgroup: 1.06 ms; 6 waves and 3 per SIMD: fp16 0.76 ms).
-// pack_direct_kernel: one wave per item, words stored as they are (8 bytes
-// each, every one in its own line); it serves appends and the packs whose
-// 16-block workgroups would leave CUs idle (below).
+// pack_direct_kernel: one wave per item (two for an append's fp16 item), words
+// stored as they are (8 bytes each, every one in its own line); it serves
+// appends and the packs whose 16-block workgroups would leave CUs idle (below).
 //
 // Append (n_old given): a block's fp16 scale depends on every token in it, so
 // a unit growing from n_old to n tokens re-packs blocks floor(n_old/64) ..
