@@ -107,6 +107,7 @@ constexpr int kCovThreads = 2 * kCovPairs * kWave;
 constexpr size_t kPartDoubles = (size_t)kCovTiles * 256 + kD;  // of one chunk: tiles as the lanes hold them, sums
 static_assert((kD * kD + kCalChunks * kPartDoubles) * sizeof(double) <= kCalUnitBytes, "calibration workspace");
 typedef double v4f64 __attribute__((ext_vector_type(4)));
+typedef float v4f32 __attribute__((ext_vector_type(4)));
 
 __host__ __device__ constexpr int tile_row(int t) {  // tile t of the upper triangle in row order: its block row
   int r = 0;
@@ -579,6 +580,55 @@ __global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* _
       const int row = 32 * (e >> 2) + 4 * li + (e & 3);
       Vs[row * kD + (col ^ (4 * ((row >> 2) & 7)))] = (float)((double)v[e] * is);
     }
+  }
+  __syncthreads();
+  // ---- V <- V (3 I - V^T V) / 2 = V + V E: the rotations leave the columns
+  // orthogonal to the rounding of their dot products (|V^T V - I|_F 5e-5), one
+  // Newton step to that of V's entries (1e-6).  E = (I - V^T V) / 2 in fp64, wave
+  // w its block row w, the blocks 4 to 7 to the right by symmetry; V E, a
+  // correction of 1e-6, in fp32. ----
+  {
+    const int i16 = lane & 15, g = lane >> 4;
+    auto at = [&](int row, int col) { return Vs[row * kD + (col ^ (4 * ((row >> 2) & 7)))]; };
+    float* E = X[buf];
+    v4f64 e[5];
+#pragma unroll
+    for (int t = 0; t < 5; ++t) e[t] = (v4f64){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int k = 0; k < kD; k += 4) {
+      const double a = (double)at(k + g, 16 * wave + i16);
+#pragma unroll
+      for (int t = 0; t < 5; ++t)
+        e[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)at(k + g, 16 * ((wave + t) & 7) + i16), e[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * wave + 4 * r + g, col = 16 * ((wave + t) & 7) + i16;
+        const float v = (float)(0.5 * ((row == col ? 1.0 : 0.0) - e[t][r]));
+        E[row * kD + col] = v;
+        if (t > 0 && t < 4) E[col * kD + row] = v;
+      }
+    __syncthreads();
+    v4f32 d[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) d[t] = (v4f32){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int k = 0; k < kD; k += 4) {
+      const float b = E[(k + g) * kD + 16 * wave + i16];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(16 * t + i16, k + g), b, d[t], 0, 0, 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * t + 4 * g + r;
+        float* v = &Vs[row * kD + ((16 * wave + i16) ^ (4 * ((row >> 2) & 7)))];
+        *v = __fadd_rn(*v, d[t][r]);
+      }
   }
   __syncthreads();
   // ---- eigenvalues: v^T C v / v^T v in fp64; wave w forms C V for columns

@@ -467,3 +467,27 @@ def test_scan_topk_sample_steps(G):
                     oi, ov, _ = oracle.topk(ref[u][h], k, lo, tail)
                     assert np.array_equal(idx[u, h].cpu().numpy(), oi), (u, h, lo, bound)
                     assert np.array_equal(val[u, h].cpu().numpy(), ov, equal_nan=True), (u, h, lo, bound)
+
+
+def spectrum_keys(rng, kind, n):
+    """Keys [n][128] of a covariance with the named spectrum in a random basis."""
+    Q = np.linalg.qr(rng.standard_normal((D, D)))[0]
+    s = {"decaying": np.geomspace(3.0, 0.05, D), "isotropic": np.ones(D), "steep": np.geomspace(30.0, 1e-3, D),
+         "outlier": np.where(np.arange(D) < 4, 40.0, np.exp(0.5 * rng.standard_normal(D)))}[kind]
+    return (rng.standard_normal((n, D)) * s) @ Q.T
+
+
+@pytest.mark.parametrize("kind", ["decaying", "isotropic", "steep", "outlier"])
+def test_calibrate_orthonormal(kind):
+    """The basis is orthonormal to the rounding of its entries, so that (qV).(kV)
+    is q.k.  Bound: entries rounded to fp32 (2^-24 relative) move the dot product
+    of two unit columns by at most 2^-23, so |V^T V - I|_F <= 128 * 2^-23."""
+    rng = np.random.default_rng(len(kind))
+    ns = [6000, 3001, 129, 40, 2]
+    K = np.zeros((len(ns), max(ns), D), np.float32)
+    for u, n in enumerate(ns):
+        K[u, :n] = spectrum_keys(rng, kind, n)
+    _, V, _ = F.fathom_klt_calibrate(dev(K), dev(np.array(ns, np.int64)))
+    V = V.cpu().numpy().astype(np.float64)
+    for u, n in enumerate(ns):
+        assert np.linalg.norm(V[u].T @ V[u] - np.eye(D)) <= D * 2.0 ** -23, (u, n)
