@@ -659,7 +659,11 @@ __global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* _
     den += __shfl_xor(den, 16, kWave);
     num += __shfl_xor(num, 32, kWave);
     den += __shfl_xor(den, 32, kWave);
-    if (g == 0) lam[c] = num / den;
+    // a covariance has no negative eigenvalue: a null direction's quotient is
+    // rounding error of either sign, and a negative variance is no input to the
+    // depth allocation (the test leaves a NaN as it is)
+    const double w0 = num / den;
+    if (g == 0) lam[c] = w0 < 0.0 ? 0.0 : w0;
   }
   __syncthreads();
   // ---- order by eigenvalue (descending, ties by position), fix signs, write ----

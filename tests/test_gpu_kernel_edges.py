@@ -491,3 +491,22 @@ def test_calibrate_orthonormal(kind):
     V = V.cpu().numpy().astype(np.float64)
     for u, n in enumerate(ns):
         assert np.linalg.norm(V[u].T @ V[u] - np.eye(D)) <= D * 2.0 ** -23, (u, n)
+
+
+def test_calibrate_few_keys():
+    """Units of 2 to 7 keys: the covariance has at most 6 directions, and the other
+    eigenvalues are rounding error of either sign.  None is negative, and the depth
+    allocation takes them as variances: no status bit, no plane for a channel whose
+    variance is zero while others are not."""
+    rng = np.random.default_rng(11)
+    U = 48
+    ns = 2 + np.arange(U) % 6
+    K = (rng.standard_normal((U, 7, D)) * np.exp(rng.standard_normal(D)) + 3.0).astype(np.float32)
+    n = dev(ns.astype(np.int64))
+    _, V, lam = F.fathom_klt_calibrate(dev(K), n)
+    assert bool((lam >= 0).all())
+    q = F.fathom_klt_rotate_q(dev(rng.standard_normal((U, 4, D)).astype(np.float32)), V)
+    st = F.new_status()
+    d, _ = F.fathom_alloc_depths(q, lam, F.FATHOM_WATERFILL, 4, dev_status=st)
+    assert status(st) == 0
+    assert bool(((d > 0) <= (lam > 0)).all())
