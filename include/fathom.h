@@ -325,7 +325,9 @@ size_t fathom_klt_calibrate_workspace_size(int U);
  *   out      [U] blocks of ld_out_unit floats (ld_out_unit >= n_cap * D): row i of
  *            unit u at out[u*ld_out_unit + i*D]; rows i < n[u] are written, the
  *            rest left as they were.  Pack it with fathom_pack (FATHOM_F32,
- *            ld_tok = D, ld_unit = ld_out_unit).
+ *            ld_tok = D, ld_unit = ld_out_unit).  fp32 keys may be rotated in
+ *            place (out == K, ld_tok == D, and with U > 1 ld_out_unit ==
+ *            ld_unit); otherwise out must not overlap K.
  * Device status: BAD_N.
  */
 fathom_status fathom_klt_rotate_keys(const void* K, fathom_dtype kdt, int64_t ld_tok, int64_t ld_unit,

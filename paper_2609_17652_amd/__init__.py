@@ -342,7 +342,8 @@ def fathom_klt_calibrate(K, n, mu=None, V=None, lam=None, ws=None, dev_status=No
 
 def fathom_klt_rotate_keys(K, n, mu, V, out=None, dev_status=None, stream=None):
     """Sec. 3.5: (k - mu) V for the first n[u] keys of each unit -> fp32 [U][n_cap][D] (rows past n[u]
-    are left as they were); pack it with fathom_pack."""
+    are left as they were); pack it with fathom_pack.  out may be K itself (fp32, contiguous rows), and must not
+    overlap it otherwise."""
     _dev(K, n, mu, V)
     U, ncap, D = K.shape
     if K.stride(2) != 1 or not mu.is_contiguous() or not V.is_contiguous():

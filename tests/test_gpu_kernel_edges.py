@@ -510,3 +510,23 @@ def test_calibrate_few_keys():
     d, _ = F.fathom_alloc_depths(q, lam, F.FATHOM_WATERFILL, 4, dev_status=st)
     assert status(st) == 0
     assert bool(((d > 0) <= (lam > 0)).all())
+
+
+@pytest.mark.parametrize("U,cap", [(1, 1), (3, 18), (2, 1027), (5, 4099), (1, 70001)])
+def test_rotate_keys_in_place(U, cap):
+    """fp32 keys rotated into their own rows, with ragged ends of groups and runs,
+    an empty unit, and U = 1 with any unit stride: the bits of a call with an
+    output of its own, and rows past n left as they were."""
+    rng = np.random.default_rng(cap)
+    ns = rng.integers(0, cap + 1, U)
+    ns[0] = cap
+    if U > 2:
+        ns[1] = 0
+    n = dev(ns.astype(np.int64))
+    K = torch.randn((U, cap, D), device=DEV)
+    mu = dev(rng.standard_normal((U, D)).astype(np.float32))
+    V = dev(rng.standard_normal((U, D, D)).astype(np.float32))
+    ref = K.clone()
+    F.fathom_klt_rotate_keys(K, n, mu, V, out=ref)
+    F.fathom_klt_rotate_keys(K, n, mu, V, out=K)
+    assert torch.equal(K.view(torch.int32), ref.view(torch.int32))
