@@ -530,3 +530,22 @@ def test_rotate_keys_in_place(U, cap):
     F.fathom_klt_rotate_keys(K, n, mu, V, out=ref)
     F.fathom_klt_rotate_keys(K, n, mu, V, out=K)
     assert torch.equal(K.view(torch.int32), ref.view(torch.int32))
+
+
+@pytest.mark.parametrize("share", [1.0, 0.8, 0.5, 0.1])
+def test_topk_shared_bins(share):
+    """A share of a row's scores in one bin of every digit (one value), the rest
+    spread: the first pass adds up a wave's lanes of one bin, or not, by chunk;
+    odd ends of chunks and rows of one score.  Indices and values equal to the
+    oracle's."""
+    rng = np.random.default_rng(int(10 * share))
+    ns = [12289, 4096, 65, 1, 8191]
+    s = rng.standard_normal((len(ns), 3, max(ns))).astype(np.float32)
+    s = np.where(rng.random(s.shape) < share, np.float32(0.75), s)
+    for k in (1, 70, 2500):
+        idx, val = F.fathom_topk(dev(s), dev(np.array(ns, np.int64)), k)
+        idx, val = idx.cpu().numpy(), val.cpu().numpy()
+        for u, n in enumerate(ns):
+            for h in range(3):
+                oi, ov, _ = oracle.topk(s[u, h, :n], k, 0, 0)
+                assert np.array_equal(idx[u, h], oi) and np.array_equal(val[u, h], ov, equal_nan=True), (k, u, h)
