@@ -103,6 +103,11 @@ __global__ __launch_bounds__(1024) void topk_init_kernel(RowState* __restrict__ 
 }
 static_assert(kBins == 4 * 1024, "topk_init_kernel clears 4 bins per thread");
 
+// Chunks whose equal keys at the threshold are counted together.
+__device__ __forceinline__ int64_t tie_chunks(const RowRange& rr) {
+  return ((rr.hi - rr.lo + kChunk - 1) / kChunk + kBins - 1) / kBins;
+}
+
 // Pass `pass` over the scores (see above).  Every workgroup of a row sees the
 // state the pass before left, and only the one that arrives last changes it.
 __global__ __launch_bounds__(kTopkThreads) void topk_pass_kernel(const float* __restrict__ scores, int64_t ld_s,
@@ -137,13 +142,19 @@ __global__ __launch_bounds__(kTopkThreads) void topk_pass_kernel(const float* __
     for (; c0 < rr.hi; c0 += step) {
       load();
       uint32_t take = 0;
-      int mine = 0;
+      int mine = 0, same = 0;
 #pragma unroll
       for (int e = 0; e < kPerThread; ++e) {
         const uint32_t key = score_key(v[e]);
-        const bool in = c0 + (int64_t)e * kTopkThreads + tid < rr.hi && (strict ? key > prefix : key >= prefix);
+        const bool ok = c0 + (int64_t)e * kTopkThreads + tid < rr.hi, in = ok && (strict ? key > prefix : key >= prefix);
         take |= (uint32_t)in << e;
         mine += in;
+        same += ok && key == prefix;
+      }
+      if (strict) {  // the equal keys of the chunk (the histogram is all zeros by now)
+        same = wave_sum_int(same);
+        if (lane == 0 && same > 0)
+          atomicAdd(&ws.hist[(int64_t)r * kBins + ((c0 - rr.lo) / kChunk) / tie_chunks(rr)], (uint32_t)same);
       }
       if (__ballot(take != 0) == 0) continue;
       int inc = mine;  // positions: one reservation per wave
@@ -309,6 +320,63 @@ __device__ void sort_desc(uint64_t* buf, int P) {
     }
 }
 
+// Exclusive prefix of hist[0 .. ns) in place (thread t owns a run of ns / kRankT,
+// or one), hist[ns] = c; first[y] = the sub-bucket where part y of 2^lp starts, the
+// first whose first position is at least y K / 2^lp.  Returns the largest count.
+__device__ __forceinline__ uint32_t rank_prefix(uint32_t* hist, uint32_t (*red)[kRankT / kWave], uint32_t* first, int ns, uint32_t c, uint32_t K, int lp) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kPer = kRankMaxSub / kRankT;
+  const int per = (ns + kRankT - 1) / kRankT, x0 = tid * per;
+  uint32_t hv[kPer], run = 0, most = 0;  // this thread's run (0 past it)
+#pragma unroll
+  for (int x = 0; x < kPer; ++x) hv[x] = x < per && x0 + x < ns ? hist[x0 + x] : 0u;
+#pragma unroll
+  for (int x = 0; x < kPer; ++x) {
+    run += hv[x];
+    most = hv[x] > most ? hv[x] : most;
+  }
+  uint32_t inc = run;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(inc, o, kWave);
+    if (lane >= o) inc += y;
+    const uint32_t m = __shfl_xor(most, o, kWave);
+    most = m > most ? m : most;
+  }
+  if (lane == 63) {
+    red[0][wave] = inc;
+    red[2][wave] = most;
+  }
+  if (tid <= 1 << lp && (uint32_t)tid * K >> lp == 0u) first[tid] = 0u;
+  __syncthreads();
+  uint32_t acc = inc - run;
+#pragma unroll
+  for (int x = 0; x < kRankT / kWave; ++x) {
+    if (x < wave) acc += red[0][x];
+    most = red[2][x] > most ? red[2][x] : most;
+  }
+  uint32_t at[kPer + 1];
+  at[0] = acc;
+#pragma unroll
+  for (int x = 0; x < kPer; ++x) {
+    at[x + 1] = at[x] + hv[x];
+    if (x < per && x0 + x < ns) hist[x0 + x] = at[x];
+  }
+#pragma unroll
+  for (int y = 1; y <= kRankShare; ++y) {  // bounds among this thread's positions
+    const uint32_t b = (uint32_t)y * K >> lp;
+    if (y <= 1 << lp && acc < b && at[kPer] >= b) {
+      int f = x0 + 1;
+#pragma unroll
+      for (int x = 1; x <= kPer; ++x) f += at[x] < b;
+      first[y] = (uint32_t)f;
+    }
+  }
+  if (tid == 0) hist[ns] = c;
+  __syncthreads();
+  return most;
+}
+
 __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restrict__ scores, int64_t ld_s,
                                                            const int64_t* __restrict__ n, int G, int R, int64_t lo,
                                                            int64_t tail, int k, TopkWs ws, int32_t* __restrict__ idx,
@@ -317,7 +385,6 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
   __shared__ uint32_t hist[kRankMaxSub + 1];
   __shared__ uint32_t red[3][kRankT / kWave];
   __shared__ uint32_t s_first[kRankShare + 1];
-  __shared__ uint32_t s_fill;
   // a row's workgroups on one XCD (workgroups are dealt to the 8 XCDs in turn): its list comes into one L2
   const int r = (int)(blockIdx.x / (8 * kRankShare)) * 8 + (int)(blockIdx.x % 8);
   const int z = (int)(blockIdx.x / 8) % kRankShare;
@@ -338,50 +405,53 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
     idx[(int64_t)r * k + rank] = i;
     if (val) val[(int64_t)r * k + rank] = row[i];
   };
-  if (S.strict) {  // the keys above, then the first equal ones in index order
-    if (z != 0) return;
+  if (S.strict) {
+    // behind the c keys above stand the first k - c equal ones in index order: the
+    // counts of the chunks give their positions, and the parts share the chunks
     const RowRange rr = row_range(n, u, ld_s, lo, tail, nullptr);
-    int P = 1;
-    while (P < k) P <<= 1;
-    for (uint32_t e = tid; e < (uint32_t)P; e += kRankT) grp[e] = e < c ? list[e] : 0ull;
-    if (tid == 0) s_fill = c;
+    const int64_t per = tie_chunks(rr) * kChunk;
+    const int nb = (int)((rr.hi - rr.lo + per - 1) / per);
+    for (int b = tid; b < nb; b += kRankT) hist[b] = ws.hist[(int64_t)r * kBins + b];
     __syncthreads();
-    for (int64_t b = rr.lo; b < rr.hi && s_fill < (uint32_t)k; b += kRankT * kRankRegs) {
-      const int64_t i0 = b + tid * kRankRegs;  // eight in a row per thread: thread order is index order
-      uint32_t eq = 0;
+    const uint32_t need = (uint32_t)k - c;
+    rank_prefix(hist, red, s_first, nb, 0u, 0u, 0);
+    for (int b = z; b < nb && hist[b] < need; b += kRankShare) {
+      uint32_t at0 = hist[b];
+      if (b + 1 < nb && hist[b + 1] == at0) continue;  // none
+      const int64_t end = rr.lo + (b + 1) * per < rr.hi ? rr.lo + (b + 1) * per : rr.hi;
+      for (int64_t i = rr.lo + b * per; i < end && at0 < need; i += kChunk) {
+        const int64_t i0 = i + tid * kRankRegs;  // eight in a row per thread: thread order is index order
+        uint32_t eq = 0;
 #pragma unroll
-      for (int x = 0; x < kRankRegs; ++x)
-        if (i0 + x < rr.hi && score_key(row[i0 + x]) == S.prefix) eq |= 1u << x;
-      const int mine = __popc(eq);
-      int inc = mine;
+        for (int x = 0; x < kRankRegs; ++x)
+          if (i0 + x < end && score_key(row[i0 + x]) == S.prefix) eq |= 1u << x;
+        const int mine = __popc(eq);
+        int inc = mine;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += y;
-      }
-      if (lane == 63) red[0][wave] = (uint32_t)inc;
-      __syncthreads();
-      uint32_t at = s_fill + (uint32_t)(inc - mine), sum = 0;
-      for (int x = 0; x < kRankT / kWave; ++x) {
-        if (x < wave) at += red[0][x];
-        sum += red[0][x];
-      }
-#pragma unroll
-      for (int x = 0; x < kRankRegs; ++x)
-        if (eq & (1u << x)) {
-          if (at < (uint32_t)k) grp[at] = ((uint64_t)S.prefix << 32) | (uint64_t)(~(uint32_t)(i0 + x));
-          ++at;
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(inc, o, kWave);
+          if (lane >= o) inc += y;
         }
-      __syncthreads();  // s_fill and red read by all
-      if (tid == 0) s_fill += sum;
-      __syncthreads();
+        if (lane == 63) red[0][wave] = (uint32_t)inc;
+        __syncthreads();
+        uint32_t at = at0 + (uint32_t)(inc - mine);
+        for (int x = 0; x < kRankT / kWave; ++x) {
+          if (x < wave) at += red[0][x];
+          at0 += red[0][x];
+        }
+#pragma unroll
+        for (int x = 0; x < kRankRegs; ++x)
+          if (eq & (1u << x)) {
+            if (at < need) emit(c + at, (uint64_t)(~(uint32_t)(i0 + x)));
+            ++at;
+          }
+        __syncthreads();  // red read by all
+      }
     }
-    sort_desc(grp, P);
-    for (int e = tid; e < k; e += kRankT) emit((uint32_t)e, grp[e]);
-    return;
+    __syncthreads();
   }
   const uint32_t K = c < (uint32_t)k ? c : (uint32_t)k;
-  if (z == 0 && K < (uint32_t)k) {  // fewer eligible keys than k
+  if (z == 0 && !S.strict && K < (uint32_t)k) {  // fewer eligible keys than k
     for (int e = (int)K + tid; e < k; e += kRankT) {
       idx[(int64_t)r * k + e] = -1;
       if (val) val[(int64_t)r * k + e] = __uint_as_float(0x7FC00000u);
@@ -427,46 +497,7 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
   };
   each([&](uint64_t v) { atomicAdd(&hist[sub_of(v)], 1u); });
   __syncthreads();
-  // exclusive prefix in place (thread t owns a run of ns / kRankT sub-buckets, or one), hist[ns] = c
-  const int per = ns / kRankT > 0 ? ns / kRankT : 1, x0 = tid * per;
-  uint32_t run = 0, most = 0;
-  for (int x = x0; x < x0 + per && x < ns; ++x) {
-    run += hist[x];
-    most = hist[x] > most ? hist[x] : most;
-  }
-  uint32_t inc = run;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(inc, o, kWave);
-    if (lane >= o) inc += y;
-    const uint32_t m = __shfl_xor(most, o, kWave);
-    most = m > most ? m : most;
-  }
-  if (lane == 63) {
-    red[0][wave] = inc;
-    red[2][wave] = most;
-  }
-  if (tid <= kRankShare && (uint32_t)tid * K / kRankShare == 0u) s_first[tid] = 0u;
-  __syncthreads();
-  uint32_t acc = inc - run;
-  for (int x = 0; x < kRankT / kWave; ++x) {
-    if (x < wave) acc += red[0][x];
-    most = red[2][x] > most ? red[2][x] : most;
-  }
-  for (int x = x0; x < x0 + per && x < ns; ++x) {
-    const uint32_t hx = hist[x];
-    hist[x] = acc;
-    // part y starts at the first sub-bucket whose first position is at least y K / parts:
-    // after the one whose positions cross that bound
-#pragma unroll
-    for (int y = 1; y <= kRankShare; ++y) {
-      const uint32_t b = (uint32_t)y * K / kRankShare;
-      if (acc < b && acc + hx >= b) s_first[y] = (uint32_t)x + 1u;
-    }
-    acc += hx;
-  }
-  if (tid == 0) hist[ns] = c;
-  __syncthreads();
+  const uint32_t most = rank_prefix(hist, red, s_first, ns, c, K, 3);
   bool sorted = most > (uint32_t)kRankSame;
   for (int y = 0; y < kRankShare; ++y) sorted |= hist[s_first[y + 1]] - hist[s_first[y]] > (uint32_t)kRankGroup;
   if (sorted) {  // the same for every workgroup of the row: the first sorts the whole list

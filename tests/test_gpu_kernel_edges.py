@@ -549,3 +549,28 @@ def test_topk_shared_bins(share):
             for h in range(3):
                 oi, ov, _ = oracle.topk(s[u, h, :n], k, 0, 0)
                 assert np.array_equal(idx[u, h], oi) and np.array_equal(val[u, h], ov, equal_nan=True), (k, u, h)
+
+
+@pytest.mark.parametrize("n,k,lo", [(131072, 1, 0), (131071, 1024, 5), (262144, 8192, 0), (1 << 20, 300, 4),
+                                    (4096 * 4096 + 70001, 2000, 3)])
+def test_topk_ties_by_chunk(n, k, lo):
+    """More equal scores at the threshold than a list holds, standing late, spread
+    thin, in every second chunk, and from the window's start on, with few and with
+    k - 1 scores above them; the last shape counts two chunks together.  The first
+    equal ones in index order: indices and values equal to the oracle's."""
+    rng = np.random.default_rng(k)
+    s = -1.0 - rng.random((4, n)).astype(np.float32)
+    ties = max(4 * k + 4096, n // 8)
+    s[0, n - ties:] = 0.0
+    s[1, rng.permutation(n)[:ties]] = 0.0
+    s[2, (np.arange(n) - lo) // 4096 % 2 == 1] = 0.0
+    s[3] = 0.0
+    s[0, rng.integers(lo, n, min(k, 50) - 1)] = 2.0
+    s[1, lo + rng.permutation(n - lo)[: k - 1]] = rng.integers(1, 9, k - 1)
+    s[3, ::3] = -0.0
+    idx, val = F.fathom_topk(dev(s[:, None]), dev(np.full(4, n, np.int64)), k, lo, 0)
+    idx, val = idx.cpu().numpy(), val.cpu().numpy()
+    for u in range(4):
+        oi, ov, _ = oracle.topk(s[u], k, lo, 0)
+        assert np.array_equal(idx[u, 0], oi), u
+        assert np.array_equal(val[u, 0], ov), u
