@@ -10,16 +10,18 @@
 //     Each row decides for itself; a row that is done leaves the later passes at
 //     once.  Scores spread over a few binades take one histogram and one
 //     collection: the scores are read twice.
-//   - the rank pass orders the lists and writes the top k: 8 workgroups a row
-//     share its output positions by a counting sort on interpolated
-//     sub-buckets, so that only keys sharing a sub-bucket are compared.
-//     Lists with many equal keys are sorted by one workgroup instead.
+//   - the rank pass orders the lists and writes the top k: up to 8 workgroups a
+//     row share its output positions by a counting sort on sub-buckets, so that
+//     only keys sharing a sub-bucket are compared: interpolated ones, or, where
+//     the scores are uneven, ones between entries of the list.
 //   - more equal keys at the threshold than a list holds: the list gets the
-//     keys above, and the rank pass takes the first equal ones in index order.
+//     keys above, the collecting pass counts the equal ones of every chunk, and
+//     the rank pass writes the first of them in index order from those counts.
 // Rows are split into chunks of kChunk elements so that a launch has many
-// workgroups even for a few rows.  32 rows of 131072 scores, k = 1024: 46 us
-// in 6 launches (13 launches with three histograms and single-thread pivots,
-// count, scan and write passes and a bitonic sort, before: 106 us).
+// workgroups even for a few rows.  32 rows of 131072 scores, k = 1024, in 6
+// launches: 38 us, 58 with ties at the threshold, 46 rounded to quarters, 63 in
+// one binade (13 launches with three histograms and single-thread pivots, count,
+// scan and write passes and a bitonic sort, before: 104, 155, 122, 112 us).
 #include <algorithm>
 #include <type_traits>
 
@@ -292,44 +294,36 @@ __global__ __launch_bounds__(kTopkThreads) void topk_pass_kernel(const float* __
 
 // ---------------------------------------------------------------- ranks
 constexpr int kRankT = 512;
-constexpr int kRankShare = 8;     // workgroups per row
+constexpr int kRankWaves = kRankT / kWave;
+constexpr int kRankShare = 8;     // workgroups per row at most
 constexpr int kRankMaxSub = 4096; // sub-buckets at most
 constexpr int kRankGroup = 4096;  // keys one workgroup groups at most
-constexpr int kRankSame = 64;     // keys of one sub-bucket at most (else the row is sorted)
+constexpr int kRankSame = 64;     // keys of one interpolated sub-bucket at most (else splitters)
 constexpr int kRankRegs = 8;      // list entries per thread kept in registers
+constexpr int kRankSplit = 255;   // splitters: 256 sub-buckets, an entry's in one byte
+constexpr int kRankFew = 512;     // lists up to here are ranked key against key
 
-static inline size_t rank_lds_keys(int lcap) {  // composites: a workgroup's group, or a whole list to sort
-  size_t p = kRankGroup;
-  while (p < (size_t)lcap) p <<= 1;
-  return p;
-}
+static_assert(4 * (kRankMaxSub + 320 - (kRankSplit + 2)) >= 2 * FATHOM_MAX_K, "a byte for every entry of a list");
 
-// Bitonic sort of buf[0..P) into descending order.
-__device__ void sort_desc(uint64_t* buf, int P) {
-  for (int size = 2; size <= P; size <<= 1)
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int x = threadIdx.x; x < P / 2; x += kRankT) {
-        const int i = ((x & ~(stride - 1)) << 1) | (x & (stride - 1));
-        const uint64_t a = buf[i], b = buf[i + stride];
-        if ((i & size) == 0 ? a < b : a > b) {
-          buf[i] = b;
-          buf[i + stride] = a;
-        }
-      }
-      __syncthreads();
-    }
-}
+struct RankLds {
+  __attribute__((aligned(16))) uint64_t grp[kRankGroup];
+  uint32_t hist[kRankMaxSub + 320];  // with splitters: 257 counts, then the entries' sub-buckets
+  uint64_t split[kRankSplit + 1];
+  uint32_t at[kRankSplit + 1];
+  uint32_t red[3][kRankWaves];
+  uint32_t first[kRankShare + 1];
+};
 
 // Exclusive prefix of hist[0 .. ns) in place (thread t owns a run of ns / kRankT,
 // or one), hist[ns] = c; first[y] = the sub-bucket where part y of 2^lp starts, the
 // first whose first position is at least y K / 2^lp.  Returns the largest count.
-__device__ __forceinline__ uint32_t rank_prefix(uint32_t* hist, uint32_t (*red)[kRankT / kWave], uint32_t* first, int ns, uint32_t c, uint32_t K, int lp) {
+__device__ __forceinline__ uint32_t rank_prefix(RankLds& L, int ns, uint32_t c, uint32_t K, int lp) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int kPer = kRankMaxSub / kRankT;
   const int per = (ns + kRankT - 1) / kRankT, x0 = tid * per;
   uint32_t hv[kPer], run = 0, most = 0;  // this thread's run (0 past it)
 #pragma unroll
-  for (int x = 0; x < kPer; ++x) hv[x] = x < per && x0 + x < ns ? hist[x0 + x] : 0u;
+  for (int x = 0; x < kPer; ++x) hv[x] = x < per && x0 + x < ns ? L.hist[x0 + x] : 0u;
 #pragma unroll
   for (int x = 0; x < kPer; ++x) {
     run += hv[x];
@@ -344,23 +338,23 @@ __device__ __forceinline__ uint32_t rank_prefix(uint32_t* hist, uint32_t (*red)[
     most = m > most ? m : most;
   }
   if (lane == 63) {
-    red[0][wave] = inc;
-    red[2][wave] = most;
+    L.red[0][wave] = inc;
+    L.red[2][wave] = most;
   }
-  if (tid <= 1 << lp && (uint32_t)tid * K >> lp == 0u) first[tid] = 0u;
+  if (tid <= 1 << lp && (uint32_t)tid * K >> lp == 0u) L.first[tid] = 0u;
   __syncthreads();
   uint32_t acc = inc - run;
 #pragma unroll
-  for (int x = 0; x < kRankT / kWave; ++x) {
-    if (x < wave) acc += red[0][x];
-    most = red[2][x] > most ? red[2][x] : most;
+  for (int x = 0; x < kRankWaves; ++x) {
+    if (x < wave) acc += L.red[0][x];
+    most = L.red[2][x] > most ? L.red[2][x] : most;
   }
   uint32_t at[kPer + 1];
   at[0] = acc;
 #pragma unroll
   for (int x = 0; x < kPer; ++x) {
     at[x + 1] = at[x] + hv[x];
-    if (x < per && x0 + x < ns) hist[x0 + x] = at[x];
+    if (x < per && x0 + x < ns) L.hist[x0 + x] = at[x];
   }
 #pragma unroll
   for (int y = 1; y <= kRankShare; ++y) {  // bounds among this thread's positions
@@ -369,25 +363,32 @@ __device__ __forceinline__ uint32_t rank_prefix(uint32_t* hist, uint32_t (*red)[
       int f = x0 + 1;
 #pragma unroll
       for (int x = 1; x <= kPer; ++x) f += at[x] < b;
-      first[y] = (uint32_t)f;
+      L.first[y] = (uint32_t)f;
     }
   }
-  if (tid == 0) hist[ns] = c;
+  if (tid == 0) L.hist[ns] = c;
   __syncthreads();
   return most;
 }
 
+// A row's list in order: `parts` workgroups share its K output positions by a
+// counting sort on sub-buckets interpolated between the smallest and the largest
+// key, so that only keys sharing a sub-bucket are compared.  Where those come out
+// uneven (equal scores, an outlier) the sub-buckets lie between 256 entries of the
+// list instead, taken at scattered places: composites are distinct, so these are
+// even whatever the scores (a sub-bucket of 8 times the mean among 16384 entries:
+// one row in 30).  Short uneven lists, and what still does not fit, are ranked
+// key against key.
 __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restrict__ scores, int64_t ld_s,
                                                            const int64_t* __restrict__ n, int G, int R, int64_t lo,
-                                                           int64_t tail, int k, TopkWs ws, int32_t* __restrict__ idx,
-                                                           float* __restrict__ val, uint32_t* __restrict__ st) {
-  extern __shared__ __attribute__((aligned(16))) uint64_t grp[];
-  __shared__ uint32_t hist[kRankMaxSub + 1];
-  __shared__ uint32_t red[3][kRankT / kWave];
-  __shared__ uint32_t s_first[kRankShare + 1];
+                                                           int64_t tail, int k, int lp, TopkWs ws,
+                                                           int32_t* __restrict__ idx, float* __restrict__ val,
+                                                           uint32_t* __restrict__ st) {
+  __shared__ RankLds L;
   // a row's workgroups on one XCD (workgroups are dealt to the 8 XCDs in turn): its list comes into one L2
-  const int r = (int)(blockIdx.x / (8 * kRankShare)) * 8 + (int)(blockIdx.x % 8);
-  const int z = (int)(blockIdx.x / 8) % kRankShare;
+  const int parts = 1 << lp;
+  const int r = (int)(blockIdx.x >> (3 + lp)) * 8 + (int)(blockIdx.x % 8);
+  const int z = (int)(blockIdx.x / 8) & (parts - 1);
   if (r >= R) return;
   const int u = r / G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t* list = ws.list + (int64_t)r * ws.lcap;
@@ -400,8 +401,7 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
   const RowState S = ws.state[r];
   const float* row = scores + (int64_t)r * ld_s;
   const uint32_t c = S.count < (uint32_t)ws.lcap ? S.count : (uint32_t)ws.lcap;
-  auto emit = [&](uint32_t rank, uint64_t v) {
-    const int32_t i = (int32_t)(~(uint32_t)v);
+  auto emit = [&](uint32_t rank, int32_t i) {
     idx[(int64_t)r * k + rank] = i;
     if (val) val[(int64_t)r * k + rank] = row[i];
   };
@@ -411,13 +411,13 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
     const RowRange rr = row_range(n, u, ld_s, lo, tail, nullptr);
     const int64_t per = tie_chunks(rr) * kChunk;
     const int nb = (int)((rr.hi - rr.lo + per - 1) / per);
-    for (int b = tid; b < nb; b += kRankT) hist[b] = ws.hist[(int64_t)r * kBins + b];
+    for (int b = tid; b < nb; b += kRankT) L.hist[b] = ws.hist[(int64_t)r * kBins + b];
     __syncthreads();
     const uint32_t need = (uint32_t)k - c;
-    rank_prefix(hist, red, s_first, nb, 0u, 0u, 0);
-    for (int b = z; b < nb && hist[b] < need; b += kRankShare) {
-      uint32_t at0 = hist[b];
-      if (b + 1 < nb && hist[b + 1] == at0) continue;  // none
+    rank_prefix(L, nb, 0u, 0u, 0);
+    for (int b = z; b < nb && L.hist[b] < need; b += parts) {
+      uint32_t at0 = L.hist[b];
+      if (b + 1 < nb && L.hist[b + 1] == at0) continue;  // none
       const int64_t end = rr.lo + (b + 1) * per < rr.hi ? rr.lo + (b + 1) * per : rr.hi;
       for (int64_t i = rr.lo + b * per; i < end && at0 < need; i += kChunk) {
         const int64_t i0 = i + tid * kRankRegs;  // eight in a row per thread: thread order is index order
@@ -432,17 +432,17 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
           const int y = __shfl_up(inc, o, kWave);
           if (lane >= o) inc += y;
         }
-        if (lane == 63) red[0][wave] = (uint32_t)inc;
+        if (lane == 63) L.red[0][wave] = (uint32_t)inc;
         __syncthreads();
         uint32_t at = at0 + (uint32_t)(inc - mine);
-        for (int x = 0; x < kRankT / kWave; ++x) {
-          if (x < wave) at += red[0][x];
-          at0 += red[0][x];
+        for (int x = 0; x < kRankWaves; ++x) {
+          if (x < wave) at += L.red[0][x];
+          at0 += L.red[0][x];
         }
 #pragma unroll
         for (int x = 0; x < kRankRegs; ++x)
           if (eq & (1u << x)) {
-            if (at < need) emit(c + at, (uint64_t)(~(uint32_t)(i0 + x)));
+            if (at < need) emit(c + at, (int32_t)(i0 + x));
             ++at;
           }
         __syncthreads();  // red read by all
@@ -459,17 +459,51 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
     if (tid == 0) set_status(st, FATHOM_DEV_TOPK_SHORT);
   }
   if (K == 0) return;
-  auto each = [&](auto fn) {  // every list entry
+  auto each = [&](auto fn) {  // every list entry and its place
 #pragma unroll
     for (int x = 0; x < kRankRegs; ++x)
-      if (tid + kRankT * x < (int)c) fn(pv[x]);
-    for (uint32_t e = tid + kRankT * kRankRegs; e < c; e += kRankT) fn(list[e]);
+      if (tid + kRankT * x < (int)c) fn(pv[x], (uint32_t)(tid + kRankT * x));
+    for (uint32_t e = tid + kRankT * kRankRegs; e < c; e += kRankT) fn(list[e], e);
+  };
+  // (hist zeroed before:) counts the sub-buckets, finds this part's and orders its keys; false (to every
+  // thread of every part alike) if a sub-bucket or a part's share is too large
+  auto order = [&](int ns, uint32_t same, auto sub_of, auto keep, auto kept) {
+    each([&](uint64_t v, uint32_t e) {
+      const int sb = sub_of(v);
+      keep(e, sb);
+      atomicAdd(&L.hist[sb], 1u);
+    });
+    __syncthreads();
+    bool over = rank_prefix(L, ns, c, K, lp) > same;
+    for (int y = 0; y < parts; ++y) over |= L.hist[L.first[y + 1]] - L.hist[L.first[y]] > (uint32_t)kRankGroup;
+    if (over) {
+      __syncthreads();  // the bounds are read before the next attempt's
+      return false;
+    }
+    const int s0 = (int)L.first[z], s1 = (int)L.first[z + 1];
+    if (s0 == s1) return true;
+    const uint32_t start = L.hist[s0], share = L.hist[s1] - start;
+    __syncthreads();  // every bound read before hist[s0 .. s1) serve as cursors
+    each([&](uint64_t v, uint32_t e) {  // group by sub-bucket; hist[s] ends at the group's end
+      const int sb = kept(v, e);
+      if (sb >= s0 && sb < s1) L.grp[atomicAdd(&L.hist[sb], 1u) - start] = v;
+    });
+    __syncthreads();
+    for (uint32_t e = tid; e < share; e += kRankT) {
+      const uint64_t v = L.grp[e];
+      const int sb = sub_of(v);
+      const uint32_t g0 = sb > s0 ? L.hist[sb - 1] : start, g1 = L.hist[sb];
+      uint32_t rank = g0;
+      for (uint32_t x = g0; x < g1; ++x) rank += L.grp[x - start] > v;
+      if (rank < K) emit(rank, (int32_t)(~(uint32_t)v));
+    }
+    return true;
   };
   int ns = 64;  // sub-buckets: a power of two, at least the entries
   while (ns < (int)c && ns < kRankMaxSub) ns <<= 1;
-  for (int x = tid; x <= ns; x += kRankT) hist[x] = 0u;
+  for (int x = tid; x < ns; x += kRankT) L.hist[x] = 0u;
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  each([&](uint64_t v) {
+  each([&](uint64_t v, uint32_t) {
     const uint32_t key = (uint32_t)(v >> 32);
     kmin = key < kmin ? key : kmin;
     kmax = key > kmax ? key : kmax;
@@ -481,51 +515,66 @@ __global__ __launch_bounds__(kRankT) void topk_rank_kernel(const float* __restri
     kmax = b > kmax ? b : kmax;
   }
   if (lane == 0) {
-    red[0][wave] = kmin;
-    red[1][wave] = kmax;
+    L.red[0][wave] = kmin;
+    L.red[1][wave] = kmax;
   }
   __syncthreads();
-  for (int x = 0; x < kRankT / kWave; ++x) {
-    kmin = red[0][x] < kmin ? red[0][x] : kmin;
-    kmax = red[1][x] > kmax ? red[1][x] : kmax;
+  for (int x = 0; x < kRankWaves; ++x) {
+    kmin = L.red[0][x] < kmin ? L.red[0][x] : kmin;
+    kmax = L.red[1][x] > kmax ? L.red[1][x] : kmax;
   }
   // sub-bucket: floor((kmax - key) * scale), not decreasing as the key falls
   const float scale = kmax > kmin ? (float)(ns - 1) / (float)(kmax - kmin) : 0.0f;
-  auto sub_of = [&](uint64_t v) {
+  auto sub_even = [&](uint64_t v) {
     const int sb = (int)__fmul_rn((float)(kmax - (uint32_t)(v >> 32)), scale);
     return sb < ns - 1 ? sb : ns - 1;
   };
-  each([&](uint64_t v) { atomicAdd(&hist[sub_of(v)], 1u); });
-  __syncthreads();
-  const uint32_t most = rank_prefix(hist, red, s_first, ns, c, K, 3);
-  bool sorted = most > (uint32_t)kRankSame;
-  for (int y = 0; y < kRankShare; ++y) sorted |= hist[s_first[y + 1]] - hist[s_first[y]] > (uint32_t)kRankGroup;
-  if (sorted) {  // the same for every workgroup of the row: the first sorts the whole list
-    if (z != 0) return;
-    int P = 1;
-    while (P < (int)c) P <<= 1;
-    for (uint32_t e = tid; e < (uint32_t)P; e += kRankT) grp[e] = e < c ? list[e] : 0ull;
-    __syncthreads();
-    sort_desc(grp, P);
-    for (uint32_t e = tid; e < K; e += kRankT) emit(e, grp[e]);
+  if (order(ns, (uint32_t)kRankSame, sub_even, [](uint32_t, int) {}, [&](uint64_t v, uint32_t) { return sub_even(v); }))
     return;
+  if (c > (uint32_t)kRankFew) {
+    const int x = tid & kRankSplit, half = tid / (kRankSplit + 1);  // two threads a splitter, half of the others each
+    const uint64_t mine = x < kRankSplit ? list[((uint64_t)((uint32_t)(x + 1) * 0x9E3779B1u) * c) >> 32] : 0ull;
+    if (half == 0) {
+      L.grp[x] = mine;
+      L.at[x] = 0u;
+      L.hist[x] = 0u;
+    }
+    __syncthreads();
+    uint32_t above = 0;
+#pragma unroll 8
+    for (int y = 0; y < (kRankSplit + 1) / 2; ++y) {
+      const int o = half * ((kRankSplit + 1) / 2) + y;
+      const uint64_t v = L.grp[o];
+      above += v > mine || (v == mine && o < x);
+    }
+    atomicAdd(&L.at[x], above);
+    __syncthreads();
+    if (half == 0) L.split[L.at[x]] = mine;  // largest first
+    __syncthreads();
+    uint8_t* id = reinterpret_cast<uint8_t*>(&L.hist[kRankSplit + 2]);
+    auto sub_split = [&](uint64_t v) {  // splitters above v
+      int b = 0;
+#pragma unroll
+      for (int h = (kRankSplit + 1) / 2; h >= 1; h >>= 1)
+        if (L.split[b + h - 1] > v) b += h;
+      return b;
+    };
+    if (order(kRankSplit + 1, (uint32_t)kRankGroup, sub_split, [&](uint32_t e, int sb) { id[e] = (uint8_t)sb; },
+              [&](uint64_t, uint32_t e) { return (int)id[e]; }))
+      return;
   }
-  const int s0 = (int)s_first[z], s1 = (int)s_first[z + 1];
-  if (s0 == s1) return;
-  const uint32_t start = hist[s0], share = hist[s1] - start;
-  __syncthreads();  // every bound read before hist[s0 .. s1) serve as cursors
-  each([&](uint64_t v) {  // group by sub-bucket; hist[s] ends at the group's end
-    const int sb = sub_of(v);
-    if (sb >= s0 && sb < s1) grp[atomicAdd(&hist[sb], 1u) - start] = v;
-  });
-  __syncthreads();
-  for (uint32_t e = tid; e < share; e += kRankT) {
-    const uint64_t v = grp[e];
-    const int sb = sub_of(v);
-    const uint32_t g0 = sb > s0 ? hist[sb - 1] : start, g1 = hist[sb];
-    uint32_t rank = g0;
-    for (uint32_t x = g0; x < g1; ++x) rank += grp[x - start] > v;
-    if (rank < K) emit(rank, v);
+  for (uint32_t e0 = z * kRankT; e0 < c; e0 += parts * kRankT) {
+    const uint64_t v = e0 + tid < c ? list[e0 + tid] : 0ull;
+    uint32_t rank = 0;
+    for (uint32_t b = 0; b < c; b += kRankGroup) {
+      const uint32_t m = c - b < (uint32_t)kRankGroup ? c - b : (uint32_t)kRankGroup;
+      __syncthreads();
+      for (uint32_t x = tid; x < m; x += kRankT) L.grp[x] = list[b + x];
+      __syncthreads();
+#pragma unroll 8
+      for (uint32_t x = 0; x < m; ++x) rank += L.grp[x] > v;
+    }
+    if (e0 + tid < c && rank < K) emit(rank, (int32_t)(~(uint32_t)v));
   }
 }
 
@@ -544,8 +593,13 @@ fathom_status launch_topk(const float* scores, int64_t ld_s, const int64_t* n, i
   for (int pass = 0; pass <= kDigits; ++pass)
     hipLaunchKernelGGL(topk_pass_kernel, dim3((unsigned)even(std::min(nch, pass < 2 ? most : few)), (unsigned)R),
                        dim3(kTopkThreads), 0, s, scores, ld_s, n, G, lo, tail, pass, w, st);
-  hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)((R + 7) / 8 * 8 * kRankShare)), dim3(kRankT),
-                     rank_lds_keys(w.lcap) * 8, s, scores, ld_s, n, G, R, lo, tail, k, w, idx, val, st);
+  // Workgroups a row: 8 while three a CU hold them all, then fewer (each reads and
+  // counts the whole list), but a share of at most 2048 positions each.
+  int lp = 3;
+  static_assert(kRankShare == 8, "8 = 2^3 workgroups a row");
+  while (lp > 0 && (int64_t)R << lp > 3 * 256 && k <= 2048 << (lp - 1)) --lp;
+  hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)((R + 7) / 8 * 8) << lp), dim3(kRankT), 0, s, scores, ld_s, n, G,
+                     R, lo, tail, k, lp, w, idx, val, st);
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;
 }

@@ -574,3 +574,32 @@ def test_topk_ties_by_chunk(n, k, lo):
         oi, ov, _ = oracle.topk(s[u], k, lo, 0)
         assert np.array_equal(idx[u, 0], oi), u
         assert np.array_equal(val[u, 0], ov), u
+
+
+@pytest.mark.parametrize("kind", ["round", "outlier", "narrow", "pair", "normal", "same"])
+@pytest.mark.parametrize("R,n,k", [(10, 1000, 40), (10, 30000, 8192), (100, 9001, 2048), (104, 9001, 5000), (200, 7000, 700),
+                                   (400, 3000, 30), (400, 9001, 2048)])
+def test_topk_uneven_lists(kind, R, n, k):
+    """Lists whose interpolated sub-buckets are uneven (scores rounded to quarters,
+    an outlier above or below the rest, one binade, two values, one value), short
+    ones and long ones, beside even ones: 8, 4, 2 and 1 workgroups a row.  Indices
+    and values equal to the oracle's."""
+    rng = np.random.default_rng(R + k)
+    s = rng.standard_normal((R, 1, n)).astype(np.float32)
+    if kind == "round":
+        s = np.round(4 * s) / 4
+    elif kind == "outlier":
+        s[:, 0, 7] = 1e30
+        s[::2, 0, n - 1] = np.inf
+    elif kind == "narrow":
+        s = (1000 + 1e-3 * s).astype(np.float32)
+    elif kind == "pair":
+        s = np.where(s > 2.5, np.float32(2), np.float32(1))
+    elif kind == "same":
+        s[:] = -3.0
+    idx, val = F.fathom_topk(dev(s), dev(np.full(R, n, np.int64)), k)
+    idx, val = idx.cpu().numpy(), val.cpu().numpy()
+    for u in sorted({0, 1, 7, 8, R // 2, R - 1}):
+        oi, ov, _ = oracle.topk(s[u, 0], k, 0, 0)
+        assert np.array_equal(idx[u, 0], oi), u
+        assert np.array_equal(val[u, 0], ov), u
