@@ -1183,7 +1183,9 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 // Every part reads the whole list and builds the whole histogram, so with more
 // rows than one round of the chip holds at 8 parts (3 workgroups a CU) a row has
 // one part up to k = 1024 and two up to k = 2048, whose workgroups order up to
-// kRankCapFew keys (two a CU): every list that 8 parts could order, and more.
+// kRankCapFew keys (two a CU): every list that 8 parts could order, and more, but
+// no more than kRankCap keys of one sub-bucket, which are compared pair by pair
+// (512 rows with 7488 equal scores at k = 2048: 11.1 ms, 2.0 as exact rows).
 // 512 rows at k = 1024: 39.5 us with 8 parts, 21.5 with 4, 14.2 with 2, 10.0
 // with one.
 constexpr int kRankParts = 8;
@@ -1201,6 +1203,7 @@ struct RankShared {
   uint32_t s_c, s_ovf;
   float s_tau;
   int64_t s_n;
+  uint32_t s_same;  // a sub-bucket has more than kRankCap keys (fewer than 8 parts)
 };
 // Part z of row r (every thread of the workgroup calls it, for a row whose
 // list holds its top k); grp and hist are LDS areas of kRankCap composites
@@ -1232,6 +1235,7 @@ __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict_
   else if (tid == 1) s_tau = gload(a.ws.tau + r);
   else if (tid == 2) s_ovf = gload(a.ws.uovf + u);
   else if (tid == 3) s_n = gload(a.n + u);
+  else if (kRankParts < 8 && tid == 4) RS.s_same = 0u;
   __syncthreads();
   int64_t nu = s_n;
   if (nu < 0 || nu > a.nb_cap * kBlockTokens) nu = 0;
@@ -1307,6 +1311,12 @@ __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict_
     uint32_t run = 0;
 #pragma unroll
     for (int x = 0; x < kPerMax; ++x) run += hv[x];
+    if constexpr (kRankParts < 8) {  // (8 parts: no share holds as many)
+      uint32_t most = 0;
+#pragma unroll
+      for (int x = 0; x < kPerMax; ++x) most = hv[x] > most ? hv[x] : most;
+      if (most > (uint32_t)kRankCap) RS.s_same = 1u;
+    }
     const uint32_t inc = wave_incl_scan_u(run);
     if (lane == kWave - 1) s_part[wave] = inc;
     __syncthreads();
@@ -1346,7 +1356,7 @@ __device__ bool rank_part(const FusedArgs& a, int r, int z, int32_t* __restrict_
     }
   }
   __syncthreads();
-  bool over = false;
+  bool over = kRankParts < 8 && RS.s_same != 0u;
 #pragma unroll
   for (int x = 0; x < kRankParts; ++x)
     over |= hist[s_first[x + 1]] - hist[s_first[x]] > (uint32_t)(kRankParts < 8 ? kRankCapFew : kRankCap);

@@ -603,3 +603,31 @@ def test_topk_uneven_lists(kind, R, n, k):
         oi, ov, _ = oracle.topk(s[u, 0], k, 0, 0)
         assert np.array_equal(idx[u, 0], oi), u
         assert np.array_equal(val[u, 0], ov), u
+
+
+@pytest.mark.parametrize("k", [1000, 2000])
+def test_scan_topk_rank_equal_scores(k):
+    """112 rows, one and two rank parts a row, with units whose best keys are 62 or
+    70 equal blocks: 3968 equal scores are ranked, 4480 are more than a sub-bucket
+    may hold (4096), so the rows are computed exactly, as the flag says.  Bit-exact
+    to the oracle."""
+    rng = np.random.default_rng(k)
+    U, G, nb = 28, 4, 375
+    n = dev(np.full(U, 64 * nb, np.int64))
+    q = rng.standard_normal((U, G, D)).astype(np.float32)
+    K = torch.randn((U, 64 * nb, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
+    d, _ = F.fathom_alloc_depths(dev(q), dev(np.ones((U, D), np.float32)), F.FATHOM_WATERFILL, 48)
+    for m in (62, 70):
+        Km = K.clone()
+        Km.view(U, nb, 64, D)[:2, dev(rng.permutation(nb)[:m])] = dev(16 * q[:2].sum(1)).view(2, 1, 1, D)
+        planes, scales = F.fathom_pack(Km, n)
+        st = F.new_status()
+        idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, dev_status=st, max_unit_bits=48)
+        assert status(st) == (F.FATHOM_DEV_TOPK_FALLBACK if 64 * m > 4096 else 0), m
+        for u in (0, 1, 2, U - 1):
+            ref = oracle.scores_f32(planes[u].cpu().numpy().view(np.uint64), scales[u].cpu().numpy().view(np.uint16),
+                                    64 * nb, q[u], d[u].cpu().numpy())
+            for h in range(G):
+                oi, ov, _ = oracle.topk(ref[h], k, 0, 0)
+                assert u > 1 or ov[0] == ov[-1]  # the equal ones fill the top k
+                assert np.array_equal(idx[u, h].cpu().numpy(), oi) and np.array_equal(val[u, h].cpu().numpy(), ov), (m, u, h)
