@@ -1182,7 +1182,10 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 // 8 XCDs in turn), so the list is read once into that XCD's L2.
 // Every part reads the whole list and builds the whole histogram, so with more
 // rows than one round of the chip holds at 8 parts (3 workgroups a CU) a row has
-// one part up to k = 1024 and two up to k = 2048, whose workgroups order up to
+// one part up to k = 1024 and two up to k = 2048 (two as well up to 128 rows,
+// where one part would leave half of the CUs without any: 128 rows with every
+// score 156 times 80.5 us the call with one part, 73.5 with two, the same without
+// equal scores; 192 rows 45.8 and 47.1 without), whose workgroups order up to
 // kRankCapFew keys (two a CU): every list that 8 parts could order, and more, but
 // no more than kRankCap keys of one sub-bucket, which are compared pair by pair
 // (512 rows with 7488 equal scores at k = 2048: 11.1 ms, 2.0 as exact rows).
@@ -2009,7 +2012,7 @@ fathom_status launch_scan_topk_fused(const uint64_t* planes, const uint16_t* sca
                        (int)rank_wg, slots, idx, val);
   } else {
     const unsigned rows8 = (unsigned)((R + kRankXcd - 1) / kRankXcd) * kRankXcd;
-    if (rows8 * kRankParts > kRankRound && k <= 1024)
+    if (rows8 * kRankParts > kRankRound && rows8 > 128 && k <= 1024)
       hipLaunchKernelGGL(fused_rank_kernel<1>, dim3(rows8), dim3(kRankThreads), 0, s, fa, R, idx, val);
     else if (rows8 * kRankParts > kRankRound && k <= 2048)
       hipLaunchKernelGGL(fused_rank_kernel<2>, dim3(rows8 * 2), dim3(kRankThreads), 0, s, fa, R, idx, val);

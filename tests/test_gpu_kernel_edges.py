@@ -607,12 +607,12 @@ def test_topk_uneven_lists(kind, R, n, k):
 
 @pytest.mark.parametrize("k", [1000, 2000])
 def test_scan_topk_rank_equal_scores(k):
-    """112 rows, one and two rank parts a row, with units whose best keys are 62 or
+    """136 rows, one and two rank parts a row, with units whose best keys are 62 or
     70 equal blocks: 3968 equal scores are ranked, 4480 are more than a sub-bucket
     may hold (4096), so the rows are computed exactly, as the flag says.  Bit-exact
     to the oracle."""
     rng = np.random.default_rng(k)
-    U, G, nb = 28, 4, 375
+    U, G, nb = 34, 4, 375
     n = dev(np.full(U, 64 * nb, np.int64))
     q = rng.standard_normal((U, G, D)).astype(np.float32)
     K = torch.randn((U, 64 * nb, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
