@@ -192,9 +192,12 @@ template <int G>
 static void launch_scan_g(const uint64_t* planes, const uint16_t* scales, const int64_t* n, int U, int64_t nb_cap,
                           const void* q, fathom_dtype qdt, const uint8_t* depths, float* scores, int64_t ld_s,
                           uint32_t* st, hipStream_t s) {
-  // 4 blocks a wave where that fills the chip, 1 where it would not: a unit of
-  // 3000 keys takes 13.9 us with one and 21.6 with four.
-  if ((nb_cap + 15) / 16 * U >= 256)
+  // 4 blocks a wave where that gives every CU more than one workgroup (the more so
+  // the more heads: their accumulators lengthen a wave), else 1.  A unit of 3000
+  // keys takes 13.9 us with one and 21.6 with four; at 48 bits, 2 x 131072 keys (256
+  // workgroups of four) 9.6 and 10.4 us at 1 head, 13.2 and 18.3 at 8; 3 x 131072
+  // (384) 12.7 and 11.3, 16.7 and 18.6; 4 x 131072 15.0 and 11.5, 19.4 and 18.5.
+  if ((nb_cap + 15) / 16 * U >= 256 + 16 * G)
     hipLaunchKernelGGL((scan_kernel<G, 4>), dim3((unsigned)((nb_cap + 15) / 16), (unsigned)U), dim3(kScanThreads), 0, s,
                        planes, scales, n, nb_cap, q, qdt, depths, scores, ld_s, st);
   else

@@ -192,7 +192,7 @@ def test_topk_refinement(kind, k, lo, tail):
 
 
 @pytest.mark.parametrize("G,qdt", [(1, np.float32), (3, np.float16), (4, np.float16), (8, np.float32)])
-@pytest.mark.parametrize("U,nb_cap", [(43, 90), (2, 19)])
+@pytest.mark.parametrize("U,nb_cap", [(43, 90), (2, 19), (80, 90)])
 def test_scan_stages(G, qdt, U, nb_cap):
     """fathom_scan with four blocks and one block a wave, 0 to 128 active channels
     (none to four stages), every depth, ragged ends and a score row shorter than
