@@ -182,12 +182,12 @@ __global__ __launch_bounds__(kAttnThreads) void attn_chunk_kernel(AttnArgs a, in
   attn_chunk<VEC>(a, r, c, [&](int i, float v) { gstore_f(wp + i, v); });
 }
 
-// Rows of at most kRowChunks chunks (one wave each): one workgroup takes the
-// whole row and combines its chunks' partials in LDS, in the order of the
-// combine kernel (the same bits), so there is no second launch and no workspace
-// traffic.  One KV head at k = 64: 5.1 us of kernel time against 6.5 in two
-// launches; 32 rows at k = 500 (16 chunks) the same time in one launch as in
-// two; at 32 chunks, two a wave, a row's CU is the bound: 17.7 us against 11.0.
+// Rows of at most kRowChunks chunks (one wave each; the launch's rule): one
+// workgroup takes the whole row and combines its chunks' partials in LDS, in the
+// order of the combine kernel (the same bits), so there is no second launch and no
+// workspace traffic.  One KV head at k = 64: 5.1 us of kernel time against 6.5 in
+// two launches; at 32 chunks, two a wave, a row's CU is the bound: 17.7 us against
+// 11.0.
 constexpr int kRowChunks = 16;
 constexpr int kRowThreads = 1024;
 template <bool VEC>
@@ -296,9 +296,14 @@ fathom_status launch_sparse_attn(const void* q, fathom_dtype qdt, const uint16_t
   // 16-byte row loads when every row start is 16-byte aligned
   const bool vec = ((reinterpret_cast<uintptr_t>(Krows) | reinterpret_cast<uintptr_t>(Vrows)) & 15) == 0 &&
                    (ld_tok & 7) == 0 && (ld_unit & 7) == 0;
-  // (with more rows than CUs a 16-wave workgroup per row gains nothing: 512 rows
-  // of 16 chunks take 29.2 us against 28.1)
-  if (S <= kRowChunks / 2 || (S <= kRowChunks && U * G <= 256)) {
+  // With more rows than CUs a 16-wave workgroup per row gains nothing (512 rows of
+  // 16 chunks: 29.2 us against 28.1 in two launches), and with few rows the chunks
+  // of a row are better spread over the idle CUs from some length on (4 or 32 rows:
+  // 10 chunks 7.5 and 7.7 us against 7.7 and 8.0, 16 chunks 9.8 and 10.0 against 7.7
+  // and 8.0; 96 rows, 12 and 14 chunks: 9.3 and 10.8 against 9.9 and 10.3; 160 rows, 16
+  // chunks: 13.5 against 14.7).
+  const int rows = U * G;
+  if (S <= kRowChunks / 2 || (S <= kRowChunks && rows <= 256 && S <= 9 + rows / 22)) {
     const dim3 threads(S <= 4 ? 256 : S <= 8 ? 512 : kRowThreads);
     if (vec) hipLaunchKernelGGL(attn_row_kernel<true>, dim3((unsigned)(U * G)), threads, 0, s, a, S, out);
     else hipLaunchKernelGGL(attn_row_kernel<false>, dim3((unsigned)(U * G)), threads, 0, s, a, S, out);

@@ -313,10 +313,10 @@ def test_scan_topk_81_to_128_cells(G, qdt):
 
 
 @pytest.mark.parametrize("k", [0, 1, 92, 128, 220, 257, 476, 512, 513])
-@pytest.mark.parametrize("U", [3, 70])
+@pytest.mark.parametrize("U", [3, 45, 70])
 def test_sparse_attn_row_lists(k, U):
     """Row lists of 1 to 17 chunks on both sides of the one-workgroup rule (at most
-    8 chunks, or 16 with at most 256 rows), with sink and local rows, skipped
+    8 chunks, 9 with 12 rows, 16 with 180, 8 with more than 256), with sink and local rows, skipped
     entries, a short unit, an empty unit and empty chunks.  Bound: the oracle's,
     1e-5 of the softmax-weighted mean of |V|, at most 1e-5 max |V|."""
     rng = np.random.default_rng(k + U)
