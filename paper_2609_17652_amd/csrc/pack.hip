@@ -25,8 +25,9 @@
 // plane).  70 KB of LDS and 128 VGPRs: two workgroups, 4 waves per SIMD (8
 // blocks a workgroup: 1.06 ms; 6 waves and 3 per SIMD: fp16 0.76 ms).
 // pack_direct_kernel: one wave per item (two for an append's fp16 item), words
-// stored as they are (8 bytes each, every one in its own line); it serves
+// stored as they are (8 bytes each, every one in its own line); it serves large
 // appends and the packs whose 16-block workgroups would leave CUs idle (below).
+// pack_append_kernel: a token a lane; it serves the appends of a decode step.
 //
 // Append (n_old given): a block's fp16 scale depends on every token in it, so
 // a unit growing from n_old to n tokens re-packs blocks floor(n_old/64) ..
@@ -349,6 +350,82 @@ __device__ __forceinline__ void direct_item(const KT* Ku, int64_t ld_tok, int64_
   }
 }
 
+// Tokens of a unit and the blocks [bs, be) that an append re-packs, from the first
+// block holding a new token; false leaves the unit as it was.
+__device__ __forceinline__ bool append_range(const int64_t* n, const int64_t* n_old, int u, int64_t max_blocks,
+                                             int64_t nb_cap, uint32_t* st, int64_t* nu, int64_t* bs, int64_t* be) {
+  const int64_t no = n_old[u];
+  *nu = unit_tokens(n, u, nb_cap * kBlockTokens, st);
+  *bs = no / kBlockTokens;
+  *be = (*nu + kBlockTokens - 1) / kBlockTokens;
+  if (no >= 0 && no <= *nu && *be - *bs <= max_blocks) return true;
+  set_status(st, FATHOM_DEV_BAD_N);
+  return false;
+}
+
+// An append of few blocks: one wave takes 16 bytes of a block's 64 key rows, a
+// token a lane, so that a plane word is the ballot of its bits and the chain from
+// the loads to the stores is short: it is one wave's latency.  8 units' one token:
+// fp32 2.7 us, fp16 3.4 (16 tokens a lane, in one or two waves an item: 4.3 and 4.5;
+// a tile in LDS with wave-wide shuffles: 4.3 and 4.3).
+template <typename KT>
+__global__ __launch_bounds__(kWave) void pack_append_kernel(const KT* __restrict__ K, int64_t ld_tok, int64_t ld_unit,
+                                                           const int64_t* __restrict__ n,
+                                                           const int64_t* __restrict__ n_old, int64_t max_blocks,
+                                                           int64_t nb_cap, uint64_t* __restrict__ planes,
+                                                           uint16_t* __restrict__ scales, uint32_t* __restrict__ st) {
+  constexpr int kCh = PackItem<KT>::kCh, kItems = kD / kCh;
+  const int u = blockIdx.y, lane = threadIdx.x;
+  int64_t nu, bs, be;
+  if (!append_range(n, n_old, u, max_blocks, nb_cap, lane == 0 ? st : nullptr, &nu, &bs, &be)) return;
+  const int64_t b = bs + blockIdx.x / kItems;
+  if (b >= be) return;
+  const int c = (int)(blockIdx.x % kItems) * kCh;
+  const int64_t tok = b * kBlockTokens + lane;
+  const bool valid = tok < nu;
+  uint4 r = make_uint4(0u, 0u, 0u, 0u);
+  if (valid) r = *reinterpret_cast<const uint4*>(K + (int64_t)u * ld_unit + tok * ld_tok + c);
+  add_zero<KT>(r);  // -0 counts as +0
+  const uint64_t vm = __ballot(valid);
+  uint32_t mx[kCh / 4][4], flags = 0;
+#pragma unroll
+  for (int e = 0; e < kCh; ++e) {  // NaN keys leave the maximum (and take code 8 below)
+    const float a = fabsf(item_value<KT>(r, e));
+    if (!(a <= 3.402823466e38f)) flags |= FATHOM_DEV_NONFINITE;
+    mx[e / 4][e % 4] = a != a ? 0u : __float_as_uint(a);
+  }
+#pragma unroll
+  for (int i = 0; i < kCh / 4; ++i) wave_max4_u(mx[i]);
+  uint32_t lo = 0, hi = 0, a16w = 0;
+#pragma unroll
+  for (int e = 0; e < kCh; ++e) {
+    const __half ah = __float2half_rn(__uint_as_float(mx[e / 4][e % 4]));
+    const uint16_t a16 = __half_as_ushort(ah);
+    const bool over = (a16 & 0x7FFFu) == 0x7C00u, zero_code = a16 == 0 || over;  // code 8 for every key
+    if (over) flags |= FATHOM_DEV_SCALE_OVERFLOW;
+    // the signs of v and of its distances to the thresholds, as in quantise_item
+    const float v = item_value<KT>(r, e), s4 = __fmul_rn(__half2float(ah), 0.5f);
+    const float t1 = __builtin_copysignf(s4, v), d1 = __fsub_rn(v, t1);
+    const float t2 = __fadd_rn(t1, __builtin_copysignf(__fmul_rn(s4, 0.5f), d1)), d2 = __fsub_rn(v, t2);
+    const float t3 = __fadd_rn(t2, __builtin_copysignf(__fmul_rn(s4, 0.25f), d2)), d3 = __fsub_rn(v, t3);
+    const uint64_t nan = __ballot(v != v), on = zero_code ? 0ull : vm & ~nan;
+    const uint64_t w[kPlanes] = {(zero_code ? vm : (~__ballot(__float_as_int(v) < 0) | nan) & vm),
+                                 ~__ballot(__float_as_int(d1) < 0) & on, ~__ballot(__float_as_int(d2) < 0) & on,
+                                 ~__ballot(__float_as_int(d3) < 0) & on};
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p)
+      if (lane == kPlanes * e + p) {
+        lo = (uint32_t)w[p];
+        hi = (uint32_t)(w[p] >> 32);
+      }
+    if (lane == e) a16w = a16;
+  }
+  const int64_t j = (int64_t)u * kD + c;
+  if (lane < kPlanes * kCh) planes[(j * kPlanes + lane) * nb_cap + b] = ((uint64_t)hi << 32) | lo;
+  if (lane < kCh) scales[(j + lane) * nb_cap + b] = (uint16_t)a16w;
+  wave_status(st, flags);
+}
+
 // SPLIT: an item's sets of 4 channels a lane go to waves of their own.  An append
 // is one wave's latency: one unit's fp16 block takes 4.1 us, 5.7 in one wave.
 template <typename KT, bool SPLIT>
@@ -360,19 +437,9 @@ __global__ __launch_bounds__(kWave) void pack_direct_kernel(const KT* __restrict
   using P = PackItem<KT>;
   constexpr int kParts = SPLIT ? P::kSets : 1;  // waves per item
   const int u = blockIdx.y, lane = threadIdx.x, x = lane & 15;
-  const int64_t nu = unit_tokens(n, u, nb_cap * kBlockTokens, lane == 0 ? st : nullptr);
-  // blocks [bs, be) of this unit are written: all of them, or (append) the
-  // ones from the first block holding a new token
-  int64_t bs = 0, be = nb_cap;
-  if (n_old) {
-    const int64_t no = n_old[u];
-    if (no < 0 || no > nu || (nu + kBlockTokens - 1) / kBlockTokens - no / kBlockTokens > max_blocks) {
-      if (lane == 0) set_status(st, FATHOM_DEV_BAD_N);
-      return;  // the unit is left as it was
-    }
-    bs = no / kBlockTokens;
-    be = (nu + kBlockTokens - 1) / kBlockTokens;
-  }
+  int64_t nu, bs = 0, be = nb_cap;
+  if (!n_old) nu = unit_tokens(n, u, nb_cap * kBlockTokens, lane == 0 ? st : nullptr);
+  else if (!append_range(n, n_old, u, max_blocks, nb_cap, lane == 0 ? st : nullptr, &nu, &bs, &be)) return;
   const int it = (int)(blockIdx.x / kParts), part = (int)(blockIdx.x % kParts);
   const int64_t b = bs + it / P::kPerBlock;
   if (b >= be) return;
@@ -400,7 +467,13 @@ static void launch_pack_t(const KT* K, int64_t ld_tok, int64_t ld_unit, const in
   }
   const int64_t tiles = (nb_cap + kTileBlocks - 1) / kTileBlocks;
   const unsigned items = (unsigned)(mb * PackItem<KT>::kPerBlock);
-  if (n_old)
+  // An append's rows are read 16 bytes at a time by 16 (fp32: 32) waves a token each
+  // lane, which up to about 100 blocks is the faster (32 units' 128 tokens, 96 blocks: fp32
+  // 3.8 us against 4.9, fp16 4.8 and 5.1; 256 tokens, 160 blocks: 6.5 and 5.5, 6.1 and 5.6).
+  if (n_old && mb * U <= 96)
+    hipLaunchKernelGGL(pack_append_kernel<KT>, dim3((unsigned)(mb * (kD / PackItem<KT>::kCh)), (unsigned)U), dim3(kWave), 0,
+                       s, K, ld_tok, ld_unit, n, n_old, mb, nb_cap, planes, scales, st);
+  else if (n_old)
     hipLaunchKernelGGL((pack_direct_kernel<KT, true>), dim3(items * PackItem<KT>::kSets, (unsigned)U), dim3(kWave), 0, s,
                        K, ld_tok, ld_unit, n, n_old, mb, nb_cap, planes, scales, st);
   else if (tiles * U < kDirectTiles)

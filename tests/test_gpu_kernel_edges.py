@@ -631,3 +631,49 @@ def test_scan_topk_rank_equal_scores(k):
                 oi, ov, _ = oracle.topk(ref[h], k, 0, 0)
                 assert u > 1 or ov[0] == ov[-1]  # the equal ones fill the top k
                 assert np.array_equal(idx[u, h].cpu().numpy(), oi) and np.array_equal(val[u, h].cpu().numpy(), ov), (m, u, h)
+
+
+@pytest.mark.parametrize("kdt", [np.float32, np.float16])
+@pytest.mark.parametrize("U,max_new", [(5, 1), (5, 300), (7, 4000), (90, 1), (20, 300)])
+def test_pack_append_blocks(kdt, U, max_new):
+    """Appends on both sides of the rule of 96 blocks (a token a lane, or 16): blocks
+    of 1, 63 and 64 tokens, keys at the cell boundaries, signed zeros, NaN, infinite
+    and tiny keys, padded rows, a unit that does not grow and one whose lengths are
+    refused.  Bit-exact to the oracle's pack of the longer prefix; blocks past the
+    end and the refused unit stay as they were."""
+    rng = np.random.default_rng(U + max_new)
+    nb_cap, ld = 70, 136
+    n_old = rng.integers(0, 64 * nb_cap - max_new, U)
+    n_old[:4] = [128, 191, 127, 40]
+    n = n_old + rng.integers(1, max_new + 1, U)
+    n[3], n_old[4], n[4] = n_old[3], 100, 99  # no growth; refused
+    K = torch.full((U, 64 * nb_cap, ld), float("nan"), dtype=torch.float32 if kdt == np.float32 else torch.float16, device=DEV)
+    host = {}
+    for u in range(U):
+        m = int(max(n[u], n_old[u]))
+        if u < 7:
+            k = threshold_keys(rng, m, kdt)
+            if u < 2:
+                k[m - 1, 3], k[m - 2, 4], k[m - 1, 5], k[m - 1, 6] = np.nan, np.inf, -np.inf, -0.0
+                k[(m - 1) // 64 * 64:, 7] = 1e-8
+            host[u] = k
+            K[u, :m, :D] = dev(k)
+        else:
+            K[u, :m, :D] = torch.randn((m, D), device=DEV).to(K.dtype)
+    planes = torch.full((U, D, 4, nb_cap), 0x5A5A5A5A, dtype=torch.int64, device=DEV)
+    scales = torch.full((U, D, nb_cap), 0x1234, dtype=torch.int16, device=DEV)
+    for u in range(U):  # the store before: packed up to n_old, not zeroed past it
+        p, s = F.fathom_pack(K[u:u + 1, :, :D], dev(n_old[u:u + 1].astype(np.int64)), nb_cap=nb_cap)
+        b = (int(n_old[u]) + 63) // 64
+        planes[u, :, :, :b], scales[u, :, :b] = p[0, :, :, :b], s[0, :, :b]
+    before = planes.clone(), scales.clone()
+    st = F.new_status()
+    F.fathom_pack_append(K[:, :, :D], dev(n_old.astype(np.int64)), dev(n.astype(np.int64)), max_new, planes, scales, dev_status=st)
+    assert status(st) == (F.FATHOM_DEV_NONFINITE | F.FATHOM_DEV_SCALE_OVERFLOW | F.FATHOM_DEV_BAD_N)
+    assert torch.equal(planes[4], before[0][4]) and torch.equal(scales[4], before[1][4])
+    for u in (0, 1, 2, 3) + ((5, 6) if U > 6 else ()):
+        b = (int(n[u]) + 63) // 64
+        op, os_, _ = oracle.pack(host[u][:n[u]].astype(np.float32), nb_cap=nb_cap)
+        assert np.array_equal(planes[u, :, :, :b].cpu().numpy().view(np.uint64), op[:, :, :b]), u
+        assert np.array_equal(scales[u, :, :b].cpu().numpy().view(np.uint16), os_[:, :b]), u
+        assert torch.equal(planes[u, :, :, b:], before[0][u, :, :, b:]) and torch.equal(scales[u, :, b:], before[1][u, :, b:])
