@@ -339,16 +339,32 @@ def test_sparse_attn_row_lists(k, U):
             assert np.abs(out[u] - ref).max() <= 1e-5 * np.abs(V[u].astype(np.float32)).max(), (u, sink)
 
 
+def filtered_rows(ws, U, G, k):
+    """Rows [U][G] that the filter served, from the workspace of a call: a threshold
+    and a survivor list that holds the top k.  Layout: a threshold a row, then a
+    256-byte line a row whose first word counts the survivors; the list's capacity
+    is twice min(2k + 2048, 16384)."""
+    R = U * G
+    tau = ws[: 4 * R].view(torch.float32).cpu().numpy()
+    at = (4 * R + 255) // 256 * 256
+    cnt = ws[at: at + 256 * R].view(torch.int32).view(R, 64)[:, 0].cpu().numpy()
+    return (np.isfinite(tau) & (cnt >= k) & (cnt <= 2 * min(2 * k + 2048, 16384))).reshape(U, G)
+
+
 @pytest.mark.parametrize("k", [1, 1000, 1024, 1025, 2048, 2049])
-def test_scan_topk_many_rows(k):
-    """112 rows: more than one round of the chip at 8 rank parts a row, so 1, 2 or 8
-    parts by k; a unit with many equal scores (keys drawn from four blocks), one
-    whose ends are inside a sampled quad (odd stride), and windows.  Bit-exact to
-    the oracle."""
+@pytest.mark.parametrize("U", [28, 36])
+def test_scan_topk_many_rows(U, k):
+    """112 and 144 rows: more than one round of the chip at 8 rank parts a row, so 1,
+    2 or 8 parts by rows and k; a unit with many equal scores (keys drawn from four
+    blocks), one whose ends are inside a sampled quad (odd stride), and windows.
+    Bit-exact to the oracle; the filter serves all but a few rows of the other units
+    from k = 1000 (the rank pass is reached, not only the exact rows; a threshold
+    misses by chance in one row of some thousands)."""
     rng = np.random.default_rng(k)
-    U, G, cap = 28, 4, 24003
+    G, cap = 4, 24003
     ns = rng.integers(16000, cap + 1, U)
     ns[0] = cap
+    torch.manual_seed(1000 * U + k)
     K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
     K[1] = K[1, :256].repeat(94, 1)[:cap]
     n = dev(ns.astype(np.int64))
@@ -356,10 +372,14 @@ def test_scan_topk_many_rows(k):
     q = rng.standard_normal((U, G, D)).astype(np.float16)
     var = np.exp(2 * rng.standard_normal((U, D))).astype(np.float32)
     d, _ = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, 48)
+    ws = torch.empty((F.fathom_scan_topk_workspace_size(U, G, 64 * planes.shape[-1], k),), dtype=torch.uint8, device=DEV)
     for lo, tail in [(0, 0), (4, 32)]:
         st = F.new_status()
-        idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, lo, tail, dev_status=st, max_unit_bits=48)
+        idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, lo, tail, ws=ws, dev_status=st, max_unit_bits=48)
         assert status(st) & ~F.FATHOM_DEV_TOPK_FALLBACK == 0
+        served = filtered_rows(ws, U, G, k)
+        served[1] = True
+        assert k == 1 or (~served).sum() <= 2
         for u in [0, 1, 2, 13, U - 1]:
             ref = oracle.scores_f32(planes[u].cpu().numpy().view(np.uint64), scales[u].cpu().numpy().view(np.uint16),
                                     int(ns[u]), q[u].astype(np.float32), d[u].cpu().numpy())
@@ -375,10 +395,13 @@ def test_scan_topk_more_than_4_heads(G, qdt, B):
     """5 to 8 query heads: the cell filter 4 heads at a time for every slice count
     (and units above the bound, which are computed exactly), beside a unit that is
     computed directly and an empty one; with and without a bound, which takes the
-    exact path.  Bit-exact to the oracle, and the fallback flag as documented."""
+    exact path.  Bit-exact to the oracle, and the fallback flag as documented; the
+    flag is raised for more than 4 heads either way, so that the filter served the
+    long units' rows, both fours of them, is read from the workspace."""
     rng = np.random.default_rng(G * B)
     ns = [40000, 23457, 2000, 0, 33000]
     U, cap, k = len(ns), 40000, 300
+    torch.manual_seed(G * B)
     K = torch.randn((U, cap, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
     n = dev(np.array(ns, np.int64))
     planes, scales = F.fathom_pack(K, n)
@@ -387,11 +410,13 @@ def test_scan_topk_more_than_4_heads(G, qdt, B):
     d, _ = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, B)
     P, S, dn = planes.cpu().numpy().view(np.uint64), scales.cpu().numpy().view(np.uint16), d.cpu().numpy()
     ref = [oracle.scores_f32(P[u], S[u], ns[u], q[u].astype(np.float32), dn[u]) for u in range(U)]
+    ws = torch.empty((F.fathom_scan_topk_workspace_size(U, G, 64 * planes.shape[-1], k),), dtype=torch.uint8, device=DEV)
     for lo, tail in [(0, 0), (4, 32)]:
         for bound in (min(B, 96), 0):
             st = F.new_status()
-            idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, lo, tail, dev_status=st, max_unit_bits=bound)
+            idx, val = F.fathom_scan_topk(planes, scales, n, dev(q), d, k, lo, tail, ws=ws, dev_status=st, max_unit_bits=bound)
             assert status(st) == (F.FATHOM_DEV_TOPK_FALLBACK | F.FATHOM_DEV_TOPK_SHORT)
+            assert (filtered_rows(ws, U, G, k)[[0, 1, 4]] == (B <= bound)).all(), (lo, bound)
             for u in range(U):
                 for h in range(G):
                     oi, ov, _ = oracle.topk(ref[u][h], k, lo, tail)
@@ -615,6 +640,7 @@ def test_scan_topk_rank_equal_scores(k):
     U, G, nb = 34, 4, 375
     n = dev(np.full(U, 64 * nb, np.int64))
     q = rng.standard_normal((U, G, D)).astype(np.float32)
+    torch.manual_seed(k)
     K = torch.randn((U, 64 * nb, D), device=DEV) * torch.exp(torch.randn((U, 1, D), device=DEV))
     d, _ = F.fathom_alloc_depths(dev(q), dev(np.ones((U, D), np.float32)), F.FATHOM_WATERFILL, 48)
     for m in (62, 70):
