@@ -297,11 +297,11 @@ size_t fathom_sparse_attn_workspace_size(int U, int G, int k, int n_sink, int n_
  *
  * fathom_klt_calibrate -- per unit: mu = mean of its n[u] keys, covariance
  * C = (1/n) sum (k - mu)(k - mu)^T (fp64 sums), and its eigen-decomposition
- * (fp32 one-sided Jacobi on the fp64 Cholesky factor, until the columns are
- * orthogonal to fp32 rounding; eigenvalues v^T C v in fp64, not below 0).  Columns
- * are ordered by eigenvalue, largest first (the paper orders by calibration score
- * variance, the same order for isotropic queries); each column's
- * largest-magnitude entry is positive.  A unit with n[u] = 0 gets mu = 0, V = I, lambda = 0.
+ * (fp32 one-sided Jacobi on the fp64 Cholesky factor, at most 16 sweeps, and a
+ * Newton step that makes the columns orthonormal to the rounding of their entries;
+ * eigenvalues v^T C v in fp64, not below 0).  Columns are ordered by eigenvalue,
+ * largest first (the paper orders by calibration score variance, the same order
+ * for isotropic queries); each column's largest-magnitude entry is positive.  A unit with n[u] = 0 gets mu = 0, V = I, lambda = 0.
  *   K        [U][n][D] keys (kdt), element (u, i, c) at K[u*ld_unit + i*ld_tok + c];
  *            ld_tok >= D, ld_unit >= 0; element-aligned.
  *   n        [U] int64 (device), 0 <= n[u] <= n_cap, else BAD_N and the unit is empty.

@@ -46,9 +46,9 @@
 // plan; (2) tau, only for the wide pass: per row the m-th largest
 // sample, m ~ 1.25 k sampled / eligible + 16 (the cell filter finds the same
 // tau itself); (3) the full pass: the cell filter, and the wide pass above
-// when launched; (4) select: 8 workgroups per row share out its top k
-// positions by a histogram of the survivors' scores and order their share in
-// LDS, and rows with at most 2k + 2048 eligible keys, and rows whose
+// when launched; (4) select: 8 workgroups per row (1 or 2 in a pass of their own
+// where the rows are many) share out its top k positions by a histogram of the
+// survivors' scores and order their share in LDS, and rows with at most 2k + 2048 eligible keys, and rows whose
 // survivors cannot give the top k (fewer than k reached tau, the list
 // overflowed, or too many equal scores for one workgroup's share;
 // FATHOM_DEV_TOPK_FALLBACK), are computed from exact scores by a chunked
@@ -1176,9 +1176,9 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 // in [z K / parts, (z + 1) K / parts) and orders their survivors in LDS; only
 // survivors sharing a sub-bucket are compared.  Composites are distinct (they
 // carry the index), so the positions are a permutation.  A row whose share
-// for some part exceeds kRankCap (many equal scores) is computed exactly by
-// its own parts instead; every part reaches the same decision from the same
-// histogram.  The parts of a row run on one XCD (workgroups are dealt to the
+// for some part exceeds the part's LDS (many equal scores) is computed exactly
+// instead, by its own parts in the select pass and by the exact rows after the
+// rank pass; every part reaches the same decision from the same histogram.  The parts of a row run on one XCD (workgroups are dealt to the
 // 8 XCDs in turn), so the list is read once into that XCD's L2.
 // Every part reads the whole list and builds the whole histogram, so with more
 // rows than one round of the chip holds at 8 parts (3 workgroups a CU) a row has
@@ -1196,7 +1196,7 @@ constexpr int kRankRound = 3 * 256;
 constexpr int kRankCapFew = 7936;
 constexpr int kRankThreads = 512;   // the rank pass's workgroup (the select pass's is kXThreads)
 constexpr int kRankPer = 8;      // survivors per thread read with the count (the rest re-read)
-constexpr int kRankCap = 4096;   // survivors one part orders at most
+constexpr int kRankCap = 4096;   // survivors one of 8 parts orders at most, and of one sub-bucket
 constexpr int kRankSub = 4096;   // sub-buckets at most
 constexpr int kRankXcd = 8;
 template <int T, int kRankParts>
@@ -1209,8 +1209,8 @@ struct RankShared {
   uint32_t s_same;  // a sub-bucket has more than kRankCap keys (fewer than 8 parts)
 };
 // Part z of row r (every thread of the workgroup calls it, for a row whose
-// list holds its top k); grp and hist are LDS areas of kRankCap composites
-// and kRankSub + 1 counts, 16-byte aligned.  Returns true when a part's share
+// list holds its top k); grp and hist are LDS areas of kRankCap (fewer than 8
+// parts: kRankCapFew) composites and kRankSub + 1 counts, 16-byte aligned.  Returns true when a part's share
 // exceeds its area after all (many equal scores): the row is then computed
 // exactly.
 template <int T, int kRankParts>

@@ -9,9 +9,10 @@
 //                     shifted by the unit's first, on the fp64 matrix cores.
 //   klt_reduce_kernel the chunks' sums in chunk order: mean and covariance.
 //   klt_eig_kernel    one workgroup per unit: Cholesky factor in fp64, cyclic
-//                     one-sided Jacobi on it in fp32, eigenvalues in fp64, and
-//                     finally the columns ordered by eigenvalue (descending)
-//                     with each column's largest-magnitude entry made positive.
+//                     one-sided Jacobi on it in fp32, one Newton step to an
+//                     orthonormal basis, eigenvalues in fp64, and finally the
+//                     columns ordered by eigenvalue (descending) with each
+//                     column's largest-magnitude entry made positive.
 // fathom_klt_rotate_keys (prefill) and fathom_klt_rotate_q (per step) compute
 // in fp32 in a fixed order: d_j = fl(k_j - mu_j) (no mean for q), then for
 // j = 0 .. D-1: acc_c = fl(acc_c + fl(d_j V[j][c])), no fused multiply-add, so
@@ -25,7 +26,10 @@ namespace fathom {
 constexpr size_t kCalUnitBytes = (size_t)32 * kD * (kD + 1) * sizeof(double);  // calibration workspace of one unit
 constexpr int kCalChunks = 54;        // token chunks per unit in the calibration sums, at most (they fit the above)
 constexpr int kEigThreads = 512;
-constexpr int kJacobiSweeps = 16;     // at most; covariances of 128 channels take 3 to 8
+// At most.  128 channels take 2 to 7 sweeps for fewer keys than 8, 8 to 10 for
+// eigenvalues over up to four decades, 11 to 14 over nine and up to all 16 over more
+// than ten, where what is left is below the rounding of the largest.
+constexpr int kJacobiSweeps = 16;
 // A pair whose cosine is below 1.4e-6 (the rounding of a dot product) is not
 // rotated.  The sweeps end when every rotation of a sweep was of a cosine below
 // 1e-4 by a tangent below 2^-10: what the up to 127 rotations of a column leave
