@@ -1178,8 +1178,9 @@ __device__ __forceinline__ float key_to_score(uint32_t key) {
 // carry the index), so the positions are a permutation.  A row whose share
 // for some part exceeds the part's LDS (many equal scores) is computed exactly
 // instead, by its own parts in the select pass and by the exact rows after the
-// rank pass; every part reaches the same decision from the same histogram.  The parts of a row run on one XCD (workgroups are dealt to the
-// 8 XCDs in turn), so the list is read once into that XCD's L2.
+// rank pass; every part reaches the same decision from the same histogram.  The
+// parts of a row run on one XCD (workgroups are dealt to the 8 XCDs in turn), so
+// the list is read once into that XCD's L2.
 // Every part reads the whole list and builds the whole histogram, so with more
 // rows than one round of the chip holds at 8 parts (3 workgroups a CU) a row has
 // one part up to k = 1024 and two up to k = 2048 (two as well up to 128 rows,

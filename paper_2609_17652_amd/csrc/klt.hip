@@ -26,7 +26,7 @@ namespace fathom {
 constexpr size_t kCalUnitBytes = (size_t)32 * kD * (kD + 1) * sizeof(double);  // calibration workspace of one unit
 constexpr int kCalChunks = 54;        // token chunks per unit in the calibration sums, at most (they fit the above)
 constexpr int kEigThreads = 512;
-// At most.  128 channels take 2 to 7 sweeps for fewer keys than 8, 8 to 10 for
+// At most.  128 channels take 2 to 6 sweeps for fewer than 8 keys, 4 to 10 for
 // eigenvalues over up to four decades, 11 to 14 over nine and up to all 16 over more
 // than ten, where what is left is below the rounding of the largest.
 constexpr int kJacobiSweeps = 16;
