@@ -298,17 +298,18 @@ size_t fathom_sparse_attn_workspace_size(int U, int G, int k, int n_sink, int n_
  * fathom_klt_calibrate -- per unit: mu = mean of its n[u] keys, covariance
  * C = (1/n) sum (k - mu)(k - mu)^T (fp64 sums), and its eigen-decomposition
  * (fp32 one-sided Jacobi on the fp64 Cholesky factor, at most 16 sweeps, and a
- * Newton step that makes the columns orthonormal to the rounding of their entries;
- * eigenvalues v^T C v in fp64, not below 0).  Columns are ordered by eigenvalue,
- * largest first (the paper orders by calibration score variance, the same order
- * for isotropic queries); each column's largest-magnitude entry is positive.  A unit with n[u] = 0 gets mu = 0, V = I, lambda = 0.
+ * refinement in fp64 to the rounding of the columns' entries; eigenvalues
+ * v^T C v in fp64, not below 0).  Columns are ordered by eigenvalue, largest first
+ * (the paper orders by calibration score variance, the same order for isotropic
+ * queries); each column's largest-magnitude entry is positive.  A unit with
+ * n[u] = 0 gets mu = 0, V = I, lambda = 0.
  *   K        [U][n][D] keys (kdt), element (u, i, c) at K[u*ld_unit + i*ld_tok + c];
  *            ld_tok >= D, ld_unit >= 0; element-aligned.
  *   n        [U] int64 (device), 0 <= n[u] <= n_cap, else BAD_N and the unit is empty.
  *   mu       [U][D] fp32, V [U][D][D] fp32 (V[u][j][c]: entry j of eigenvector c),
  *   lam      [U][D] fp32 -- written.
  *   ws       device workspace of fathom_klt_calibrate_workspace_size(U) bytes,
- *            256-byte aligned (chunk partial sums; contents on entry unused).
+ *            256-byte aligned (chunk sums, the basis; contents on entry unused).
  * One-time per store (prefill); about 4 MiB of workspace per unit.
  */
 fathom_status fathom_klt_calibrate(const void* K, fathom_dtype kdt, int64_t ld_tok, int64_t ld_unit,

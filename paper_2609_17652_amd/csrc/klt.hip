@@ -9,9 +9,9 @@
 //                     shifted by the unit's first, on the fp64 matrix cores.
 //   klt_reduce_kernel the chunks' sums in chunk order: mean and covariance.
 //   klt_eig_kernel    one workgroup per unit: Cholesky factor in fp64, cyclic
-//                     one-sided Jacobi on it in fp32, one Newton step to an
-//                     orthonormal basis, eigenvalues in fp64, and finally the
-//                     columns ordered by eigenvalue (descending) with each
+//                     one-sided Jacobi on it in fp32.
+//   klt_refine_kernel the basis refined and the eigenvalues, in fp64.
+//   klt_order_kernel  the columns ordered by eigenvalue (descending), with each
 //                     column's largest-magnitude entry made positive.
 // fathom_klt_rotate_keys (prefill) and fathom_klt_rotate_q (per step) compute
 // in fp32 in a fixed order: d_j = fl(k_j - mu_j) (no mean for q), then for
@@ -36,6 +36,9 @@ constexpr int kJacobiSweeps = 16;
 // of its other pairs' cosines is then about sqrt(127) * 1e-7.
 constexpr float kJacobiSkip2 = 2e-12f, kJacobiTol2 = 1e-8f, kJacobiTan = 0x1p-10f;
 constexpr double kCholShift = 1e-7;   // of the trace
+// Rotations of the refinement are left out from this size on (its square stays in
+// V^T V - I), and between eigenvalues closer than this share of the trace.
+constexpr double kRefineMax = 0x1p-13, kRefineGap = 1e-10;
 constexpr int kRotThreads = 256;
 constexpr int kRotTokens = 4;         // tokens a wave rotates at a time
 
@@ -272,8 +275,7 @@ __global__ __launch_bounds__(256) void klt_reduce_kernel(const KT* __restrict__ 
 // into multiples of the eigenvectors: one 128 x 128 fp32 matrix, no separate
 // basis, and only columns are ever combined, so a pair of columns stays in the
 // registers of 8 lanes (16 rows each) and its dot product is 16 multiply-adds
-// and three DPP additions.  The eigenvalues are Rayleigh quotients of the
-// result with the fp64 covariance.
+// and three DPP additions.
 //
 // The order of rotations: the 128 columns are 16 blocks of 8; each of the 8
 // waves holds two blocks, one as "top" and one as "bottom" columns, lane group i
@@ -402,6 +404,19 @@ __device__ __forceinline__ bool rotate_pair(JacobiCol& p, JacobiCol& q) {
   return big;
 }
 
+// What the decomposition's kernels hand on of a unit (in the chunks' sums' place).
+struct alignas(256) EigUnit {
+  float basis[kD * kD];    // unit columns, row-major
+  float refined[kD * kD];  // after the refinement
+  double approx[kD];       // eigenvalues to fp32 rounding
+  float lam[kD];           // Rayleigh quotients
+};
+static_assert(kD * kD * sizeof(double) + sizeof(EigUnit) <= kCalUnitBytes, "calibration workspace");
+
+// A basis in LDS as rows: every 4 rows shift their 4-column groups, so that a
+// column's reads use other banks.
+__device__ __forceinline__ int basis_col(int row, int col) { return col ^ (4 * ((row >> 2) & 7)); }
+
 // Columns in LDS: 128 rows each; the 32-row quarters of odd columns change
 // places in pairs, so that two columns' 16-byte reads use all banks.
 __device__ __forceinline__ int col_addr(int col, int quarter, int li) {
@@ -427,12 +442,9 @@ __device__ __forceinline__ void store_col(float* X, int col, int li, const Jacob
                     __fmul_rn(c.v[4 * i + 2], c.scale), __fmul_rn(c.v[4 * i + 3], c.scale));
 }
 
-__global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* __restrict__ cov,
-                                                                float* __restrict__ V_out,
-                                                                float* __restrict__ lam_out) {
+__global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* __restrict__ cov, EigUnit* __restrict__ eig) {
   __shared__ __attribute__((aligned(16))) float X[2][kD * kD];  // columns; at the end one holds the basis as rows
-  __shared__ double colj[kD], diag[kD], lam[kD];
-  __shared__ int order[kD];
+  __shared__ double colj[kD], diag[kD];
   __shared__ int again[2];
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* Cu = cov + (int64_t)u * kD * kD;
@@ -452,10 +464,10 @@ __global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* _
   double tr = diag[lane] + diag[lane + 64];
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) tr += __shfl_xor(tr, m, kWave);
-  float* Vo = V_out + (int64_t)u * kD * kD;
+  EigUnit& out = eig[u];
   if (tr == 0.0) {  // no keys, or all equal: every basis is one, the identity is given
-    for (int e = tid; e < kD * kD; e += kEigThreads) Vo[e] = e / kD == e % kD ? 1.0f : 0.0f;
-    if (tid < kD) lam_out[(int64_t)u * kD + tid] = 0.0f;
+    for (int e = tid; e < kD * kD; e += kEigThreads) out.basis[e] = e / kD == e % kD ? 1.0f : 0.0f;
+    if (tid < kD) out.approx[tid] = 0.0;
     return;
   }
   // ---- pivoted Cholesky of C / trace + delta I; the factor's column k goes to X[0] ----
@@ -563,7 +575,8 @@ __global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* _
     if (tid == 0) again[(sweep & 1) ^ 1] = 0;
   }
   __syncthreads();
-  // ---- unit columns, as rows of the basis in the other buffer ----
+  // ---- unit columns, as rows of the basis (through the other buffer), and their
+  // eigenvalues to fp32 rounding ----
   const float* Xf = X[buf];
   float* Vs = X[buf ^ 1];
 #pragma unroll
@@ -582,118 +595,136 @@ __global__ __launch_bounds__(kEigThreads, 2) void klt_eig_kernel(const double* _
 #pragma unroll
     for (int e = 0; e < kColRows; ++e) {
       const int row = 32 * (e >> 2) + 4 * li + (e & 3);
-      Vs[row * kD + (col ^ (4 * ((row >> 2) & 7)))] = (float)((double)v[e] * is);
+      Vs[row * kD + basis_col(row, col)] = (float)((double)v[e] * is);
     }
+    if (li == 0) out.approx[col] = (s - kCholShift) * tr;
   }
   __syncthreads();
-  // ---- V <- V (3 I - V^T V) / 2 = V + V E: the rotations leave the columns
-  // orthogonal to the rounding of their dot products (|V^T V - I|_F 5e-5), one
-  // Newton step to that of V's entries (1e-6).  E = (I - V^T V) / 2 in fp64, wave
-  // w its block row w, the blocks 4 to 7 to the right by symmetry; V E, a
-  // correction of 1e-6, in fp32. ----
-  {
-    const int i16 = lane & 15, g = lane >> 4;
-    auto at = [&](int row, int col) { return Vs[row * kD + (col ^ (4 * ((row >> 2) & 7)))]; };
-    float* E = X[buf];
-    v4f64 e[5];
+  for (int e = tid; e < kD * kD; e += kEigThreads) out.basis[e] = Vs[(e / kD) * kD + basis_col(e / kD, e % kD)];
+}
+
+// ---- eigenvalues, and one step of Ogita and Aishima's refinement ("Iterative
+// refinement for symmetric eigenvalue decomposition", 2018).  The rotations leave
+// the rounding of their 1000 fp32 steps: |V^T V - I|_F 5e-5 and an off-diagonal of
+// V^T C V of 7e-6 of |C|_F.  With R = I - V^T V and S = V^T C V in fp64,
+//   V <- V (I + R / 2 + X),  X_ij = (S_ij + (l_i + l_j) R_ij / 2) / (l_j - l_i),
+// leaves 4e-7 and 4e-8 (under 2e-6 where many eigenvalues are close), the rounding
+// of V's entries.  X is left out
+// where it is not small: close eigenvalues, whose vectors may be any of their plane.
+// Workgroup x takes columns 16 x .. 16 x + 15 and wave t the rows 16 t .. of C V (C is
+// symmetric: its rows serve as the A operand's columns), R, S and the result; C V goes
+// through LDS as the B operand of S.  Bound by the latency of its operands: 16 us for 8
+// units (on the CU of the kernel above 22, and its code cost the rotations a tenth of
+// their time).
+constexpr int kRefThreads = 512;
+constexpr int kRefSteps = kD / 4;
+__global__ __launch_bounds__(kRefThreads) void klt_refine_kernel(const double* __restrict__ cov, EigUnit* __restrict__ eig) {
+  __shared__ __attribute__((aligned(16))) float Vs[kD * kD];
+  __shared__ double cv[kD * 16], la[kD];
+  __shared__ float E[kD * 16];
+  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, g = lane >> 4, t = tid >> 6;
+  const int c = 16 * (int)blockIdx.x + i16;
+  const double* Cu = cov + (int64_t)u * kD * kD;
+  EigUnit& out = eig[u];
+  double cu[kRefSteps];
 #pragma unroll
-    for (int t = 0; t < 5; ++t) e[t] = (v4f64){0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int k = 0; k < kD; k += 4) {
-      const double a = (double)at(k + g, 16 * wave + i16);
+  for (int s = 0; s < kRefSteps; ++s) cu[s] = Cu[(4 * s + g) * kD + 16 * t + i16];
 #pragma unroll
-      for (int t = 0; t < 5; ++t)
-        e[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)at(k + g, 16 * ((wave + t) & 7) + i16), e[t], 0, 0, 0);
-    }
+  for (int x = 0; x < kD * kD / 4 / kRefThreads; ++x) {
+    const int e = 4 * (tid + x * kRefThreads), row = e / kD;
+    *reinterpret_cast<float4*>(&Vs[row * kD + basis_col(row, e % kD)]) = *reinterpret_cast<const float4*>(&out.basis[e]);
+  }
+  if (tid < kD) la[tid] = out.approx[tid];
+  __syncthreads();
+  auto at = [&](int row, int col) { return Vs[row * kD + basis_col(row, col)]; };
+  v4f64 w = {0.0, 0.0, 0.0, 0.0}, rr = w, ss = w;
 #pragma unroll
-    for (int t = 0; t < 5; ++t)
+  for (int s = 0; s < kRefSteps; ++s) w = __builtin_amdgcn_mfma_f64_16x16x4f64(cu[s], (double)at(4 * s + g, c), w, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * wave + 4 * r + g, col = 16 * ((wave + t) & 7) + i16;
-        const float v = (float)(0.5 * ((row == col ? 1.0 : 0.0) - e[t][r]));
-        E[row * kD + col] = v;
-        if (t > 0 && t < 4) E[col * kD + row] = v;
-      }
-    __syncthreads();
-    v4f32 d[8];
+  for (int r = 0; r < 4; ++r) cv[(16 * t + 4 * r + g) * 16 + i16] = w[r];
+  __syncthreads();
+#pragma unroll 8
+  for (int k = g; k < kD; k += 4) {
+    const double y = (double)at(k, 16 * t + i16);
+    rr = __builtin_amdgcn_mfma_f64_16x16x4f64(y, (double)at(k, c), rr, 0, 0, 0);
+    ss = __builtin_amdgcn_mfma_f64_16x16x4f64(y, cv[k * 16 + i16], ss, 0, 0, 0);
+  }
+  double tr = la[lane] + la[lane + 64];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) d[t] = (v4f32){0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-    for (int k = 0; k < kD; k += 4) {
-      const float b = E[(k + g) * kD + 16 * wave + i16];
+  for (int m = 32; m >= 1; m >>= 1) tr += __shfl_xor(tr, m, kWave);
+  const double lj = la[c];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(16 * t + i16, k + g), b, d[t], 0, 0, 0);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * t + 4 * g + r;
-        float* v = &Vs[row * kD + ((16 * wave + i16) ^ (4 * ((row >> 2) & 7)))];
-        *v = __fadd_rn(*v, d[t][r]);
-      }
+  for (int r = 0; r < 4; ++r) {
+    const int i = 16 * t + 4 * r + g;
+    const double h = 0.5 * ((i == c ? 1.0 : 0.0) - rr[r]), gap = lj - la[i];
+    const double q = __fma_rn(la[i] + lj, h, ss[r]);
+    E[i * 16 + i16] = (float)(fabs(gap) > kRefineGap * tr && fabs(q) < kRefineMax * fabs(gap) ? h + q / gap : h);
+    // The Rayleigh quotient is that of the refined vector too (the step is of first
+    // order).  A covariance has no negative eigenvalue: a null direction's quotient is
+    // rounding error of either sign, and a negative variance is no input to the depth
+    // allocation (the test leaves a NaN as it is).
+    if (i == c) out.lam[c] = ss[r] < 0.0 ? 0.0f : (float)(ss[r] / rr[r]);
   }
   __syncthreads();
-  // ---- eigenvalues: v^T C v / v^T v in fp64; wave w forms C V for columns
-  // 16 w .. 16 w + 15 (C is symmetric: its rows serve as the A operand's columns) ----
-  {
-    const int i16 = lane & 15, g = lane >> 4, c = 16 * wave + i16;
-    auto basis = [&](int row) { return (double)Vs[row * kD + (c ^ (4 * ((row >> 2) & 7)))]; };
-    v4f64 w[8];
+  v4f32 d = {0.0f, 0.0f, 0.0f, 0.0f};  // V (R / 2 + X), a correction of 1e-6, in fp32
+#pragma unroll 8
+  for (int k = g; k < kD; k += 4) d = __builtin_amdgcn_mfma_f32_16x16x4f32(at(16 * t + i16, k), E[k * 16 + i16], d, 0, 0, 0);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) w[t] = (v4f64){0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int k = 0; k < kD; k += 4) {
-      const double b = basis(k + g);
-#pragma unroll
-      for (int t = 0; t < 8; ++t)
-        w[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Cu[(k + g) * kD + 16 * t + i16], b, w[t], 0, 0, 0);
-    }
-    double num = 0.0, den = 0.0;
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const double v = basis(16 * t + 4 * r + g);
-        num = __fma_rn(v, w[t][r], num);
-        den = __fma_rn(v, v, den);
-      }
-    num += __shfl_xor(num, 16, kWave);
-    den += __shfl_xor(den, 16, kWave);
-    num += __shfl_xor(num, 32, kWave);
-    den += __shfl_xor(den, 32, kWave);
-    // a covariance has no negative eigenvalue: a null direction's quotient is
-    // rounding error of either sign, and a negative variance is no input to the
-    // depth allocation (the test leaves a NaN as it is)
-    const double w0 = num / den;
-    if (g == 0) lam[c] = w0 < 0.0 ? 0.0 : w0;
+  for (int r = 0; r < 4; ++r) {
+    const int row = 16 * t + 4 * g + r;
+    out.refined[row * kD + c] = __fadd_rn(at(row, c), d[r]);
   }
+}
+
+// Columns by eigenvalue (descending, ties by position), each with its
+// largest-magnitude entry (the first of equal ones) positive.  Four threads a column.
+__global__ __launch_bounds__(kEigThreads) void klt_order_kernel(const EigUnit* __restrict__ eig, float* __restrict__ V_out,
+                                                                float* __restrict__ lam_out) {
+  __shared__ float Vs[kD * (kD + 1)], lam[kD];
+  __shared__ int order[kD];
+  const int u = blockIdx.x, tid = threadIdx.x;
+  const EigUnit& in = eig[u];
+#pragma unroll
+  for (int x = 0; x < kD * kD / kEigThreads; ++x) {
+    const int e = tid + x * kEigThreads;
+    Vs[(e / kD) * (kD + 1) + e % kD] = in.refined[e];
+  }
+  if (tid < kD) lam[tid] = in.lam[tid];
   __syncthreads();
-  // ---- order by eigenvalue (descending, ties by position), fix signs, write ----
-  if (tid < kD) {
-    const int c = tid;
-    const float lc = (float)lam[c];
-    int rank = 0;
-    for (int x = 0; x < kD; ++x) {
-      const float lx = (float)lam[x];
-      rank += (lx > lc) || (lx == lc && x < c);
+  const int c = tid >> 2, part = tid & 3;
+  const float lc = lam[c];
+  int rank = 0, first = 0;
+  float best = -1.0f, at = 0.0f;
+#pragma unroll 8
+  for (int i = 32 * part; i < 32 * part + 32; ++i) {
+    rank += (lam[i] > lc) || (lam[i] == lc && i < c);
+    const float v = Vs[i * (kD + 1) + c];
+    if (fabsf(v) > best) {
+      best = fabsf(v);
+      at = v;
+      first = i;
     }
-    float best = -1.0f, at = 0.0f;
-    for (int i = 0; i < kD; ++i) {
-      const float v = Vs[i * kD + (c ^ (4 * ((i >> 2) & 7)))];
-      if (fabsf(v) > best) {
-        best = fabsf(v);
-        at = v;
-      }
+  }
+#pragma unroll
+  for (int m = 1; m < 4; m <<= 1) {
+    rank += __shfl_xor(rank, m, kWave);
+    const float ob = __shfl_xor(best, m, kWave), oa = __shfl_xor(at, m, kWave);
+    const int of = __shfl_xor(first, m, kWave);
+    if (ob > best || (ob == best && of < first)) {
+      best = ob;
+      at = oa;
+      first = of;
     }
+  }
+  if (part == 0) {
     order[rank & (kD - 1)] = at < 0.0f ? c | kD : c;
     lam_out[(int64_t)u * kD + (rank & (kD - 1))] = lc;
   }
   __syncthreads();
+  float* Vo = V_out + (int64_t)u * kD * kD;
   for (int e = tid; e < kD * kD; e += kEigThreads) {
-    const int i = e / kD, o = order[e % kD];
-    const float v = Vs[i * kD + ((o & (kD - 1)) ^ (4 * ((i >> 2) & 7)))];
+    const int o = order[e % kD];
+    const float v = Vs[(e / kD) * (kD + 1) + (o & (kD - 1))];
     Vo[e] = (o & kD) ? -v : v;
   }
 }
@@ -857,7 +888,10 @@ fathom_status launch_klt_calibrate(const void* K, fathom_dtype kdt, int64_t ld_t
     hipLaunchKernelGGL(klt_reduce_kernel<float>, gr, dim3(256), 0, s, Kf, ld_unit, n, n_cap, nch, part, cov, mu);
   else
     hipLaunchKernelGGL(klt_reduce_kernel<__half>, gr, dim3(256), 0, s, Kh, ld_unit, n, n_cap, nch, part, cov, mu);
-  hipLaunchKernelGGL(klt_eig_kernel, dim3((unsigned)U), dim3(kEigThreads), 0, s, cov, V, lam);
+  EigUnit* eig = reinterpret_cast<EigUnit*>(part);  // the chunks' sums are read by then
+  hipLaunchKernelGGL(klt_eig_kernel, dim3((unsigned)U), dim3(kEigThreads), 0, s, cov, eig);
+  hipLaunchKernelGGL(klt_refine_kernel, dim3(kD / 16, (unsigned)U), dim3(kRefThreads), 0, s, cov, eig);
+  hipLaunchKernelGGL(klt_order_kernel, dim3((unsigned)U), dim3(kEigThreads), 0, s, eig, V, lam);
   FATHOM_LAUNCH_CHECK();
   return FATHOM_OK;
 }

@@ -505,8 +505,11 @@ def spectrum_keys(rng, kind, n):
 @pytest.mark.parametrize("kind", ["decaying", "isotropic", "steep", "outlier"])
 def test_calibrate_orthonormal(kind):
     """The basis is orthonormal to the rounding of its entries, so that (qV).(kV)
-    is q.k.  Bound: entries rounded to fp32 (2^-24 relative) move the dot product
-    of two unit columns by at most 2^-23, so |V^T V - I|_F <= 128 * 2^-23."""
+    is q.k, and decorrelates the keys to it.  Bounds: entries rounded to fp32 (2^-24
+    relative) move the dot product of two unit columns by at most 2^-23, so
+    |V^T V - I|_F <= 128 * 2^-23, and V by at most 2^-24 sqrt(128) in the 2-norm of its
+    entries, so the off-diagonal of V^T C V by twice that share of |C|_F (twice more
+    where close eigenvalues leave rotations out: the isotropic covariances)."""
     rng = np.random.default_rng(len(kind))
     ns = [6000, 3001, 129, 40, 2]
     K = np.zeros((len(ns), max(ns), D), np.float32)
@@ -516,6 +519,11 @@ def test_calibrate_orthonormal(kind):
     V = V.cpu().numpy().astype(np.float64)
     for u, n in enumerate(ns):
         assert np.linalg.norm(V[u].T @ V[u] - np.eye(D)) <= D * 2.0 ** -23, (u, n)
+        x = K[u, :n].astype(np.float64) - K[u, :n].astype(np.float64).mean(0)
+        C = x.T @ x / n
+        W = V[u].T @ C @ V[u]
+        off = np.linalg.norm(W - np.diag(np.diag(W))) / np.linalg.norm(C)
+        assert off <= (4 if kind == "isotropic" else 2) * 2.0 ** -24 * np.sqrt(D), (u, n, off)
 
 
 def test_calibrate_few_keys():
