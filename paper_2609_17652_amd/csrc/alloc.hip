@@ -23,6 +23,9 @@ __device__ __forceinline__ float load_q_as(const void* q, int64_t i) {
   return ((const __attribute__((address_space(1))) float*)q)[i];
 }
 
+// Outside the defined inputs, in the order of their bit patterns as doubles: above
+// every candidate.
+constexpr uint32_t kKeyInf = 0xFFFFFFFDu, kKeyNan = 0xFFFFFFFEu, kKeyNeg = 0xFFFFFFFFu;
 constexpr int kExpBias = 160;  // a candidate's exponent, -156 .. 126, plus this fits 9 bits and is not 0
 
 __device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
@@ -71,12 +74,12 @@ __global__ __launch_bounds__(kWave) void alloc_waterfill_kernel(const void* __re
     const float g = __fmul_rn(s, r ? v1 : v0);
     const bool fine = g >= 0.0f && g <= 3.402823466e38f;
     if (!fine) flags |= FATHOM_DEV_NONFINITE;
+    const uint32_t odd = g != g ? kKeyNan : g < 0.0f ? kKeyNeg : kKeyInf;
     const uint64_t w = (uint64_t)__double_as_longlong((double)g);  // subnormal g is normal here
     const uint32_t k0 = (uint32_t)(w >> 29) - ((uint32_t)(1023 - kExpBias) << 23);  // (exponent + kExpBias, mantissa)
 #pragma unroll
     for (int m = 1; m <= 4; ++m) {
-      // outside the defined inputs: above every candidate
-      key[r][m - 1] = !fine ? 0xFFFFFFFFu : g == 0.0f ? 0u : k0 - ((uint32_t)(2 * m - 1) << 23);
+      key[r][m - 1] = !fine ? odd : g == 0.0f ? 0u : k0 - ((uint32_t)(2 * m - 1) << 23);
       any |= key[r][m - 1];
       all &= key[r][m - 1];
     }
@@ -105,6 +108,7 @@ __global__ __launch_bounds__(kWave) void alloc_waterfill_kernel(const void* __re
       }
     }
   }
+  T = min(T, kKeyNan);  // a water line is no negative value: at NaN
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     int t = 0;
@@ -114,7 +118,10 @@ __global__ __launch_bounds__(kWave) void alloc_waterfill_kernel(const void* __re
   }
   if (lane == 0 && theta) {
     const uint64_t w = ((uint64_t)T + ((uint64_t)(1023 - kExpBias) << 23)) << 29;
-    theta[u] = T == 0u ? 0.0f : T == 0xFFFFFFFFu ? __builtin_huge_valf() : (float)__longlong_as_double((long long)w);
+    theta[u] = T == 0u         ? 0.0f
+               : T == kKeyInf ? __builtin_huge_valf()
+               : T == kKeyNan ? __builtin_nanf("")
+                              : (float)__longlong_as_double((long long)w);
   }
   uint32_t f = flags;
 #pragma unroll

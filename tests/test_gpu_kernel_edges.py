@@ -711,3 +711,37 @@ def test_pack_append_blocks(kdt, U, max_new):
         assert np.array_equal(planes[u, :, :, :b].cpu().numpy().view(np.uint64), op[:, :, :b]), u
         assert np.array_equal(scales[u, :, :b].cpu().numpy().view(np.uint16), os_[:, :b]), u
         assert torch.equal(planes[u, :, :, b:], before[0][u, :, :, b:]) and torch.equal(scales[u, :, b:], before[1][u, :, b:])
+
+
+@pytest.mark.parametrize("G", [1, 5])
+def test_alloc_depths_nonfinite(G):
+    """Importances outside the defined inputs stand above every candidate, infinite
+    ones below NaN and those below negative ones (as their bit patterns do): the
+    channels above the water line keep 4 planes, and a water line among them is
+    infinite or NaN.  Three such channels of each kind, budgets that put the line
+    into every group; NONFINITE is raised."""
+    rng = np.random.default_rng(G)
+    q = rng.standard_normal((1, G, D)).astype(np.float32)
+    var = np.exp(rng.standard_normal((1, D))).astype(np.float32)
+    neg, nan, inf = [3, 64, 127], [0, 65, 70], [5, 63, 126]
+    var[0, neg], var[0, nan], var[0, inf] = -1.0, np.nan, np.inf
+    rest = var.copy()
+    rest[0, neg + nan + inf] = 0.0
+    for B in (0, 11, 12, 23, 24, 35, 36, 60, 511):
+        st = F.new_status()
+        d, th = F.fathom_alloc_depths(dev(q), dev(var), F.FATHOM_WATERFILL, B, dev_status=st)
+        d, th = d.cpu().numpy()[0], float(th.item())
+        assert status(st) == F.FATHOM_DEV_NONFINITE
+        want = np.zeros(D, np.uint8)
+        want[neg] = 4
+        if B < 24:
+            assert np.isnan(th), B
+        elif B < 36:
+            want[nan] = 4
+            assert th == np.inf, B
+        else:
+            od, oth, _ = oracle.alloc_waterfill(q[0], rest[0], B - 36)
+            want = od.copy()
+            want[neg + nan + inf] = 4
+            assert th == np.float32(oth), B
+        assert np.array_equal(d, want), B
